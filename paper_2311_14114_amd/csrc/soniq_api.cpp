@@ -198,6 +198,18 @@ bool plan_k_conv(const uint8_t* c_bits, int64_t C, KPlan& kp, int64_t cpad[2]) {
   return true;
 }
 
+// A per-channel table by four-channel piece of a row: the channels in
+// order, and for K not a multiple of 4 a last piece of the last four
+// channels (the quantizers' pieces overlap there).
+template <class T>
+std::vector<T> by_piece(const std::vector<T>& v) {
+  const size_t K = v.size();
+  if (K % 4 == 0 || K < 4) return v;
+  std::vector<T> t(v.begin(), v.begin() + K / 4 * 4);
+  t.insert(t.end(), v.end() - 4, v.end());
+  return t;
+}
+
 template <class T>
 hipError_t dev_alloc(T** p, size_t count) {
   *p = nullptr;
@@ -232,13 +244,17 @@ struct soniq_weights_s {
   int32_t* pos = nullptr;
   uint16_t* pos16 = nullptr;  // the same positions in 16 bits (planned K <= 65536)
   uint8_t* seg = nullptr;
+  // pos and seg by four-channel piece of a row (by_piece); the same arrays
+  // where K is a multiple of 4
+  int32_t* pos4 = nullptr;
+  uint8_t* seg4 = nullptr;
   // sub-group activation scales (0 bits: one scale per precision group)
   uint64_t serial = 0;  // unique per handle (tables built for it are keyed by it)
   int act_group_bits = 0;
   int gsub[2] = {0, 0};   // granules per block
   int nsub[2] = {0, 0};   // blocks per precision group
   int32_t* grp = nullptr;  // block of each original input channel
-  int32_t* posg = nullptr;  // planned position | block << 16
+  int32_t* posg4 = nullptr;  // planned position | block << 16, by piece
   std::vector<int32_t> grp_h;  // host copy of grp
   // MFMA-native copies (SONIQ_WPACK_F8F6F4): the weight side of the plan
   // (formats, fgranule counts, region offsets) and the weight copy
@@ -313,11 +329,13 @@ void free_weights(soniq_weights w) {
   (void)hipFree(w->shw);
   (void)hipFree(w->tile_cols);
   (void)hipFree(w->colrank);
+  if (w->pos4 != w->pos) (void)hipFree(w->pos4);
+  if (w->seg4 != w->seg) (void)hipFree(w->seg4);
   (void)hipFree(w->pos);
   (void)hipFree(w->pos16);
   (void)hipFree(w->seg);
   (void)hipFree(w->grp);
-  (void)hipFree(w->posg);
+  (void)hipFree(w->posg4);
   (void)hipFree(w->fw);
   (void)hipFree(w->dense);
   (void)hipFree(w->chan);
@@ -421,12 +439,12 @@ soniq_status run_quantize(soniq_act_s& act, const float* A_dev, int64_t M, int64
                           hipStream_t st) {
   const soniq_weights w = act.w;
   if (w->act_group_bits)
-    HIP_TRY(launch_act_quant_grouped(A_dev, M, w->K, lda, act.ap, w->pos, w->grp, w->posg,
+    HIP_TRY(launch_act_quant_grouped(A_dev, M, w->K, lda, act.ap, w->pos, w->grp, w->posg4,
                                      act.partial, act.counter, act.s_a, act.packed, st));
   bool ximg = false;
   if (!w->act_group_bits)
-    HIP_TRY(launch_act_quant(A_dev, M, w->K, lda, act.ap, w->pos, w->seg, act.partial, act.counter,
-                             act.s_a, act.packed, st, act.ximg, &ximg));
+    HIP_TRY(launch_act_quant(A_dev, M, w->K, lda, act.ap, w->pos, w->seg, w->pos4, w->seg4,
+                             act.partial, act.counter, act.s_a, act.packed, st, act.ximg, &ximg));
   act.ximg_ok = ximg;
   act.M = M;
   return SONIQ_OK;
@@ -722,8 +740,9 @@ soniq_status pack_impl(const float* W_dev, int64_t N, int64_t K, int64_t ldw,
     STEP(hipMemcpyAsync(w->grp, grp_h.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, st));
     posg_h.resize(K);
     for (int64_t k = 0; k < K; ++k) posg_h[k] = w->kp.pos[k] | (grp_h[k] << 16);
-    STEP(dev_alloc(&w->posg, (size_t)K));
-    STEP(hipMemcpyAsync(w->posg, posg_h.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    posg_h = by_piece(posg_h);
+    STEP(dev_alloc(&w->posg4, posg_h.size()));
+    STEP(hipMemcpyAsync(w->posg4, posg_h.data(), posg_h.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
   }
   STEP(dev_alloc(&wbits_dev, (size_t)N));
   STEP(dev_alloc(&phys_dev, (size_t)N));
@@ -737,6 +756,19 @@ soniq_status pack_impl(const float* W_dev, int64_t N, int64_t K, int64_t ldw,
   STEP(hipMemcpyAsync(w->pos, w->kp.pos.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, st));
   STEP(hipMemcpyAsync(w->pos16, pos16_h.data(), K * sizeof(uint16_t), hipMemcpyHostToDevice, st));
   STEP(hipMemcpyAsync(w->seg, w->kp.seg.data(), K, hipMemcpyHostToDevice, st));
+  std::vector<int32_t> pos4_h;
+  std::vector<uint8_t> seg4_h;
+  if (K % 4 == 0 || K < 4) {
+    w->pos4 = w->pos;
+    w->seg4 = w->seg;
+  } else {
+    pos4_h = by_piece(w->kp.pos);
+    seg4_h = by_piece(w->kp.seg);
+    STEP(dev_alloc(&w->pos4, pos4_h.size()));
+    STEP(dev_alloc(&w->seg4, seg4_h.size()));
+    STEP(hipMemcpyAsync(w->pos4, pos4_h.data(), pos4_h.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    STEP(hipMemcpyAsync(w->seg4, seg4_h.data(), seg4_h.size(), hipMemcpyHostToDevice, st));
+  }
   STEP(hipMemcpyAsync(wbits_dev, w_bits, N, hipMemcpyHostToDevice, st));
   STEP(hipMemcpyAsync(phys_dev, w->phys_h.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, st));
   STEP(launch_wpack(W_dev, N, K, ldw, wbits_dev, w->pos, w->seg, phys_dev, w->blk_off, w->blk_c,

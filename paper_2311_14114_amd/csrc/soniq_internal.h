@@ -232,12 +232,17 @@ hipError_t launch_gemv_fused(const float* A, int64_t K, const uint16_t* pos16_de
                              float* s_a, const ActPlan& ap, const WDev& wd, const WPlan& wp,
                              int64_t N, uint16_t* Y, int32_t* acc, hipStream_t stream,
                              uint8_t* ximg);
+// pos_dev, seg_dev: planned position and group of each input channel;
+// pos4_dev, seg4_dev: the same by four-channel piece of a row, where the
+// last piece of a row whose length is not a multiple of 4 covers its last
+// four channels (K < 4: not read).
 // ximg (null: none): where a batch of one row also leaves its contiguous
 // image for the batch-1 GEMV (a plan with a 4-bit group 0 and an 8-bit
 // group 1 only); *ximg_done tells whether the launched path wrote it.
 hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
                             const ActPlan& ap, const int32_t* pos_dev,
-                            const uint8_t* seg_dev, float* partial,
+                            const uint8_t* seg_dev, const int32_t* pos4_dev,
+                            const uint8_t* seg4_dev, float* partial,
                             unsigned int* counter, float* s_a, uint8_t* packed,
                             hipStream_t stream, uint8_t* ximg = nullptr,
                             bool* ximg_done = nullptr);
@@ -248,11 +253,11 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
 // at most kGSubMax blocks.
 constexpr int kGAbsParts = 1024;
 constexpr int kGSubMax = 256;
-// posg_dev[k] = pos_dev[k] | grp_dev[k] << 16 (the single pass's table);
+// posg4_dev: pos | grp << 16 by four-channel piece, as pos4_dev above;
 // counter: the handle's grid state.
 hipError_t launch_act_quant_grouped(const float* A, int64_t M, int64_t K, int64_t lda,
                                     const ActPlan& ap, const int32_t* pos_dev,
-                                    const int32_t* grp_dev, const int32_t* posg_dev,
+                                    const int32_t* grp_dev, const int32_t* posg4_dev,
                                     float* partial, unsigned int* counter, float* s_a,
                                     uint8_t* packed, hipStream_t stream);
 hipError_t launch_mp_gemm_grouped(const uint8_t* act_packed, const float* s_a, const ActPlan& ap,

@@ -9,8 +9,7 @@
 //   k_absmax_*      two-pass form, pass 1: per-workgroup partial maxima
 //   k_act_blk16,    two-pass form, pass 2: reduce the partials, quantize,
 //   k_act_rows      pack 16- or 8-row slices (or rows)
-//   k_act_small     small batches in one launch (max, quantize, pack)
-//   k_act_row1      batches of up to 8 rows, from registers after one load
+//   k_act_batch     small batches in one launch (max, quantize, pack)
 //   k_gemm          int8 MFMA GEMM on packed operands: an LDS ring filled by
 //                   direct global->LDS buffer loads, units widened to int8
 //                   in registers right before v_mfma_i32_16x16x64_i8, one
@@ -163,38 +162,48 @@ __device__ __forceinline__ uint4 unpack_unit_rt(uint4 raw, int c) {
 }
 
 // ------------------------------------------------------------ reductions --
+// Largest of 64 non-negative values, in every lane: DPP steps within rows of
+// 16 lanes (xor 1, xor 2, then mirrors of 8 and 16), two row broadcasts,
+// and lane 63 read back.  A step costs a few cycles; six ds_bpermute
+// shuffles are an LDS round trip each, and the two reductions of a
+// workgroup's maximum took 0.75 us of a 5.9 us decode quantizer (8 x 4096).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_max_step(float v) {
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, true)));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  v = dpp_max_step<0xB1, 0xF>(v);
+  v = dpp_max_step<0x4E, 0xF>(v);
+  v = dpp_max_step<0x141, 0xF>(v);
+  v = dpp_max_step<0x140, 0xF>(v);
+  v = dpp_max_step<0x142, 0xA>(v);
+  v = dpp_max_step<0x143, 0xC>(v);
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// Largest of a workgroup's non-negative values (4 or 8 waves).
 __device__ __forceinline__ float block_max(float v, float* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  v = wave_max(v);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   __syncthreads();
   if (lane == 0) red[wid] = v;
   __syncthreads();
-  float r = red[0];
-  for (int i = 1; i < (int)(blockDim.x >> 6); ++i) r = fmaxf(r, red[i]);
-  return r;
+  return wave_max(red[lane & ((blockDim.x >> 6) - 1)]);
 }
 
-// Maxima of two values over the workgroup (one pair of barriers).
+// Maxima of two non-negative values over the workgroup (4 or 8 waves; red,
+// two words a wave, is not in use before the call; one barrier).
 __device__ __forceinline__ float2 block_max2(float2 v, float* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    v.x = fmaxf(v.x, __shfl_xor(v.x, o, 64));
-    v.y = fmaxf(v.y, __shfl_xor(v.y, o, 64));
-  }
+  v.x = wave_max(v.x);
+  v.y = wave_max(v.y);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  __syncthreads();
   if (lane == 0) {
     red[2 * wid] = v.x;
     red[2 * wid + 1] = v.y;
   }
   __syncthreads();
-  float2 r = make_float2(red[0], red[1]);
-  for (int i = 1; i < (int)(blockDim.x >> 6); ++i) {
-    r.x = fmaxf(r.x, red[2 * i]);
-    r.y = fmaxf(r.y, red[2 * i + 1]);
-  }
-  return r;
+  const int w = 2 * (lane & ((blockDim.x >> 6) - 1));
+  return make_float2(wave_max(red[w]), wave_max(red[w + 1]));
 }
 
 __device__ __forceinline__ int block_sum(int v, int* red) {
@@ -271,6 +280,20 @@ __global__ __launch_bounds__(256) void k_wpack(
 // per-workgroup device-scope fence costs tens of nanoseconds each on a chip
 // with per-XCD L2s); the pack kernel that follows reduces the partials.
 
+// Four consecutive fp32 values of a row, which may start at any element:
+// one 16-byte load (global and buffer loads of gfx950 need 4-byte alignment
+// only), so rows of any stride and length take the vector kernels.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 ld4(const float* p) {
+  const f32x4u v = *reinterpret_cast<const f32x4u*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+// First element of piece k4 of a row of K >= 4: the last piece of a row
+// whose length is not a multiple of 4 starts at K - 4 and overlaps the one
+// before it (both write the same codes; a maximum ignores the repeat).  The
+// channel tables indexed by piece hold that overlap in their last entry.
+__device__ __forceinline__ int row4(int k4, int K) { return min(4 * k4, K - 4); }
+
 __device__ __forceinline__ void max4(float4 v, uchar4 g, float& mx0, float& mx1) {
   const float a0 = fabsf(v.x), a1 = fabsf(v.y), a2 = fabsf(v.z), a3 = fabsf(v.w);
   mx0 = fmaxf(mx0, fmaxf(fmaxf(g.x ? 0.0f : a0, g.y ? 0.0f : a1), fmaxf(g.z ? 0.0f : a2, g.w ? 0.0f : a3)));
@@ -286,21 +309,22 @@ __device__ __forceinline__ void write_partial(float mx0, float mx1, float* red,
   }
 }
 
-// Rows with K % 4 == 0, lda % 4 == 0, 16-byte aligned.  Workgroup b takes
-// RB consecutive rows; thread tid owns float4 positions k4 = base + 256*j
+// Rows of K >= 4 values at any stride.  Workgroup b takes RB consecutive
+// rows; thread tid owns float4 positions k4 = base + 256*j
 // of every row, loads all RB rows of them at once, keeps their |max| over
 // the rows (one v_max per element) and folds them into the two group
 // maxima once per position batch.  Clamped rows and positions re-read
 // in-bounds data already counted, which a max ignores.
 template <int J, int RB>
-__global__ __launch_bounds__(256) void k_absmax_blk(const float4* __restrict__ A, int64_t M,
-                                                    int K4, int64_t lda4,
+__global__ __launch_bounds__(256) void k_absmax_blk(const float* __restrict__ A, int64_t M,
+                                                    int K, int64_t lda,
                                                     const uchar4* __restrict__ seg4,
                                                     float* __restrict__ partial) {
   __shared__ float red[8];
   const int tid = threadIdx.x;
   const int64_t m0 = (int64_t)blockIdx.x * RB;
   const int rows = (int)min((int64_t)RB, M - m0);
+  const int K4 = (K + 3) / 4;
   float mx0 = 0.0f, mx1 = 0.0f;
   for (int base = 0; base < K4; base += 256 * J) {
     int k4[J];
@@ -309,9 +333,9 @@ __global__ __launch_bounds__(256) void k_absmax_blk(const float4* __restrict__ A
     float4 v[RB][J];
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-      const float4* row = A + (m0 + min(r, rows - 1)) * lda4;
+      const float* row = A + (m0 + min(r, rows - 1)) * lda;
 #pragma unroll
-      for (int j = 0; j < J; ++j) v[r][j] = row[k4[j]];
+      for (int j = 0; j < J; ++j) v[r][j] = ld4(row + row4(k4[j], K));
     }
     float4 mx[J];
 #pragma unroll
@@ -501,12 +525,6 @@ __device__ __forceinline__ int qexact(float x, float lo, float hi, float zp, flo
   return (int)__builtin_amdgcn_fmed3f(t - zp, lo, hi);
 }
 
-__device__ __forceinline__ int qstore(float x, float rs, float lo, float hi, float zp, float s) {
-  bool near;
-  const int c = qfast(x, rs, lo, hi, zp, near);
-  return near ? qexact(x, lo, hi, zp, s) : c;
-}
-
 // Four elements sharing one branch for the rare exact path.
 struct QE4 {
   float rs[4], lo[4], hi[4], zp[4], s[4];
@@ -537,11 +555,14 @@ __device__ __forceinline__ void qstore4(const float4& v, const QE4& q, uint8_t* 
 // their LDS positions and group parameters are looked up once for all R
 // rows.  The first batch of rows is loaded before the partial maxima are
 // reduced, so the two latencies overlap.  Groups of 1-bit sign codes, and
-// unaligned rows, take the generic per-element quantizer (J = 0).
+// rows of fewer than four values, take the per-element quantizer (J = 0,
+// pos and seg by channel; J > 0: by piece, as row4).  Element by element a
+// 301 x 4091 batch took 46 us with its maxima; on pieces it fits the single
+// pass, 13 us.
 // Dynamic LDS: R*Kp bytes.
 template <int R, int J>
 __device__ __forceinline__ void act_rows_load(const float* __restrict__ A, int64_t m0, int rows,
-                                              int64_t lda, int K4, int base,
+                                              int64_t lda, int K, int K4, int base,
                                               const int32_t* __restrict__ pos,
                                               const uint8_t* __restrict__ seg, int4 (&p)[J],
                                               uchar4 (&g)[J], float4 (&v)[R][J]) {
@@ -552,7 +573,7 @@ __device__ __forceinline__ void act_rows_load(const float* __restrict__ A, int64
     g[j] = reinterpret_cast<const uchar4*>(seg)[k4];
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      v[r][j] = *reinterpret_cast<const float4*>(A + (m0 + min(r, rows - 1)) * lda + 4 * k4);
+      v[r][j] = ld4(A + (m0 + min(r, rows - 1)) * lda + row4(k4, K));
   }
 }
 
@@ -606,11 +627,11 @@ __global__ __launch_bounds__(256) void k_act_rows(const float* __restrict__ A, i
   const int rows = (int)min((int64_t)R, M - m0);
   const int tid = threadIdx.x;
   if constexpr (J > 0) {
-    const int K4 = (int)(K / 4);
+    const int K4 = (int)((K + 3) / 4);
     int4 p[J];
     uchar4 g[J];
     float4 v[R][J];
-    act_rows_load<R, J>(A, m0, rows, lda, K4, tid, pos, seg, p, g, v);
+    act_rows_load<R, J>(A, m0, rows, lda, (int)K, K4, tid, pos, seg, p, g, v);
     uint32_t* codes32 = reinterpret_cast<uint32_t*>(codes);
     for (int i = tid; i < rows * ap.Kp / 4; i += blockDim.x) codes32[i] = 0;
     float s0, s1;
@@ -618,7 +639,7 @@ __global__ __launch_bounds__(256) void k_act_rows(const float* __restrict__ A, i
     const QElem q0 = qelem(s0, ap.q[0], ap.zp[0]), q1 = qelem(s1, ap.q[1], ap.zp[1]);
     act_rows_quant<R, J>(codes, ap.Kp, rows, K4, tid, p, g, v, q0, q1);
     for (int base = tid + 256 * J; base < K4; base += 256 * J) {
-      act_rows_load<R, J>(A, m0, rows, lda, K4, base, pos, seg, p, g, v);
+      act_rows_load<R, J>(A, m0, rows, lda, (int)K, K4, base, pos, seg, p, g, v);
       act_rows_quant<R, J>(codes, ap.Kp, rows, K4, base, p, g, v, q0, q1);
     }
   } else {
@@ -851,8 +872,8 @@ __device__ __forceinline__ void write_block_pieces(const uint8_t* codes, int ldc
 }
 
 // ----------------------------------------------------------- k_act_blk16 --
-// RB rows (8 or 16, aligned to a 16-row block) per workgroup, aligned rows,
-// no sign-code group: the rows go through in batches of four, the next
+// RB rows (8 or 16, aligned to a 16-row block) per workgroup, no sign-code
+// group: the rows go through in batches of four, the next
 // batch's loads in flight while the current one is quantized into LDS; the
 // partial maxima are reduced once; the rows' packed units are then written
 // as whole 16-byte pieces (each 16-channel group's units of these rows are
@@ -873,7 +894,7 @@ __global__ __launch_bounds__(256) void k_act_blk16(const float* __restrict__ A, 
   const int64_t m0 = (int64_t)blockIdx.x * RB;
   const int rows = (int)min((int64_t)RB, M - m0);
   const int tid = threadIdx.x;
-  const int K4 = (int)(K / 4);
+  const int K4 = (int)((K + 3) / 4);
   int4 p[J];
   uchar4 g[J];
   float4 va[4][J], vb[4][J];
@@ -884,7 +905,7 @@ __global__ __launch_bounds__(256) void k_act_blk16(const float* __restrict__ A, 
       const int k4 = min(tid + 256 * j, K4 - 1);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        v[r][j] = *reinterpret_cast<const float4*>(A + (m0 + min(4 * b + r, rows - 1)) * lda + 4 * k4);
+        v[r][j] = ld4(A + (m0 + min(4 * b + r, rows - 1)) * lda + row4(k4, (int)K));
     }
   };
   load(va, 0);
@@ -947,11 +968,8 @@ __device__ __forceinline__ void bar_nofence() {
 // block_max2 with fence-free barriers, for workgroups whose global loads
 // must stay in flight across it; red is used once.
 __device__ __forceinline__ float2 block_max2_nofence(float2 v, float* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    v.x = fmaxf(v.x, __shfl_xor(v.x, o, 64));
-    v.y = fmaxf(v.y, __shfl_xor(v.y, o, 64));
-  }
+  v.x = wave_max(v.x);
+  v.y = wave_max(v.y);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   if (lane == 0) {
     red[2 * wid] = v.x;
@@ -959,12 +977,8 @@ __device__ __forceinline__ float2 block_max2_nofence(float2 v, float* red) {
   }
   __builtin_amdgcn_s_waitcnt(SONIQ_LGKMCNT0_IMM);
   bar_nofence();
-  float2 r = make_float2(red[0], red[1]);
-  for (int i = 1; i < (int)(blockDim.x >> 6); ++i) {
-    r.x = fmaxf(r.x, red[2 * i]);
-    r.y = fmaxf(r.y, red[2 * i + 1]);
-  }
-  return r;
+  const int w = 2 * (lane & ((blockDim.x >> 6) - 1));
+  return make_float2(wave_max(red[w]), wave_max(red[w + 1]));
 }
 
 // All but the last N loads of this wave have landed, direct-to-LDS ones
@@ -1177,15 +1191,15 @@ __device__ __forceinline__ bool grid_fold_max_n(unsigned* st, unsigned gen, unsi
 
 // Block maxima of the whole batch, by this workgroup alone (the timed-out
 // wait only): block index in bits 16.. of the planned-position table.
-__device__ __forceinline__ void absmax_all_blocks(const float* __restrict__ A, int64_t M, int K4,
+__device__ __forceinline__ void absmax_all_blocks(const float* __restrict__ A, int64_t M, int K,
                                                   int64_t lda, const int4* pos4, unsigned* mx,
                                                   int n) {
   for (int j = threadIdx.x; j < n; j += 256) mx[j] = 0u;
   __syncthreads();
   for (int64_t m = 0; m < M; ++m)
-    for (int k = threadIdx.x; k < K4; k += 256) {
+    for (int k = threadIdx.x; k < (K + 3) / 4; k += 256) {
       const int4 p = pos4[k];
-      const float4 v = *reinterpret_cast<const float4*>(A + m * lda + 4 * k);
+      const float4 v = ld4(A + m * lda + row4(k, K));
       atomicMax(&mx[p.x >> 16], __float_as_uint(fabsf(v.x)));
       atomicMax(&mx[p.y >> 16], __float_as_uint(fabsf(v.y)));
       atomicMax(&mx[p.z >> 16], __float_as_uint(fabsf(v.z)));
@@ -1197,14 +1211,14 @@ __device__ __forceinline__ void absmax_all_blocks(const float* __restrict__ A, i
 // Group maxima of the whole batch, by this workgroup alone (the timed-out
 // wait only).  pos4: LDS copy of the planned positions; group 1 starts at
 // planned position kp0.
-__device__ __forceinline__ void absmax_all(const float* __restrict__ A, int64_t M, int K4,
+__device__ __forceinline__ void absmax_all(const float* __restrict__ A, int64_t M, int K,
                                            int64_t lda, const int4* pos4, int kp0, float* red,
                                            float& g0, float& g1) {
   float mx0 = 0.0f, mx1 = 0.0f;
   for (int64_t m = 0; m < M; ++m)
-    for (int k = threadIdx.x; k < K4; k += 256) {
+    for (int k = threadIdx.x; k < (K + 3) / 4; k += 256) {
       const int4 p = pos4[k];
-      max4(*reinterpret_cast<const float4*>(A + m * lda + 4 * k),
+      max4(ld4(A + m * lda + row4(k, K)),
            make_uchar4(p.x >= kp0, p.y >= kp0, p.z >= kp0, p.w >= kp0), mx0, mx1);
     }
   const float2 r = block_max2(make_float2(mx0, mx1), red);
@@ -1397,7 +1411,7 @@ __device__ __forceinline__ void qcodes4g(const float4& v, int4 p, const float* s
 // LDS after the row slots: 3*nsub words).
 template <int T, int TL, bool GRP = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T <= 9 ? 7 : 4)))
-void k_act_coop(const float* __restrict__ A, int64_t M, int K4, int64_t lda, int RB,
+void k_act_coop(const float* __restrict__ A, int64_t M, int K, int64_t lda, int RB,
                 const int32_t* __restrict__ pos, ActPlan ap, unsigned* __restrict__ st,
                 unsigned spins, float* __restrict__ s_a_out, uint8_t* __restrict__ packed) {
   extern __shared__ __align__(16) uint8_t codes[];
@@ -1407,6 +1421,7 @@ void k_act_coop(const float* __restrict__ A, int64_t M, int K4, int64_t lda, int
   const int tid = threadIdx.x;
   const int64_t m0 = (int64_t)blockIdx.x * RB;
   const int rows = (int)min((int64_t)RB, M - m0);
+  const int K4 = (K + 3) / 4;
   const int nf = RB * K4;  // flat positions of this workgroup (T*256 >= nf)
   // uniform: kept in SGPRs (the division runs on the vector unit)
   const int q256 = __builtin_amdgcn_readfirstlane(256 / K4);
@@ -1451,7 +1466,7 @@ void k_act_coop(const float* __restrict__ A, int64_t M, int K4, int64_t lda, int
   {
     // rows through a buffer resource based at row m0: 32-bit offsets
     const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)A0, (short)0, (int)(((int64_t)(rows - 1) * lda + 4 * K4) * 4), 0x00020000);
+        (void*)A0, (short)0, (int)(((int64_t)(rows - 1) * lda + K) * 4), 0x00020000);
     const uint32_t ld4 = (uint32_t)lda * 4u;
     const uint32_t vb = lds_off(reinterpret_cast<uint8_t*>(vlds)) +
                         (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6) * 1024u;
@@ -1463,7 +1478,7 @@ void k_act_coop(const float* __restrict__ A, int64_t M, int K4, int64_t lda, int
       const bool in = tid + 256 * i < nf;
       const int rc = in ? min(r, rows - 1) : rows - 1;
       const int kc = in ? k : K4 - 1;
-      const uint32_t off = (uint32_t)rc * ld4 + 16u * (uint32_t)kc;
+      const uint32_t off = (uint32_t)rc * ld4 + 4u * (uint32_t)row4(kc, K);
       if (i >= TL)
         v[i >= TL ? i - TL : 0] =
             __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(ar, off, 0, 0));
@@ -1534,7 +1549,7 @@ void k_act_coop(const float* __restrict__ A, int64_t M, int K4, int64_t lda, int
     }
     __syncthreads();
     if (!flag && tid == 0) bar_add(st + kActStallWord, 1u);
-    if (!flag) absmax_all_blocks(A, M, K4, lda, pos4, bmax, nsub);
+    if (!flag) absmax_all_blocks(A, M, K, lda, pos4, bmax, nsub);
     for (int j = tid; j < nsub; j += 256) {
       const float sc = group_scale(__uint_as_float(bmax[j]), j < ap.nsub[0] ? ap.q[0] : ap.q[1]);
       stab[j] = sc;
@@ -1554,7 +1569,7 @@ void k_act_coop(const float* __restrict__ A, int64_t M, int K4, int64_t lda, int
     __syncthreads();
   }
   float g0 = gmax[0], g1 = gmax[1];
-  if (!GRP && !flag) absmax_all(A, M, K4, lda, pos4, kp0, red, g0, g1);
+  if (!GRP && !flag) absmax_all(A, M, K, lda, pos4, kp0, red, g0, g1);
   const float s0 = group_scale(g0, ap.q[0]);
   const float s1 = ap.S == 2 ? group_scale(g1, ap.q[1]) : 0.0f;
   if (!GRP && blockIdx.x == 0 && tid == 0) {
@@ -1627,70 +1642,156 @@ void k_act_coop(const float* __restrict__ A, int64_t M, int K4, int64_t lda, int
   }
 }
 
-// ----------------------------------------------------------- k_act_small --
-// Small batches (M <= 64, M*K <= kSmallElems, contiguous aligned rows): one
-// launch.  Every workgroup reduces the group maxima of the whole batch
-// itself (at most 256 KB, L2-resident after the first pass), then
-// quantizes and packs its own row.  Dynamic LDS: Kp bytes.
-constexpr int kSmallElems = 65536;
-constexpr int kSmallU = 4;
-
-__global__ __launch_bounds__(256) void k_act_small(const float* __restrict__ A, int M, int K,
-                                                   int64_t lda, const int32_t* __restrict__ pos,
-                                                   const uint8_t* __restrict__ seg, ActPlan ap,
-                                                   float* __restrict__ s_a_out,
-                                                   uint8_t* __restrict__ packed,
-                                                   uint8_t* __restrict__ ximg) {
+// ----------------------------------------------------------- k_act_batch --
+// Small batches in one launch, rows at any alignment and stride: workgroup
+// m reads the whole batch, reduces its maxima, then quantizes and packs its
+// own row m (every workgroup computes the same maxima from the same data).
+//
+// Bound by latency, not bytes: a decode batch is 16 to 256 KB and the
+// launch is one chain of load, reduce, quantize, store, behind 1.8 us that
+// an empty kernel takes.  Threads per workgroup, back to back in a graph,
+// us: 8 x 4096: 5.4 with 256, 4.8 with 512, 5.2 with 1024; 1 x 4096: 4.5,
+// 4.3, 5.1; 64 x 256: 4.1, 3.9, 4.8 (more waves load faster but start and
+// meet at barriers later), so 512 everywhere.
+//
+// Thread (rg, col): float4 columns col + 512*j (j < J) of rows rg, rg +
+// nrg, ..., with 2^cl >= K/4 columns side by side (cl = 9 where J > 1).
+// GRP: block maxima.  A column's four |max| go to LDS words at their
+// planned positions (ds_max: several row groups may hold a column), and a
+// wave folds each 64-position granule, which lies in one block, into that
+// block's word: one LDS atomic per granule, where folding elements straight
+// into their blocks serializes a wave on one or two words.
+// Dynamic LDS: Kp code bytes, then for GRP Kp words and 3*nsub words.
+template <int J, bool GRP>
+__global__ __launch_bounds__(512) void k_act_batch(const float* __restrict__ A, int M, int K,
+                                                    int64_t lda, const int4* __restrict__ pos4,
+                                                    int cl, ActPlan ap, float* __restrict__ s_a,
+                                                    uint8_t* __restrict__ packed,
+                                                    uint8_t* __restrict__ ximg) {
+  constexpr int U = 8 / J;  // rows in flight per thread
   extern __shared__ __align__(16) uint8_t codes[];
-  __shared__ float red[8];
+  __shared__ float red[16];
   const int tid = threadIdx.x;
-  const int K4 = K / 4;
-  const int total4 = M * K4;
-  float mx0 = 0.0f, mx1 = 0.0f;
-  for (int base = tid; base < total4; base += 256 * kSmallU) {
-    float4 v[kSmallU];
-    uchar4 g[kSmallU];
-#pragma unroll
-    for (int j = 0; j < kSmallU; ++j) {
-      const int i = min(base + 256 * j, total4 - 1);  // repeats change no max
-      const int m = i / K4, k4 = i - m * K4;
-      v[j] = *reinterpret_cast<const float4*>(A + (int64_t)m * lda + 4 * k4);
-      g[j] = reinterpret_cast<const uchar4*>(seg)[k4];
-    }
-#pragma unroll
-    for (int j = 0; j < kSmallU; ++j) max4(v[j], g[j], mx0, mx1);
-  }
-  uint32_t* codes32 = reinterpret_cast<uint32_t*>(codes);
-  for (int i = tid; i < ap.Kp / 4; i += 256) codes32[i] = 0;
-  mx0 = block_max(mx0, red);
-  mx1 = block_max(mx1, red);
-  const float s0 = group_scale(mx0, ap.q[0]);
-  const float s1 = ap.S == 2 ? group_scale(mx1, ap.q[1]) : 0.0f;
-  if (blockIdx.x == 0 && tid == 0) {
-    s_a_out[0] = s0;
-    s_a_out[1] = s1;
-  }
-  const ActQ aq = make_actq(ap, s0, s1);
+  const int K4 = (K + 3) / 4;
   const int m = blockIdx.x;
-  const float* row = A + (int64_t)m * lda;
-  for (int base = tid; base < K4; base += 256 * kSmallU) {
-    float4 v[kSmallU];
-    int4 p[kSmallU];
-    uchar4 g[kSmallU];
+  const int col = tid & ((1 << cl) - 1), rg = tid >> cl, nrg = 512 >> cl;
+  const int kp0 = ap.kpad[0];
+  int off[J];
+  int4 p[J];
+  float4 x[J], mx[J];
 #pragma unroll
-    for (int j = 0; j < kSmallU; ++j) {
-      const int k4 = min(base + 256 * j, K4 - 1);
-      v[j] = reinterpret_cast<const float4*>(row)[k4];
-      p[j] = reinterpret_cast<const int4*>(pos)[k4];
-      g[j] = reinterpret_cast<const uchar4*>(seg)[k4];
+  for (int j = 0; j < J; ++j) {
+    const int k4 = min(col + 512 * j, K4 - 1);  // repeats change no max
+    off[j] = row4(k4, K);
+    p[j] = pos4[k4];
+    x[j] = ld4(A + m * lda + off[j]);
+    mx[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  }
+  const int nsub = GRP ? ap.nsub[0] + (ap.S == 2 ? ap.nsub[1] : 0) : 0;
+  unsigned* fmx = reinterpret_cast<unsigned*>(codes + ap.Kp);
+  unsigned* smax = fmx + ap.Kp;
+  float* stab = reinterpret_cast<float*>(smax + nsub);
+  float* rtab = stab + nsub;
+  for (int i = tid; i < ap.Kp / 4; i += 512) reinterpret_cast<uint32_t*>(codes)[i] = 0u;
+  if constexpr (GRP) {
+    for (int i = tid; i < ap.Kp + nsub; i += 512) fmx[i] = 0u;
+    __builtin_amdgcn_s_waitcnt(SONIQ_LGKMCNT0_IMM);
+    bar_nofence();
+  }
+  for (int r0 = rg; r0 < M; r0 += nrg * U) {
+    float4 v[U][J];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < J; ++j) v[u][j] = ld4(A + (int64_t)min(r0 + u * nrg, M - 1) * lda + off[j]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        mx[j].x = fmaxf(mx[j].x, fabsf(v[u][j].x));
+        mx[j].y = fmaxf(mx[j].y, fabsf(v[u][j].y));
+        mx[j].z = fmaxf(mx[j].z, fabsf(v[u][j].z));
+        mx[j].w = fmaxf(mx[j].w, fabsf(v[u][j].w));
+      }
+  }
+  float s0 = 0.0f, s1 = 0.0f;
+  if constexpr (GRP) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      atomicMax(&fmx[p[j].x & 0xFFFF], __float_as_uint(mx[j].x));
+      atomicMax(&fmx[p[j].y & 0xFFFF], __float_as_uint(mx[j].y));
+      atomicMax(&fmx[p[j].z & 0xFFFF], __float_as_uint(mx[j].z));
+      atomicMax(&fmx[p[j].w & 0xFFFF], __float_as_uint(mx[j].w));
     }
+    __syncthreads();
+    for (int q = tid >> 6; q < ap.Kp / kGran; q += 8) {
+      const float gm = wave_max(__uint_as_float(fmx[q * kGran + (tid & 63)]));
+      const int b = q < ap.ng[0] ? q / ap.gsub[0] : ap.nsub[0] + (q - ap.ng[0]) / ap.gsub[1];
+      if ((tid & 63) == 0) atomicMax(&smax[b], __float_as_uint(gm));
+    }
+    __syncthreads();
+    for (int j = tid; j < nsub; j += 512) {
+      const float sc = group_scale(__uint_as_float(smax[j]), j < ap.nsub[0] ? ap.q[0] : ap.q[1]);
+      stab[j] = sc;
+      rtab[j] = fast_ok(sc) ? __builtin_amdgcn_rcpf(sc) : 0.0f;
+      if (m == 0) s_a[j] = sc;
+    }
+    __syncthreads();
+  } else {
+    float mx0 = 0.0f, mx1 = 0.0f;
 #pragma unroll
-    for (int j = 0; j < kSmallU; ++j) {
-      if (base + 256 * j < K4) {
-        codes[p[j].x] = store_code(v[j].x, g[j].x, aq);
-        codes[p[j].y] = store_code(v[j].y, g[j].y, aq);
-        codes[p[j].z] = store_code(v[j].z, g[j].z, aq);
-        codes[p[j].w] = store_code(v[j].w, g[j].w, aq);
+    for (int j = 0; j < J; ++j)
+      max4(mx[j], make_uchar4(p[j].x >= kp0, p[j].y >= kp0, p[j].z >= kp0, p[j].w >= kp0), mx0, mx1);
+    const float2 mm = block_max2(make_float2(mx0, mx1), red);  // syncs
+    s0 = group_scale(mm.x, ap.q[0]);
+    s1 = ap.S == 2 ? group_scale(mm.y, ap.q[1]) : 0.0f;
+    if (m == 0 && tid == 0) {
+      s_a[0] = s0;
+      s_a[1] = s1;
+    }
+  }
+  // row m's codes: the threads of row group 0 hold its columns
+  if (rg == 0) {
+    if constexpr (GRP) {
+      const float lo0 = (float)ap.q[0].lo, hi0 = (float)ap.q[0].hi;
+      const float lo1 = (float)ap.q[1].lo, hi1 = (float)ap.q[1].hi;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (col + 512 * j >= K4) break;
+        const float xs[4] = {x[j].x, x[j].y, x[j].z, x[j].w};
+        const int pp[4] = {p[j].x, p[j].y, p[j].z, p[j].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int b = pp[e] >> 16;
+          const float sc = stab[b], rs = rtab[b];
+          const bool g1 = b >= ap.nsub[0];
+          float t = 0.0f;
+          if (sc != 0.0f) {
+            const float ex = xs[e] * rs;
+            t = __builtin_rintf(ex);
+            if (rs == 0.0f || fabsf(fabsf(ex - t) - 0.5f) <= 0x1p-9f) t = __builtin_rintf(__fdiv_rn(xs[e], sc));
+            t = fminf(fmaxf(t, g1 ? lo1 : lo0), g1 ? hi1 : hi0);
+          }
+          codes[pp[e] & 0xFFFF] = (uint8_t)(int8_t)(int)t;
+        }
+      }
+    } else if (ap.q[0].sign1 || (ap.S == 2 && ap.q[1].sign1)) {
+      const ActQ aq = make_actq(ap, s0, s1);
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (col + 512 * j >= K4) break;
+        codes[p[j].x] = store_code(x[j].x, p[j].x >= kp0, aq);
+        codes[p[j].y] = store_code(x[j].y, p[j].y >= kp0, aq);
+        codes[p[j].z] = store_code(x[j].z, p[j].z >= kp0, aq);
+        codes[p[j].w] = store_code(x[j].w, p[j].w >= kp0, aq);
+      }
+    } else {
+      const QPair q = qpair(qelem(s0, ap.q[0], ap.zp[0]), qelem(s1, ap.q[1], ap.zp[1]));
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (col + 512 * j >= K4) break;
+        const bool h[4] = {p[j].x >= kp0, p[j].y >= kp0, p[j].z >= kp0, p[j].w >= kp0};
+        qstore4g(x[j], h, q, codes, p[j]);
       }
     }
   }
@@ -1698,65 +1799,33 @@ __global__ __launch_bounds__(256) void k_act_small(const float* __restrict__ A, 
   write_act_units(codes, 1, m, ap, packed, ximg);
 }
 
-// ------------------------------------------------------------ k_act_row1 --
-// Batches of at most MT rows (decode steps), aligned, no sign-code group:
-// workgroup m loads every row of the batch and the planned positions once
-// (thread tid owns float4 positions tid + 256*j, j < J, of every row),
-// reduces the group maxima of the batch from registers, then quantizes
-// its own row m (group 1 starts at planned position kpad[0]) into LDS and
-// writes the row's units.  One HBM round trip instead of two; every
-// workgroup computes the same maxima from the same data.
-// Dynamic LDS: Kp bytes.
-template <int J, int MT>
-__global__ __launch_bounds__(256) void k_act_row1(const float* __restrict__ A, int M, int K4,
-                                                  int64_t lda, const int32_t* __restrict__ pos,
-                                                  ActPlan ap, float* __restrict__ s_a_out,
-                                                  uint8_t* __restrict__ packed,
-                                                  uint8_t* __restrict__ ximg) {
-  extern __shared__ __align__(16) uint8_t codes[];
-  __shared__ float red[8];
-  const int tid = threadIdx.x;
-  const int m = blockIdx.x;
-  const int kp0 = ap.kpad[0];
-  float4 v[MT][J];
-  int4 p[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int k4 = min(tid + 256 * j, K4 - 1);  // repeats change no max
-    p[j] = reinterpret_cast<const int4*>(pos)[k4];
-#pragma unroll
-    for (int r = 0; r < MT; ++r)
-      v[r][j] = reinterpret_cast<const float4*>(A + (int64_t)min(r, M - 1) * lda)[k4];
-  }
-  uint32_t* codes32 = reinterpret_cast<uint32_t*>(codes);
-  for (int i = tid; i < ap.Kp / 4; i += 256) codes32[i] = 0;
-  float mx0 = 0.0f, mx1 = 0.0f;
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const uchar4 g = make_uchar4(p[j].x >= kp0, p[j].y >= kp0, p[j].z >= kp0, p[j].w >= kp0);
-#pragma unroll
-    for (int r = 0; r < MT; ++r) max4(v[r][j], g, mx0, mx1);
-  }
-  const float2 mm = block_max2(make_float2(mx0, mx1), red);  // syncs
-  const float s0 = group_scale(mm.x, ap.q[0]);
-  const float s1 = ap.S == 2 ? group_scale(mm.y, ap.q[1]) : 0.0f;
-  if (m == 0 && tid == 0) {
-    s_a_out[0] = s0;
-    s_a_out[1] = s1;
-  }
-  const QPair q = qpair(qelem(s0, ap.q[0], ap.zp[0]), qelem(s1, ap.q[1], ap.zp[1]));
-#pragma unroll
-  for (int j = 0; j < J; ++j)
-    if (tid + 256 * j < K4) {
-      const bool h[4] = {p[j].x >= kp0, p[j].y >= kp0, p[j].z >= kp0, p[j].w >= kp0};
-      float4 x = v[0][j];
-#pragma unroll
-      for (int r = 1; r < MT; ++r)
-        if (r == m) x = v[r][j];
-      qstore4g(x, h, q, codes, p[j]);
-    }
-  __syncthreads();
-  write_act_units(codes, 1, m, ap, packed, ximg);
+// Whether k_act_batch takes a batch.  Every workgroup reads all rows, so
+// the batch is small: up to 8 rows of up to 16384 values, or up to
+// kBatchElems values in 64 rows (64 x 1024: 5.5 us against 8.1 for the
+// two launches that larger batches take).
+constexpr int kBatchElems = 65536;
+bool act_batch_takes(int64_t M, int64_t K) {
+  return K >= 4 && K <= 16384 && (M <= 8 || (M <= 64 && M * K <= kBatchElems));
+}
+
+// The launch; pos4 holds position | block << 16 with sub-group scales.
+template <bool GRP>
+hipError_t launch_act_batch(const float* A, int64_t M, int64_t K, int64_t lda, const ActPlan& ap,
+                            const int32_t* pos4, float* s_a, uint8_t* packed, hipStream_t stream,
+                            uint8_t* ximg, size_t lds) {
+  const int K4 = (int)((K + 3) / 4);
+  int cl = 6;
+  while (cl < 9 && (1 << cl) < K4) ++cl;
+  const int J = (K4 + 511) / 512;
+#define SONIQ_BATCH(J_)                                                                            \
+  hipLaunchKernelGGL((k_act_batch<J_, GRP>), dim3((unsigned)M), dim3(512), lds, stream, A, (int)M, \
+                     (int)K, lda, reinterpret_cast<const int4*>(pos4), cl, ap, s_a, packed, ximg)
+  if (J <= 1) SONIQ_BATCH(1);
+  else if (J <= 2) SONIQ_BATCH(2);
+  else if (J <= 4) SONIQ_BATCH(4);
+  else SONIQ_BATCH(8);
+#undef SONIQ_BATCH
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------ GEMM/GEMV --
@@ -4235,7 +4304,7 @@ bool coop_launch(const float* A, int64_t M, int64_t K, int64_t lda, int RB, cons
                  const int32_t* pos_dev, unsigned* bar, float* s_a,
                  uint8_t* packed, hipStream_t stream, hipError_t& e) {
   const int nsub = GRP ? ap.nsub[0] + (ap.S == 2 ? ap.nsub[1] : 0) : 0;
-  const size_t lds = (size_t)RB * ap.Kp + 16 * (size_t)((K / 4 + 63) / 64 * 64) + 4096 * TL +
+  const size_t lds = (size_t)RB * ap.Kp + 16 * (size_t)(((K + 3) / 4 + 63) / 64 * 64) + 4096 * TL +
                      (size_t)(12 * nsub + 15) / 16 * 16;
   const int64_t blocks = (M + RB - 1) / RB;
   // a workgroup's rows are addressed with 32-bit byte offsets
@@ -4244,7 +4313,7 @@ bool coop_launch(const float* A, int64_t M, int64_t K, int64_t lda, int RB, cons
   unsigned spins = kBarrierSpins;
   if (const char* env = getenv("SONIQ_COOP_SPINS")) spins = (unsigned)strtoul(env, nullptr, 10);
   hipLaunchKernelGGL((k_act_coop<T, TL, GRP>), dim3((unsigned)blocks), dim3(256), lds, stream, A, M,
-                     (int)(K / 4), lda, RB, pos_dev, ap, bar, spins, s_a, packed);
+                     (int)K, lda, RB, pos_dev, ap, bar, spins, s_a, packed);
   e = hipGetLastError();
   return true;
 }
@@ -4255,7 +4324,9 @@ bool launch_act_coop(const float* A, int64_t M, int64_t K, int64_t lda, const Ac
                      uint8_t* packed, hipStream_t stream, hipError_t& e, bool grp = false) {
   if (const char* env = getenv("SONIQ_ACT_COOP"))
     if (atoi(env) == 0) return false;
-  const int64_t K4 = K / 4;
+  const int64_t K4 = (K + 3) / 4;
+  // direct global -> LDS row slots (T = 9) take 16-byte aligned rows
+  const bool aligned = K % 4 == 0 && lda % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
   // candidates (RB, T) ordered by wasted register slots, more workgroups
   // first (they spread the quantize work more evenly over the CUs)
   struct Cand {
@@ -4265,7 +4336,7 @@ bool launch_act_coop(const float* A, int64_t M, int64_t K, int64_t lda, const Ac
   int nc = 0;
   for (int rb : {4, 8, 16}) {
     const int64_t need = (rb * K4 + 255) / 256;
-    const int t = need <= 6 ? 6 : need <= 9 ? 9 : need <= 12 ? 12 : need <= 18 ? 18 : 0;
+    const int t = need <= 6 ? 6 : need <= 9 && aligned ? 9 : need <= 12 ? 12 : need <= 18 ? 18 : 0;
     if (t == 0) continue;
     cand[nc++] = {rb, t, 256 * (int64_t)t - rb * K4};
   }
@@ -4643,92 +4714,6 @@ __global__ __launch_bounds__(256) void k_gabsmax4(const float4* __restrict__ A, 
   }
   __syncthreads();
   for (int j = tid; j < nsub; j += 256) part[(int64_t)blockIdx.x * nsub + j] = __uint_as_float(smax[j]);
-}
-
-// Sub-group scales for batches of at most MT <= 8 rows in one launch:
-// workgroup m loads every row of the batch once (J float4 per thread and
-// row), folds their block maxima into LDS, turns them into the block
-// scales, and quantizes its own row m with them, with the arithmetic of
-// k_gabsmax4, k_gscales and k_gquant4 (so the codes and scales are
-// theirs).  Workgroup 0 stores the scales.  Dynamic LDS: Kp code bytes,
-// then nsub maxima, scales and reciprocals.
-template <int J, int MT>
-__global__ __launch_bounds__(256) void k_gact_rows(const float4* __restrict__ A, int M, int K4,
-                                                   int64_t lda4, const int4* __restrict__ pos4,
-                                                   const int4* __restrict__ grp4, ActPlan ap,
-                                                   int nsub, float* __restrict__ s_a,
-                                                   uint8_t* __restrict__ packed) {
-  extern __shared__ __align__(16) uint8_t codes[];
-  unsigned* smax = reinterpret_cast<unsigned*>(codes + ap.Kp);
-  float* stab = reinterpret_cast<float*>(smax + nsub);
-  float* rtab = stab + nsub;
-  const int tid = threadIdx.x;
-  const int m = blockIdx.x;
-  float4 v[MT][J];
-  int4 p[J], gb[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int k4 = min(tid + 256 * j, K4 - 1);  // repeats change no max
-    p[j] = pos4[k4];
-    gb[j] = grp4[k4];
-#pragma unroll
-    for (int r = 0; r < MT; ++r) v[r][j] = A[(int64_t)min(r, M - 1) * lda4 + k4];
-  }
-  uint32_t* codes32 = reinterpret_cast<uint32_t*>(codes);
-  for (int i = tid; i < ap.Kp / 4; i += 256) codes32[i] = 0u;
-  for (int j = tid; j < nsub; j += 256) smax[j] = 0u;
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    float4 mx = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-    for (int r = 0; r < MT; ++r) {
-      mx.x = fmaxf(mx.x, fabsf(v[r][j].x));
-      mx.y = fmaxf(mx.y, fabsf(v[r][j].y));
-      mx.z = fmaxf(mx.z, fabsf(v[r][j].z));
-      mx.w = fmaxf(mx.w, fabsf(v[r][j].w));
-    }
-    atomicMax(&smax[gb[j].x], __float_as_uint(mx.x));
-    atomicMax(&smax[gb[j].y], __float_as_uint(mx.y));
-    atomicMax(&smax[gb[j].z], __float_as_uint(mx.z));
-    atomicMax(&smax[gb[j].w], __float_as_uint(mx.w));
-  }
-  __syncthreads();
-  for (int j = tid; j < nsub; j += 256) {
-    const float sc = group_scale(__uint_as_float(smax[j]), j < ap.nsub[0] ? ap.q[0] : ap.q[1]);
-    stab[j] = sc;
-    rtab[j] = fast_ok(sc) ? __builtin_amdgcn_rcpf(sc) : 0.0f;
-    if (m == 0) s_a[j] = sc;
-  }
-  __syncthreads();
-  const float lo0 = (float)ap.q[0].lo, hi0 = (float)ap.q[0].hi;
-  const float lo1 = (float)ap.q[1].lo, hi1 = (float)ap.q[1].hi;
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    if (tid + 256 * j >= K4) break;
-    float4 x = v[0][j];
-#pragma unroll
-    for (int r = 1; r < MT; ++r)
-      if (r == m) x = v[r][j];
-    const float xs[4] = {x.x, x.y, x.z, x.w};
-    const int pp[4] = {p[j].x, p[j].y, p[j].z, p[j].w};
-    const int gg[4] = {gb[j].x, gb[j].y, gb[j].z, gb[j].w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float sc = stab[gg[e]], rs = rtab[gg[e]];
-      const bool g1 = gg[e] >= ap.nsub[0];
-      float t = 0.0f;
-      if (sc != 0.0f) {
-        const float ex = xs[e] * rs;
-        t = __builtin_rintf(ex);
-        if (rs == 0.0f || fabsf(fabsf(ex - t) - 0.5f) <= 0x1p-9f) t = __builtin_rintf(__fdiv_rn(xs[e], sc));
-        t = fminf(fmaxf(t, g1 ? lo1 : lo0), g1 ? hi1 : hi0);
-      }
-      codes[pp[e]] = (uint8_t)(int8_t)(int)t;
-    }
-  }
-  __syncthreads();
-  write_act_units(codes, 1, m, ap, packed);
 }
 
 template <int R, int J>
@@ -5403,64 +5388,36 @@ hipError_t launch_conv_quant(const float* X, int64_t B, int64_t C, int64_t H, in
 
 hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
                             const ActPlan& ap, const int32_t* pos_dev,
-                            const uint8_t* seg_dev, float* partial,
+                            const uint8_t* seg_dev, const int32_t* pos4_dev,
+                            const uint8_t* seg4_dev, float* partial,
                             unsigned int* counter, float* s_a, uint8_t* packed,
                             hipStream_t stream, uint8_t* ximg, bool* ximg_done) {
   // the row image is written by the per-row quantizers below, for one row
   if (M != 1) ximg = nullptr;
   if (ximg_done) *ximg_done = false;
-  const bool aligned = (K % 4 == 0) && (lda % 4 == 0) &&
-                       (reinterpret_cast<uintptr_t>(A) % 16 == 0);
   const bool sign = ap.q[0].sign1 || (ap.S == 2 && ap.q[1].sign1);
-  // batches of one row (up to 16 float4 per thread) or up to 8 rows (up
-  // to 4 float4 per thread and row): every row loaded once
-  if (aligned && !sign && ((M == 1 && K / 4 <= 256 * 16) || (M <= 8 && K / 4 <= 256 * 4))) {
-    const int K4 = (int)(K / 4);
-    const int J = (K4 + 255) / 256;
-#define SONIQ_ROWS(J_, MT_)                                                                       \
-  hipLaunchKernelGGL((k_act_row1<J_, MT_>), dim3((unsigned)M), dim3(256), (size_t)ap.Kp, stream, A, \
-                     (int)M, K4, lda, pos_dev, ap, s_a, packed, ximg)
-    if (M == 1) {
-      if (J <= 1) SONIQ_ROWS(1, 1);
-      else if (J <= 2) SONIQ_ROWS(2, 1);
-      else if (J <= 4) SONIQ_ROWS(4, 1);
-      else if (J <= 8) SONIQ_ROWS(8, 1);
-      else SONIQ_ROWS(16, 1);
-    } else if (M <= 2) {
-      if (J <= 2) SONIQ_ROWS(2, 2); else SONIQ_ROWS(4, 2);
-    } else if (M <= 4) {
-      if (J <= 2) SONIQ_ROWS(2, 4); else SONIQ_ROWS(4, 4);
-    } else {
-      if (J <= 2) SONIQ_ROWS(2, 8); else SONIQ_ROWS(4, 8);
-    }
-#undef SONIQ_ROWS
+  const bool vec = K >= 4;  // rows split into four-value pieces (row4)
+  if (act_batch_takes(M, K)) {
     if (ximg_done) *ximg_done = ximg != nullptr;
-    return hipGetLastError();
+    return launch_act_batch<false>(A, M, K, lda, ap, pos4_dev, s_a, packed, stream, ximg, (size_t)ap.Kp);
   }
-  if (aligned && M <= 64 && M * K <= kSmallElems) {
-    hipLaunchKernelGGL(k_act_small, dim3((unsigned)M), dim3(256), (size_t)ap.Kp, stream, A,
-                       (int)M, (int)K, lda, pos_dev, seg_dev, ap, s_a, packed, ximg);
-    if (ximg_done) *ximg_done = ximg != nullptr;
-    return hipGetLastError();
-  }
-  if (aligned && !sign && M * K >= kCoopMinElems) {
+  if (vec && !sign && M * K >= kCoopMinElems) {
     hipError_t e = hipSuccess;
-    if (launch_act_coop(A, M, K, lda, ap, pos_dev, counter, s_a, packed, stream, e))
+    if (launch_act_coop(A, M, K, lda, ap, pos4_dev, counter, s_a, packed, stream, e))
       return e;
   }
   int nparts;
-  if (aligned && M <= 16 * (int64_t)kAbsmaxBlocks) {
+  if (vec && M <= 16 * (int64_t)kAbsmaxBlocks) {
     // 8 (or 16) rows per workgroup keep the grid within the partial buffer
-    const int K4 = (int)(K / 4);
+    const int K4 = (int)((K + 3) / 4);
     const int RB = M <= 8 * (int64_t)kAbsmaxBlocks ? 8 : 16;
     const int64_t blocks = (M + RB - 1) / RB;
     nparts = (int)blocks;
     const int J = K4 <= 256 ? 1 : K4 <= 512 ? 2 : K4 <= 768 ? 3 : 4;
-    const float4* A4 = reinterpret_cast<const float4*>(A);
-    const uchar4* s4 = reinterpret_cast<const uchar4*>(seg_dev);
+    const uchar4* s4 = reinterpret_cast<const uchar4*>(seg4_dev);
 #define SONIQ_ABSMAX(J_, RB_)                                                                   \
-  hipLaunchKernelGGL((k_absmax_blk<J_, RB_>), dim3((unsigned)blocks), dim3(256), 0, stream, A4, M, \
-                     K4, lda / 4, s4, partial)
+  hipLaunchKernelGGL((k_absmax_blk<J_, RB_>), dim3((unsigned)blocks), dim3(256), 0, stream, A, M, \
+                     (int)K, lda, s4, partial)
     if (RB == 8) {
       if (J == 1) SONIQ_ABSMAX(1, 8); else if (J == 2) SONIQ_ABSMAX(2, 8);
       else if (J == 3) SONIQ_ABSMAX(3, 8); else SONIQ_ABSMAX(4, 8);
@@ -5477,15 +5434,16 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // groups of 1-bit sign codes, and unaligned rows, take the generic
+  // groups of 1-bit sign codes, and rows of fewer than four values, take the
   // per-element quantizer (J = 0); otherwise J float4 positions per thread
-  const int K4 = (int)(K / 4);
-  const int J = (sign || !aligned) ? 0 : K4 <= 256 ? 1 : K4 <= 512 ? 2 : K4 <= 768 ? 3 : 4;
+  const int K4 = (int)((K + 3) / 4);
+  const int J = (sign || !vec) ? 0 : K4 <= 256 ? 1 : K4 <= 512 ? 2 : K4 <= 768 ? 3 : 4;
 #define SONIQ_ACT_ROWS(R_, J_)                                                                  \
   hipLaunchKernelGGL((k_act_rows<R_, J_>),                                                      \
                      dim3((unsigned)(R_ == 4 ? ((M + 127) / 128) * 32 : (M + R_ - 1) / R_)),    \
                      dim3(256),                                                                 \
-                     (size_t)R_ * ap.Kp, stream, A, M, K, lda, pos_dev, seg_dev, ap, partial,    \
+                     (size_t)R_ * ap.Kp, stream, A, M, K, lda, J_ ? pos4_dev : pos_dev,         \
+                     J_ ? seg4_dev : seg_dev, ap, partial,                                      \
                      nparts, s_a, packed, ximg)
   // whole 8- or 16-row block slices per workgroup for larger batches
   // 16 rows per workgroup once that still gives ~1.5 workgroups per CU,
@@ -5495,7 +5453,7 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
     const size_t lds = (size_t)rbk * ap.Kp;
 #define SONIQ_BLK(J_, RB_)                                                                       \
   hipLaunchKernelGGL((k_act_blk16<J_, RB_>), dim3((unsigned)((M + RB_ - 1) / RB_)), dim3(256), lds, \
-                     stream, A, M, K, lda, pos_dev, seg_dev, ap, partial, nparts, s_a, packed)
+                     stream, A, M, K, lda, pos4_dev, seg4_dev, ap, partial, nparts, s_a, packed)
     if (rbk == 8) {
       if (J == 1) SONIQ_BLK(1, 8); else if (J == 2) SONIQ_BLK(2, 8); else SONIQ_BLK(3, 8);
     } else {
@@ -6049,39 +6007,23 @@ hipError_t launch_mp_gemv_grouped(const uint8_t* act_packed, const float* s_a, c
 // rows (at most kGAbsParts of them), block scales, then codes.
 hipError_t launch_act_quant_grouped(const float* A, int64_t M, int64_t K, int64_t lda,
                                     const ActPlan& ap, const int32_t* pos_dev,
-                                    const int32_t* grp_dev, const int32_t* posg_dev,
+                                    const int32_t* grp_dev, const int32_t* posg4_dev,
                                     float* partial, unsigned int* counter, float* s_a,
                                     uint8_t* packed, hipStream_t stream) {
   const int nsub = ap.nsub[0] + (ap.S == 2 ? ap.nsub[1] : 0);
   const size_t tab = (size_t)nsub * 8;
   const bool aligned = (K % 4 == 0) && (lda % 4 == 0) && (reinterpret_cast<uintptr_t>(A) % 16 == 0);
   // one pass over the rows when the batch fits one resident grid
-  if (aligned && M * K >= kCoopMinElems) {
+  if (K >= 4 && M * K >= kCoopMinElems) {
     hipError_t e = hipSuccess;
-    if (launch_act_coop(A, M, K, lda, ap, posg_dev, counter, s_a, packed, stream, e, true)) return e;
+    if (launch_act_coop(A, M, K, lda, ap, posg4_dev, counter, s_a, packed, stream, e, true)) return e;
   }
+  // small batches: one launch, with a granule maximum per planned position
+  const size_t blds = (size_t)ap.Kp * 5 + (size_t)nsub * 12;
+  if (act_batch_takes(M, K) && blds <= 64 * 1024)
+    return launch_act_batch<true>(A, M, K, lda, ap, posg4_dev, s_a, packed, stream, nullptr, blds);
   const int K4 = (int)(K / 4);
   const int J = (K4 + 255) / 256;
-  if (aligned && J <= 4 && M <= 8 && (size_t)ap.Kp + 3 * tab / 2 <= 64 * 1024) {
-    // decode batches: one launch, every row loaded once per workgroup
-    const size_t lds = (size_t)ap.Kp + (size_t)nsub * 12;
-    const float4* A4 = reinterpret_cast<const float4*>(A);
-    const int4* g4 = reinterpret_cast<const int4*>(grp_dev);
-    const int4* p4 = reinterpret_cast<const int4*>(pos_dev);
-#define SONIQ_GR(J_, MT_)                                                                      \
-  hipLaunchKernelGGL((k_gact_rows<J_, MT_>), dim3((unsigned)M), dim3(256), lds, stream, A4, (int)M, \
-                     K4, lda / 4, p4, g4, ap, nsub, s_a, packed)
-#define SONIQ_GR_J(MT_)                                                                     \
-  if (J == 1) SONIQ_GR(1, MT_); else if (J == 2) SONIQ_GR(2, MT_); else if (J == 3) SONIQ_GR(3, MT_); \
-  else SONIQ_GR(4, MT_)
-    if (M == 1) { SONIQ_GR_J(1); }
-    else if (M == 2) { SONIQ_GR_J(2); }
-    else if (M <= 4) { SONIQ_GR_J(4); }
-    else { SONIQ_GR_J(8); }
-#undef SONIQ_GR_J
-#undef SONIQ_GR
-    return hipGetLastError();
-  }
   if (aligned && J <= 4) {
     // four rows per workgroup at least, else up to kGAbsParts row ranges
     const int64_t rpb = std::max<int64_t>(4, (M + kGAbsParts - 1) / kGAbsParts);
