@@ -15,11 +15,12 @@
 //                   in registers right before v_mfma_i32_16x16x64_i8, one
 //                   int32 accumulator set per activation group, fixed-order
 //                   fp32 epilogue to bf16
-//   k_gemv          batch <= 8 without matrix cores: one workgroup streams
+//   k_gemv          one row without matrix cores: one workgroup streams
 //                   one 16-row weight block, v_dot8_i32_i4 on nibbles or
 //                   v_dot4_i32_i8 on bytes against activations in LDS
-//   k_gemv_mfma     batch 2..8: one workgroup per weight block, the batch
-//                   rows as the MFMA A operand, straight from global memory
+//   k_gemv_mm       batches of up to 8 rows, with or without sub-group
+//                   scales: one workgroup per weight block, both operands'
+//                   units straight from global memory into the MFMA
 //
 // Paper passages: Sec. 2.4 C1/C2/C5; Sec. 3 codec (group max-abs scale,
 // unsigned codes, Eq. 1 weight codes); Alg. 1 channel permutation and Phase
@@ -3690,15 +3691,10 @@ __device__ __forceinline__ void gemv_store_out(const GemmArgs& a, int p, int64_t
 
 // FJ > 0 (batch of one row only): the fused form, which quantizes the fp32
 // row itself (FJ float4 per thread) instead of staging packed units.
-// GB: sub-group activation scales (zero points 0, no 1-bit weights): each
-// slot's products are summed over the lanes of its rows and added into one
-// exact int32 sum per activation block in LDS (after the staged rows), and
-// the epilogue folds the blocks in order as the MFMA GEMM does.
-template <int MT, int CW, bool NIB, int FJ = 0, bool GB = false>
+template <int CW, bool NIB, int FJ = 0>
 __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int blk,
-                                            int (&red)[4][4][kBlk][2][MT]) {
-  static_assert(FJ == 0 || MT == 1, "the fused form takes one row");
-  static_assert(!GB || (FJ == 0 && CW != 1), "block sums: no fused form, no sign-bit weights");
+                                            int (&red)[4][4][kBlk][2][1]) {
+  constexpr int MT = 1;
   constexpr int U = 8 / CW;
   constexpr int CPG = 8 * CW;    // chunks per granule
   constexpr int QS = 256 / CPG;  // granules per slot of the workgroup
@@ -3770,56 +3766,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
       }
     }
   };
-  // GB: exact per-block sums in LDS, [block][batch row][block row]
-  int* gacc = reinterpret_cast<int*>(xs + a.xs_bytes);
-  const int gl16 = lane & 15;
-  auto gadd = [&](int j, int (&v)[U][MT]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int mm = 0; mm < MT; ++mm) v[u][mm] = dpp_row_sum<CW>(v[u][mm]);
-    if (gl16 < 2 * CW) {
-#pragma unroll
-      for (int mm = 0; mm < MT; ++mm)
-        if (mm < M)
-#pragma unroll
-          for (int u = 0; u < U; ++u) atomicAdd(&gacc[(j * MT + mm) * kBlk + U * gl16 + u], v[u][mm]);
-    }
-  };
   auto consume0 = [&](int s0, const uint4 (&raw)[NB0]) __attribute__((always_inline)) {
-    if constexpr (GB) {
-      // one slot's granule lies in one block; a 16-lane row of lanes never
-      // spans two granules (CW >= 2)
-      const int gpg = ap.gsub[0];
-#pragma unroll
-      for (int b = 0; b < NB0; ++b) {
-        if (256 * (s0 + b) >= nch0) break;  // the same for the whole workgroup
-        const int q = q0 + QS * (s0 + b);
-        int v[U][MT];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int mm = 0; mm < MT; ++mm) v[u][mm] = 0;
-        if constexpr (NIB) {
-#pragma unroll
-          for (int mm = 0; mm < MT; ++mm) {
-            if (mm < M) {
-              const uint2 xq = *reinterpret_cast<const uint2*>(
-                  xs + (mm * ng0 + min(q, ng0 - 1)) * 32 + kg * 8);
-#pragma unroll
-              for (int u = 0; u < U; ++u) {
-                const uint2 w = chunk_nibbles<CW>(raw[b], u);
-                v[u][mm] = dot16n(w.x, w.y, xq, 0);
-              }
-            }
-          }
-        } else {
-          bytes_into(v, raw[b], min(q, ng0 - 1), true);
-        }
-        if (q < ng0) gadd(q / gpg, v);
-      }
-      return;
-    }
     if constexpr (NIB) {
       // every slot's staged activations first (one LDS round trip), then
       // the products slot by slot as the chunks land
@@ -3854,22 +3801,6 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     }
   };
   auto consume1 = [&](int s0, const uint4 (&raw)[NB1]) __attribute__((always_inline)) {
-    if constexpr (GB) {
-      const int gpg = ap.gsub[1];
-#pragma unroll
-      for (int b = 0; b < NB1; ++b) {
-        if (256 * (s0 + b) >= nch1) break;  // the same for the whole workgroup
-        const int q = q0 + QS * (s0 + b);
-        int v[U][MT];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int mm = 0; mm < MT; ++mm) v[u][mm] = 0;
-        bytes_into(v, raw[b], ng0 + min(q, ng1 - 1), true);
-        if (q < ng1) gadd(ap.nsub[0] + q / gpg, v);
-      }
-      return;
-    }
 #pragma unroll
     for (int b = 0; b < NB1; ++b) {
       if (256 * (s0 + b) >= nch1) break;  // the same for the whole workgroup
@@ -4015,10 +3946,6 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     issue0(0, raw0);
     issue1(0, raw1);
     if (!more_x) store_x(0);
-    if constexpr (GB) {
-      const int nsub = ap.nsub[0] + (ap.S == 2 ? ap.nsub[1] : 0);
-      for (int i = tid; i < nsub * MT * kBlk; i += 256) gacc[i] = 0;
-    }
     // The staged rows must be visible to every wave, but the weight chunks
     // may still be in flight: wait for LDS writes only, then a plain
     // barrier (a full __syncthreads would also drain every chunk load).
@@ -4038,24 +3965,6 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     consume1(s0, raw);
   }
 
-  if constexpr (GB) {
-    // every block sum is in LDS: fold the blocks in order, multiply then
-    // add (y = sum_j f(ACC_j) * s_a[j]), then scale by s_w
-    __syncthreads();
-    if (tid < kBlk * M && eci.n >= 0) {
-      const int nsub0 = ap.nsub[0], nsub = nsub0 + (ap.S == 2 ? ap.nsub[1] : 0);
-      const int shb0 = NIB ? (CW == 2 ? 2 : 0) : ap.sh[0] + (eshw & 0x7F);
-      const int shb1 = ap.sh[1] + (eshw & 0x7F);
-      float y = 0.0f;
-      for (int j = 0; j < nsub; ++j) {
-        const int t = gacc[(j * MT + em) * kBlk + er] >> (j < nsub0 ? shb0 : shb1);
-        y = __fadd_rn(y, __fmul_rn((float)t, a.s_a[j]));
-        if (a.acc) a.acc[((int64_t)j * a.M + em) * a.N + eci.n] = t;
-      }
-      gemv_store_out(a, ep, em, eci.n, __fmul_rn(y, eci.s_w));
-    }
-    return;
-  }
   // Within each 16-lane row, then rows and waves through LDS.
   const int row16 = lane >> 4, l16 = lane & 15;
 #pragma unroll
@@ -4099,35 +4008,16 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
   }
 }
 
-// Dynamic LDS: the staged rows (see gemv_lds).
-template <int MT>
+// Dynamic LDS: the staged row (see gemv_lds).
 __global__ __launch_bounds__(256) void k_gemv(GemmArgs a) {
   extern __shared__ __align__(16) uint8_t xs[];
-  __shared__ int red[4][4][kBlk][2][MT];
+  __shared__ int red[4][4][kBlk][2][1];
   const int blk = blockIdx.x;
   const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv4_block<MT, 2, true>(a, xs, blk, red);
-  else if (c == 4) gemv4_block<MT, 4, true>(a, xs, blk, red);
-  else if (c == 8) gemv4_block<MT, 8, false>(a, xs, blk, red);
-  // 1-bit blocks keep eight row accumulators per lane and batch row; the
-  // host sends them here only for batches of at most 4 rows, so larger
-  // instances are compiled without that path (and its registers)
-  else if constexpr (MT <= 4) gemv4_block<MT, 1, false>(a, xs, blk, red);
-}
-
-
-// Batches of at most 8 rows whose activations have sub-group scales: the
-// GEMV with one exact int32 sum per activation block.  Dynamic LDS: the
-// staged rows (xs_bytes), then the block sums [nsub][MT][16].
-template <int MT>
-__global__ __launch_bounds__(256) void k_gemv_g(GemmArgs a) {
-  extern __shared__ __align__(16) uint8_t xs[];
-  __shared__ int red[4][4][kBlk][2][MT];
-  const int blk = blockIdx.x;
-  const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv4_block<MT, 2, true, 0, true>(a, xs, blk, red);
-  else if (c == 4) gemv4_block<MT, 4, true, 0, true>(a, xs, blk, red);
-  else gemv4_block<MT, 8, false, 0, true>(a, xs, blk, red);
+  if (c == 2) gemv4_block<2, true>(a, xs, blk, red);
+  else if (c == 4) gemv4_block<4, true>(a, xs, blk, red);
+  else if (c == 8) gemv4_block<8, false>(a, xs, blk, red);
+  else gemv4_block<1, false>(a, xs, blk, red);
 }
 
 // Batch of one row, quantized inside the GEMV: every workgroup computes
@@ -4141,128 +4031,244 @@ __global__ __launch_bounds__(256) void k_gemv_fused(GemmArgs a) {
   __shared__ int red[4][4][kBlk][2][1];
   const int blk = blockIdx.x;
   const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv4_block<1, 2, true, J>(a, xs, blk, red);
-  else if (c == 4) gemv4_block<1, 4, true, J>(a, xs, blk, red);
-  else if (c == 8) gemv4_block<1, 8, false, J>(a, xs, blk, red);
-  else gemv4_block<1, 1, false, J>(a, xs, blk, red);
+  if (c == 2) gemv4_block<2, true, J>(a, xs, blk, red);
+  else if (c == 4) gemv4_block<4, true, J>(a, xs, blk, red);
+  else if (c == 8) gemv4_block<8, false, J>(a, xs, blk, red);
+  else gemv4_block<1, false, J>(a, xs, blk, red);
 }
 
-// ----------------------------------------------------------- k_gemv_mfma --
-// Batches of 2..8 rows with activation containers 4 (group 0) and 8
-// (group 1): one workgroup per 16-row weight block, as in k_gemv, but the
-// products run on v_mfma_i32_16x16x64_i8 with the batch rows as the A
-// operand (rows past M are never read out) and the block's 16 weight rows
-// as B.  The block's bytes go global -> LDS in 16-byte chunks, all in
-// flight at once; both buffers are fragment-major, so lane l reads unit l
-// of a granule as its operand (the activations straight from global
-// memory, where every workgroup finds them in L2).  Wave w takes granules
-// w, w + 4, ... of each group in batches of kMB; the four partial 16x16
-// sums per group meet in LDS and the block's 16 columns get the GEMM's
-// exact epilogue.  Dynamic LDS: the largest block (ngt * 128 * c_hi bytes)
-// rounded up to 1 KB.
-constexpr int kMB = 4;
-
+// ------------------------------------------------------------- k_gemv_mm --
+// Batches of up to 8 rows with activation containers 4 (group 0) and 8
+// (group 1) on v_mfma_i32_16x16x64_i8: one workgroup per 16-row weight
+// block, the batch rows as the A operand (lanes of rows past M load
+// nothing and hold zeros) and the block's 16 weight rows as B.
+//
+// Bound by latency and by what is in flight: a decode layer is 5 to 30 MB
+// spread over a few thousand waves.  Both operands are fragment-major, so a
+// wave loads its units straight into the registers the MFMA reads (2*CW
+// bytes a lane, consecutive lanes consecutive units), weights and
+// activations of a granule together and all granules of its share at once:
+// the products start as the first granule lands, with no staging and no
+// barrier before the reduction.  Staging the block in LDS first took 6.9 us
+// at 8 x 11008 x 4096 (2/4-bit weights), this 5.2, of which an empty launch
+// is 1.8; loading all weights before the activations 6.0.  Four waves per
+// block: two 5.6, eight 8.1 us (each wave's unused slots are issued all the
+// same).
+//
+// A wave takes chunks of 512 bits of activations (two granules of group 0,
+// one of group 1): chunks w, w + 4, ... of each group.  GB: sub-group
+// scales, in blocks of whole chunks.  With one chunk per block (512 bits)
+// the wave that sums a chunk also scales it, f(sum) * s_a, and the fold
+// that remains is one chain of fp32 additions in block order per output,
+// over products read four at a time (pad products are -0, which an addition
+// ignores).  Larger blocks, or accumulators asked for, keep the chunks'
+// integer sums and fold those.  8 x 11008 x 4096: 7.5 us, where summing
+// slots into LDS words by atomics and folding took 21.9.
+// Dynamic LDS (gemv_mm_lds): GB: (M + 1) * 16 outputs of `ld` words, else
+// (M + 1) rows of 8 partial sums of 16 columns; row M takes the lanes of
+// rows past M.
 template <int CW>
-__device__ __forceinline__ void gemv_mfma_block(const GemmArgs& a, int blk, uint8_t* wl,
-                                                int (&red)[4][2][4][64]) {
+__device__ __forceinline__ raw_t<CW> mm_load_w(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  if constexpr (CW == 8)
+    return __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+  else if constexpr (CW == 4)
+    return __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+  else if constexpr (CW == 2)
+    return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+  else
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
+}
+
+// 512-bit chunks of a plan (group 0: pairs of granules), and the words an
+// output's chunks take in LDS (a multiple of 4 that is not one of 8, so
+// that neighbouring outputs start in different banks).
+__host__ __device__ inline int gemv_mm_chunks(int ng0, int ng1) { return (ng0 + 1) / 2 + ng1; }
+__host__ __device__ inline int gemv_mm_ld(int nch) { return (nch + 3) / 8 * 8 + 4; }
+constexpr int kMmRow = 8 * 16 + 4;  // words of one row's partial sums
+
+template <int CW, bool GB>
+__device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* red) {
+  constexpr int C0 = CW == 8 ? 4 : 7, C1 = 4;  // chunks in flight per round
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const ActPlan& ap = a.ap;
-  const int ngt = a.wp.ngt, ng0 = ap.ng[0], ng1 = ngt - ng0;
-  {
-    const int nch = ngt * 8 * CW;  // 16-byte chunks of the block
-    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.wd.packed + wblk_off(a.wp, blk)), (short)0, nch * 16, 0x00020000);
-    const uint32_t base = lds_off(wl);
-    // a wave's 64 chunks land at base + 16 * (256i + 64 wid + lane); waves
-    // wholly past the block skip, the last partial one writes zeros up to
-    // the next 64-chunk boundary (the allocation covers it)
-    for (int i = 0; 256 * i < nch; ++i) {
-      const int ch = 256 * i + tid;
-      if (256 * i + 64 * wid < nch)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            wr, (__attribute__((address_space(3))) void*)(uintptr_t)(base + (256 * i + 64 * wid) * 16),
-            16, ch < nch ? (uint32_t)ch * 16 : kOOB, 0, 0, 0);
-    }
-  }
-  const uint8_t* x0 = a.act + ap.seg_off[0] + lane * 8;
-  const uint8_t* x1 = a.act + (ap.S == 2 ? ap.seg_off[1] : 0) + lane * 16;
+  const int M = (int)a.M, ngt = a.wp.ngt, ng0 = ap.ng[0], ng1 = ngt - ng0;
+  const int nc0 = (ng0 + 1) / 2, nch = gemv_mm_chunks(ng0, ng1);
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(a.wd.packed + wblk_off(a.wp, blk)), (short)0, ngt * 128 * CW, 0x00020000);
+  // the activations: a single row's contiguous image, or the packed units
+  const bool cx = a.ximg != nullptr;
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(cx ? a.ximg : a.act), (short)0,
+      cx ? 32 * ng0 + 64 * ng1
+         : (int)(ap.S == 2 ? ap.seg_off[1] + ap.mblk_bytes[1] : ap.seg_off[0] + ap.mblk_bytes[0]),
+      0x00020000);
+  const bool xrow = (lane & 15) < M;
+  const uint32_t xo0 = cx ? (uint32_t)(lane >> 4) * 8 : (uint32_t)ap.seg_off[0] + lane * 8;
+  const uint32_t xo1 =
+      cx ? (uint32_t)(32 * ng0 + (lane >> 4) * 16) : (uint32_t)ap.seg_off[1] + lane * 16;
+  const uint32_t xs0 = cx ? 32u : 512u, xs1 = cx ? 64u : 1024u;
   // epilogue inputs, requested before the stream lands
-  const int pc = blk * kBlk + (lane & 15);
-  const ColInfo ci = a.wd.colinfo[pc];
-  const uint8_t shw = a.wd.shw[pc];
-  const float sa0 = a.s_a[0], sa1 = ap.S == 2 ? a.s_a[1] : 0.0f;
-  wait_vm<0>();
-  __syncthreads();
-
-  auto wunit = [&](int q) __attribute__((always_inline)) {
-    uint4 r = make_uint4(0u, 0u, 0u, 0u);
-    const uint8_t* p = wl + (q * 64 + lane) * 2 * CW;
-    if constexpr (CW == 8) r = *reinterpret_cast<const uint4*>(p);
-    else if constexpr (CW == 4) { const uint2 v = *reinterpret_cast<const uint2*>(p); r.x = v.x; r.y = v.y; }
-    else if constexpr (CW == 2) r.x = *reinterpret_cast<const uint32_t*>(p);
-    else r.x = *reinterpret_cast<const uint16_t*>(p);
-    return r;
-  };
-  v4i acc0 = v4i{0, 0, 0, 0}, acc1 = v4i{0, 0, 0, 0};
-  for (int q = wid; q < ng0; q += 4 * kMB) {
-    uint2 xa[kMB];
-#pragma unroll
-    for (int i = 0; i < kMB; ++i) xa[i] = *reinterpret_cast<const uint2*>(x0 + min(q + 4 * i, ng0 - 1) * 512);
-#pragma unroll
-    for (int i = 0; i < kMB; ++i)
-      if (q + 4 * i < ng0)
-        acc0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(frag_of(unpack4(xa[i].x, xa[i].y)),
-                                                     frag_of(unpack_unit<CW>(wunit(q + 4 * i))),
-                                                     acc0, 0, 0, 0);
+  const int en = tid & 15, em = tid >> 4;
+  const int ep = blk * kBlk + en;
+  const ColInfo ci = a.wd.colinfo[ep];
+  const uint8_t shw = a.wd.shw[ep];
+  const int sh0 = ap.sh[0] + (shw & 0x7F), sh1 = ap.sh[1] + (shw & 0x7F);
+  float sa0 = 0.0f, sa1 = 0.0f;
+  if constexpr (!GB) {
+    sa0 = a.s_a[0];
+    sa1 = ap.S == 2 ? a.s_a[1] : 0.0f;
   }
-  for (int q = wid; q < ng1; q += 4 * kMB) {
-    uint4 xa[kMB];
-#pragma unroll
-    for (int i = 0; i < kMB; ++i) xa[i] = *reinterpret_cast<const uint4*>(x1 + min(q + 4 * i, ng1 - 1) * 1024);
-#pragma unroll
-    for (int i = 0; i < kMB; ++i)
-      if (q + 4 * i < ng1)
-        acc1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(frag_of(xa[i]),
-                                                     frag_of(unpack_unit<CW>(wunit(ng0 + q + 4 * i))),
-                                                     acc1, 0, 0, 0);
-  }
+  const int nsub0 = GB ? ap.nsub[0] : 0, nsub = GB ? nsub0 + (ap.S == 2 ? ap.nsub[1] : 0) : 0;
+  const bool scaled = GB && ap.gsub[0] == 2 && a.acc == nullptr;
+  const int ld = gemv_mm_ld(nch);
+  // lane l's sum e is batch row 4*(l / 16) + e, column l % 16; its column's
+  // shifts are the epilogue's (tid % 16 = lane % 16)
+  int pb[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    red[wid][0][e][lane] = acc0[e];
-    red[wid][1][e][lane] = acc1[e];
+    const int m = min((lane >> 4) * 4 + e, M);
+    pb[e] = GB ? (m * 16 + (lane & 15)) * ld : m * kMmRow + (lane & 15);
+  }
+  auto put = [&](int j, const v4i& v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[pb[e] + j] = v[e];
+  };
+  auto put_chunk = [&](int j, const v4i& v, int sh, float sc) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      red[pb[e] + j] = scaled ? __float_as_int(__fmul_rn((float)(v[e] >> sh), sc)) : v[e];
+  };
+
+  float f0[C0], f1[C1];
+  raw_t<CW> w0[2 * C0], w1[C1];
+  uint2 x0[2 * C0];
+  uint4 x1[C1];
+  // granule i of a round: its chunk's half with blocks, else every fourth
+  auto gran0 = [&](int s0, int i) { return GB ? (wid + 4 * (s0 + i / 2)) * 2 + (i & 1) : wid + 4 * (2 * s0 + i); };
+  auto load = [&](int s0, int s1) __attribute__((always_inline)) {
+    if constexpr (GB) {
+#pragma unroll
+      for (int c = 0; c < C0; ++c) f0[c] = a.s_a[min(wid + 4 * (s0 + c), nsub - 1)];
+#pragma unroll
+      for (int c = 0; c < C1; ++c) f1[c] = a.s_a[min(nsub0 + wid + 4 * (s1 + c), nsub - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * C0; ++i) {
+      const int q = gran0(s0, i);
+      w0[i] = mm_load_w<CW>(wr, q < ng0 ? (uint32_t)(q * 128 * CW + lane * 2 * CW) : kOOB);
+      x0[i] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(
+                                            xr, xrow && q < ng0 ? xo0 + q * xs0 : kOOB, 0, 0));
+    }
+#pragma unroll
+    for (int i = 0; i < C1; ++i) {
+      const int q = wid + 4 * (s1 + i);
+      w1[i] = mm_load_w<CW>(wr, q < ng1 ? (uint32_t)((ng0 + q) * 128 * CW + lane * 2 * CW) : kOOB);
+      x1[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                            xr, xrow && q < ng1 ? xo1 + q * xs1 : kOOB, 0, 0));
+    }
+    // no load sinks below this point to its product
+    asm volatile("" ::: "memory");
+  };
+  v4i acc0 = v4i{0, 0, 0, 0}, acc1 = v4i{0, 0, 0, 0};
+  // granules past a group's end hold zero activations: their products are 0
+  auto use = [&](int s0, int s1) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < C0; ++c) {
+      v4i t = GB ? v4i{0, 0, 0, 0} : acc0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        t = __builtin_amdgcn_mfma_i32_16x16x64_i8(frag_of(unpack4(x0[2 * c + h].x, x0[2 * c + h].y)),
+                                                  unpack_frag<CW>(w0[2 * c + h]), t, 0, 0, 0);
+      if constexpr (GB) {
+        const int j = wid + 4 * (s0 + c);
+        if (j < nc0) put_chunk(j, t, sh0, f0[c]);
+      } else {
+        acc0 = t;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < C1; ++c) {
+      const v4i t = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+          frag_of(x1[c]), unpack_frag<CW>(w1[c]), GB ? v4i{0, 0, 0, 0} : acc1, 0, 0, 0);
+      if constexpr (GB) {
+        const int j = wid + 4 * (s1 + c);
+        if (j < ng1) put_chunk(nc0 + j, t, sh1, f1[c]);
+      } else {
+        acc1 = t;
+      }
+    }
+  };
+  load(0, 0);
+  if constexpr (GB)
+    for (int i = tid; i < M * kBlk * 8; i += 256)
+      if (nch + (i & 7) < ld) red[(i >> 3) * ld + nch + (i & 7)] = (int)0x80000000;  // -0.0
+  use(0, 0);
+  for (int s0 = C0, s1 = C1; gran0(s0, 0) < ng0 || wid + 4 * s1 < ng1; s0 += C0, s1 += C1) {
+    load(s0, s1);
+    use(s0, s1);
+  }
+  if constexpr (!GB) {
+    put(32 * wid, acc0);
+    put(32 * wid + 16, acc1);
   }
   __syncthreads();
-  if (wid == 0 && ci.n >= 0) {
-    const int sh0 = ap.sh[0] + (shw & 0x7F), sh1 = ap.sh[1] + (shw & 0x7F);
-    const int add0 = ap.zp[0] * ci.colsum[0], add1 = ap.zp[1] * ci.colsum[1];
+  if (em >= M || ci.n < 0) return;
+  if constexpr (GB) {
+    float y = 0.0f;
+    const int* rr = red + (em * kBlk + en) * ld;
+    if (scaled) {
+      const float4* pr = reinterpret_cast<const float4*>(rr);
+      for (int j = 0; j < ld / 4; j += 4) {
+        float4 v[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int m = (lane >> 4) * 4 + e;  // batch row of this lane's sum e
-      if (m < a.M) {
-        const int r0 = red[0][0][e][lane] + red[1][0][e][lane] + red[2][0][e][lane] + red[3][0][e][lane];
-        const int r1 = red[0][1][e][lane] + red[1][1][e][lane] + red[2][1][e][lane] + red[3][1][e][lane];
-        const int t0 = (r0 >> sh0) + add0;
-        const int t1 = ap.S == 2 ? (r1 >> sh1) + add1 : 0;
-        gemv_store_out(a, pc, m, ci.n, epilogue(t0, t1, ap.S, sa0, sa1, ci.s_w));
-        if (a.acc) {
-          a.acc[(int64_t)m * a.N + ci.n] = t0;
-          if (ap.S == 2) a.acc[(a.M + m) * a.N + ci.n] = t1;
-        }
+        for (int u = 0; u < 4; ++u) v[u] = pr[min(j + u, ld / 4 - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (j + u < ld / 4)
+            y = __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(y, v[u].x), v[u].y), v[u].z), v[u].w);
       }
+    } else {
+      const int per = ap.gsub[0] / 2;  // chunks of a block
+      for (int j = 0; j < nsub; ++j) {
+        const bool g1 = j >= nsub0;
+        const int c0 = g1 ? nc0 + (j - nsub0) * per : j * per;
+        const int c1 = min(c0 + per, g1 ? nch : nc0);
+        int t = 0;
+        for (int c = c0; c < c1; ++c) t += rr[c];
+        t >>= g1 ? sh1 : sh0;
+        y = __fadd_rn(y, __fmul_rn((float)t, a.s_a[j]));
+        if (a.acc) a.acc[((int64_t)j * a.M + em) * a.N + ci.n] = t;
+      }
+    }
+    gemv_store_out(a, ep, em, ci.n, __fmul_rn(y, ci.s_w));
+  } else {
+    const int* rr = red + em * kMmRow + en;
+    int r0 = 0, r1 = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      r0 += rr[32 * w];
+      r1 += rr[32 * w + 16];
+    }
+    const int t0 = (r0 >> sh0) + ap.zp[0] * ci.colsum[0];
+    const int t1 = ap.S == 2 ? (r1 >> sh1) + ap.zp[1] * ci.colsum[1] : 0;
+    gemv_store_out(a, ep, em, ci.n, epilogue(t0, t1, ap.S, sa0, sa1, ci.s_w));
+    if (a.acc) {
+      a.acc[(int64_t)em * a.N + ci.n] = t0;
+      if (ap.S == 2) a.acc[(a.M + em) * a.N + ci.n] = t1;
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_gemv_mfma(GemmArgs a) {
-  extern __shared__ __align__(16) uint8_t wl[];
-  __shared__ int red[4][2][4][64];
+template <bool GB>
+__global__ __launch_bounds__(256) void k_gemv_mm(GemmArgs a) {
+  extern __shared__ __align__(16) int mred[];
   const int blk = blockIdx.x;
   const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv_mfma_block<2>(a, blk, wl, red);
-  else if (c == 4) gemv_mfma_block<4>(a, blk, wl, red);
-  else if (c == 8) gemv_mfma_block<8>(a, blk, wl, red);
-  else gemv_mfma_block<1>(a, blk, wl, red);
+  if (c == 2) gemv_mm_block<2, GB>(a, blk, mred);
+  else if (c == 4) gemv_mm_block<4, GB>(a, blk, mred);
+  else if (c == 8) gemv_mm_block<8, GB>(a, blk, mred);
+  else gemv_mm_block<1, GB>(a, blk, mred);
 }
 
 // ------------------------------------------------- single-pass quantize --
@@ -5593,19 +5599,9 @@ hipError_t launch_mp_gemm(const uint8_t* act_packed, const float* s_a, const Act
 // The GEMM with the next layer's quantization in its epilogue (64 x 128
 // tiles at every batch size; k_gemm_g when the producer's activations have
 // sub-group scales), then the packing of that layer's rows.
-static size_t gemv_lds(int64_t M, const ActPlan& ap, const WPlan& wp);
-static size_t gemv_g_lds(int64_t M, const ActPlan& ap, const WPlan& wp);
+static size_t gemv_mm_lds(int64_t M, const ActPlan& ap);
+static void launch_gemv_form(const GemmArgs& a, hipStream_t stream);
 static bool gemv_nibble_plan(const ActPlan& ap);
-
-// k_gemv_mfma's dynamic LDS: the largest weight block in whole 64-chunk
-// (1 KB) wave batches; it applies when that and the static reduction
-// buffer (8 KB) fit in 64 KB.
-static size_t gemv_mfma_lds(const WPlan& wp) {
-  return (size_t)(wp.ngt * 8 * wp.c_hi + 63) / 64 * 1024;
-}
-static bool gemv_mfma_fits(const WPlan& wp) {
-  return gemv_mfma_lds(wp) + sizeof(int) * 2048 <= 64 * 1024;
-}
 
 template <int S, int CA0, int CA1, int CBL, int CBH>
 static void launch_gemm_qn_t(const GemmArgs& a, int64_t M, hipStream_t stream) {
@@ -5698,24 +5694,8 @@ hipError_t launch_mp_gemm_qnext(const uint8_t* act_packed, const float* s_a, con
     else if (cl == 1 && ch == 1) launch_gemm_qn_conv_t<1, 1>(a, M, stream);
     else launch_gemm_qn_conv_t<4, 8>(a, M, stream);
   } else if (gemv_form) {
-    a.xs_bytes = (int)((gemv_lds(M, ap, wp) + 15) / 16 * 16);
     if (M == 1 && gv) a.ximg = const_cast<uint8_t*>(ximg);
-    const dim3 grid((unsigned)wp.nblk);
-    if (gv_g) {
-      const size_t lds = gemv_g_lds(M, ap, wp);
-      if (M == 1) hipLaunchKernelGGL(k_gemv_g<1>, grid, dim3(256), lds, stream, a);
-      else if (M == 2) hipLaunchKernelGGL(k_gemv_g<2>, grid, dim3(256), lds, stream, a);
-      else if (M <= 4) hipLaunchKernelGGL(k_gemv_g<4>, grid, dim3(256), lds, stream, a);
-      else hipLaunchKernelGGL(k_gemv_g<8>, grid, dim3(256), lds, stream, a);
-    } else if (M >= 2 && gemv_mfma_fits(wp)) {
-      hipLaunchKernelGGL(k_gemv_mfma, grid, dim3(256), gemv_mfma_lds(wp), stream, a);
-    } else {
-      const size_t lds = gemv_lds(M, ap, wp);
-      if (M == 1) hipLaunchKernelGGL(k_gemv<1>, grid, dim3(256), lds, stream, a);
-      else if (M == 2) hipLaunchKernelGGL(k_gemv<2>, grid, dim3(256), lds, stream, a);
-      else if (M <= 4) hipLaunchKernelGGL(k_gemv<4>, grid, dim3(256), lds, stream, a);
-      else hipLaunchKernelGGL(k_gemv<8>, grid, dim3(256), lds, stream, a);
-    }
+    launch_gemv_form(a, stream);
   } else if (ap.S == 2 && ap.c[0] == 4 && ap.c[1] == 8) {
     if (cl == 4 && ch == 8) launch_gemm_qn_t<2, 4, 8, 4, 8>(a, M, stream);
     else if (cl == 2 && ch == 8) launch_gemm_qn_t<2, 4, 8, 2, 8>(a, M, stream);
@@ -5887,10 +5867,12 @@ hipError_t launch_act_bf16(const uint16_t* Y, int64_t M, int64_t K, int64_t ldy,
 
 bool gemv_fits(int64_t M, const ActPlan& ap, const WPlan& wp) {
   if (M < 1 || M > 8) return false;
-  // dynamic LDS (activation rows) plus the static reduction buffer
-  if (gemv_lds(M, ap, wp) + (size_t)2048 * 8 > 64 * 1024) return false;
-  // 1-bit weight blocks keep 8 rows per lane: at most 4 activation rows.
-  if ((wp.c_lo == 1 || wp.c_hi == 1) && M > 4) return false;
+  if (!gemv_nibble_plan(ap)) {
+    // k_gemv_any: dynamic LDS (activation rows) plus the static reduction
+    // buffer; 1-bit weight blocks keep 8 rows per lane, so at most 4 rows
+    if ((size_t)M * ap.Kp + (size_t)2048 * 8 > 64 * 1024) return false;
+    if ((wp.c_lo == 1 || wp.c_hi == 1) && M > 4) return false;
+  }
   // buffer-resource offsets into the activation and weight buffers are 32-bit
   const int64_t act_end = ap.S == 2 ? ap.seg_off[1] + ap.mblk_bytes[1] : ap.seg_off[0] + ap.mblk_bytes[0];
   if (act_end >= ((int64_t)1 << 31) || (int64_t)wp.ngt * 128 * 8 * 16 >= ((int64_t)1 << 31))
@@ -5904,14 +5886,35 @@ static bool gemv_nibble_plan(const ActPlan& ap) {
   return ap.c[0] == 4 && (ap.S == 1 || ap.c[1] == 8);
 }
 
-// Staged rows: M*Kp bytes as bytes; a nibble-path block needs
-// M*(32*ng0 + 64*ng1) <= M*Kp, which is all a launch needs when every
-// weight block takes the nibble path (2- and 4-bit containers).
-static size_t gemv_lds(int64_t M, const ActPlan& ap, const WPlan& wp) {
+// The staged row of k_gemv: Kp bytes as bytes, or 32*ng0 + 64*ng1 where
+// every weight block takes the nibble path (2- and 4-bit containers).
+static size_t gemv_lds(const ActPlan& ap, const WPlan& wp) {
   const bool all_nib = gemv_nibble_plan(ap) && (wp.c_lo == 2 || wp.c_lo == 4) &&
                        (wp.c_hi == 2 || wp.c_hi == 4);
   const int ng1 = ap.S == 2 ? ap.ng[1] : 0;
-  return all_nib ? (size_t)M * (32 * ap.ng[0] + 64 * ng1) : (size_t)M * ap.Kp;
+  return all_nib ? (size_t)(32 * ap.ng[0] + 64 * ng1) : (size_t)ap.Kp;
+}
+
+// k_gemv_mm's partial sums (or, with blocks, its chunks' products).
+static size_t gemv_mm_lds(int64_t M, const ActPlan& ap) {
+  const int ng1 = ap.S == 2 ? ap.ng[1] : 0;
+  const size_t words = ap.gsub[0] > 0 ? (size_t)kBlk * gemv_mm_ld(gemv_mm_chunks(ap.ng[0], ng1)) : kMmRow;
+  return (size_t)(M + 1) * words * 4;
+}
+
+// The GEMV of a plan with nibbles (and block scales, if any) by the batch:
+// k_gemv for a single row whose staging fits LDS: its 16-byte weight loads
+// leave the dot products less than the MFMA form's narrower ones (4.7
+// against 5.2 us at 1 x 11008 x 4096, 3.0 against 3.3 at 1 x 4096 x 4096,
+// 5.5 against 6.4 at 1 x 4096 x 11008); k_gemv_mm otherwise.
+static void launch_gemv_form(const GemmArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)a.wp.nblk), blk(256);
+  if (a.ap.gsub[0] > 0)
+    hipLaunchKernelGGL(k_gemv_mm<true>, grid, blk, gemv_mm_lds(a.M, a.ap), stream, a);
+  else if (a.M == 1 && gemv_lds(a.ap, a.wp) + (size_t)2048 * 8 <= 64 * 1024)
+    hipLaunchKernelGGL(k_gemv, grid, blk, gemv_lds(a.ap, a.wp), stream, a);
+  else
+    hipLaunchKernelGGL(k_gemv_mm<false>, grid, blk, gemv_mm_lds(a.M, a.ap), stream, a);
 }
 
 bool gemv_fused_fits(const float* A, int64_t K, const ActPlan& ap, const WPlan& wp) {
@@ -5922,7 +5925,7 @@ bool gemv_fused_fits(const float* A, int64_t K, const ActPlan& ap, const WPlan& 
 }
 
 size_t gemv_fused_lds(const ActPlan& ap, const WPlan& wp) {
-  return (gemv_lds(1, ap, wp) + 15) / 16 * 16 + (size_t)ap.Kp;
+  return (gemv_lds(ap, wp) + 15) / 16 * 16 + (size_t)ap.Kp;
 }
 
 hipError_t launch_gemv_fused(const float* A, int64_t K, const uint16_t* pos16_dev, uint8_t* act_packed,
@@ -5936,7 +5939,7 @@ hipError_t launch_gemv_fused(const float* A, int64_t K, const uint16_t* pos16_de
   a.s_a_out = s_a;
   a.act_out = act_packed;
   a.K4 = (int)(K / 4);
-  a.xs_bytes = (int)((gemv_lds(1, ap, wp) + 15) / 16 * 16);
+  a.xs_bytes = (int)((gemv_lds(ap, wp) + 15) / 16 * 16);
   const dim3 grid((unsigned)wp.nblk);
   const size_t lds = gemv_fused_lds(ap, wp);
   if (a.K4 <= 256) hipLaunchKernelGGL(k_gemv_fused<1>, grid, dim3(256), lds, stream, a);
@@ -5951,55 +5954,30 @@ hipError_t launch_mp_gemv(const uint8_t* act_packed, const float* s_a, const Act
                           const uint8_t* ximg) {
   GemmArgs a = make_args(act_packed, s_a, ap, wd, wp, M, N, Y, ldy, acc);
   if (M == 1) a.ximg = const_cast<uint8_t*>(ximg);
-  dim3 grid((unsigned)wp.nblk);
-  const size_t lds = gemv_lds(M, ap, wp);
-  // Batches of 2..8 rows: the products on matrix cores.  SONIQ_GEMV_MFMA
-  // (0: never, 2: for single rows too) overrides the choice for
-  // measurement; results are the same.
-  bool mfma = M >= 2;
-  if (const char* env = getenv("SONIQ_GEMV_MFMA")) mfma = atoi(env) == 2 || (mfma && atoi(env) != 0);
-  if (gemv_nibble_plan(ap) && mfma && gemv_mfma_fits(wp)) {
-    hipLaunchKernelGGL(k_gemv_mfma, grid, dim3(256), gemv_mfma_lds(wp), stream, a);
-  } else if (gemv_nibble_plan(ap)) {
-    if (M == 1) hipLaunchKernelGGL(k_gemv<1>, grid, dim3(256), lds, stream, a);
-    else if (M == 2) hipLaunchKernelGGL(k_gemv<2>, grid, dim3(256), lds, stream, a);
-    else if (M <= 4) hipLaunchKernelGGL(k_gemv<4>, grid, dim3(256), lds, stream, a);
-    else hipLaunchKernelGGL(k_gemv<8>, grid, dim3(256), lds, stream, a);
-  } else {
-    if (M == 1) hipLaunchKernelGGL(k_gemv_any<1>, grid, dim3(256), lds, stream, a);
-    else if (M == 2) hipLaunchKernelGGL(k_gemv_any<2>, grid, dim3(256), lds, stream, a);
-    else if (M <= 4) hipLaunchKernelGGL(k_gemv_any<4>, grid, dim3(256), lds, stream, a);
-    else hipLaunchKernelGGL(k_gemv_any<8>, grid, dim3(256), lds, stream, a);
+  if (gemv_nibble_plan(ap)) {
+    launch_gemv_form(a, stream);
+    return hipGetLastError();
   }
+  const dim3 grid((unsigned)wp.nblk);
+  const size_t lds = (size_t)M * ap.Kp;
+  if (M == 1) hipLaunchKernelGGL(k_gemv_any<1>, grid, dim3(256), lds, stream, a);
+  else if (M == 2) hipLaunchKernelGGL(k_gemv_any<2>, grid, dim3(256), lds, stream, a);
+  else if (M <= 4) hipLaunchKernelGGL(k_gemv_any<4>, grid, dim3(256), lds, stream, a);
+  else hipLaunchKernelGGL(k_gemv_any<8>, grid, dim3(256), lds, stream, a);
   return hipGetLastError();
 }
 
-// The block-sum GEMV (sub-group scales, batches of at most 8 rows): a
-// 4-bit group 0 and an 8-bit group 1, weight containers 2, 4 or 8, and
-// the staged rows plus the block sums within 64 KB of LDS.
-static size_t gemv_g_lds(int64_t M, const ActPlan& ap, const WPlan& wp) {
-  const int64_t MT = M == 1 ? 1 : M == 2 ? 2 : M <= 4 ? 4 : 8;
-  const int nsub = ap.nsub[0] + (ap.S == 2 ? ap.nsub[1] : 0);
-  return (gemv_lds(M, ap, wp) + 15) / 16 * 16 + (size_t)nsub * MT * kBlk * 4;
-}
-
+// The GEMV with sub-group scales (batches of at most 8 rows): a 4-bit group
+// 0 and an 8-bit group 1, and the chunks' products within 64 KB of LDS.
 bool gemv_g_fits(int64_t M, const ActPlan& ap, const WPlan& wp) {
-  return gemv_fits(M, ap, wp) && gemv_nibble_plan(ap) && ap.zp[0] == 0 &&
-         (ap.S == 1 || ap.zp[1] == 0) && wp.c_lo != 1 && wp.c_hi != 1 &&
-         gemv_g_lds(M, ap, wp) + (size_t)2048 * 8 <= 64 * 1024;
+  return gemv_nibble_plan(ap) && gemv_fits(M, ap, wp) && ap.zp[0] == 0 &&
+         (ap.S == 1 || ap.zp[1] == 0) && gemv_mm_lds(M, ap) <= 64 * 1024;
 }
 
 hipError_t launch_mp_gemv_grouped(const uint8_t* act_packed, const float* s_a, const ActPlan& ap,
                                   const WDev& wd, const WPlan& wp, int64_t M, int64_t N,
                                   uint16_t* Y, int64_t ldy, int32_t* acc, hipStream_t stream) {
-  GemmArgs a = make_args(act_packed, s_a, ap, wd, wp, M, N, Y, ldy, acc);
-  a.xs_bytes = (int)((gemv_lds(M, ap, wp) + 15) / 16 * 16);
-  const dim3 grid((unsigned)wp.nblk);
-  const size_t lds = gemv_g_lds(M, ap, wp);
-  if (M == 1) hipLaunchKernelGGL(k_gemv_g<1>, grid, dim3(256), lds, stream, a);
-  else if (M == 2) hipLaunchKernelGGL(k_gemv_g<2>, grid, dim3(256), lds, stream, a);
-  else if (M <= 4) hipLaunchKernelGGL(k_gemv_g<4>, grid, dim3(256), lds, stream, a);
-  else hipLaunchKernelGGL(k_gemv_g<8>, grid, dim3(256), lds, stream, a);
+  launch_gemv_form(make_args(act_packed, s_a, ap, wd, wp, M, N, Y, ldy, acc), stream);
   return hipGetLastError();
 }
 
