@@ -7,8 +7,8 @@
 //                   grid holds its rows in registers, folds the group
 //                   maxima at a grid barrier, quantizes and packs
 //   k_absmax_*      two-pass form, pass 1: per-workgroup partial maxima
-//   k_act_blk16,    two-pass form, pass 2: reduce the partials, quantize,
-//   k_act_rows      pack 16- or 8-row slices (or rows)
+//   k_act_blk,      two-pass form, pass 2: reduce the partials, quantize,
+//   k_act_rows      pack four-row slices (or rows)
 //   k_act_batch     small batches in one launch (max, quantize, pack)
 //   k_gemm          int8 MFMA GEMM on packed operands: an LDS ring filled by
 //                   direct global->LDS buffer loads, units widened to int8
@@ -550,16 +550,15 @@ __device__ __forceinline__ void qstore4(const float4& v, const QE4& q, uint8_t* 
 }
 
 // ------------------------------------------------------------ k_act_rows --
-// R activation rows per workgroup: reduce the partial maxima, quantize the
+// What k_act_blk does not take: rows too long for four in LDS (R = 1, J =
+// 4), and per element (J = 0) groups of sign codes and rows of fewer than
+// four values.  R activation rows per workgroup: reduce the partial maxima, quantize the
 // rows into LDS at their group-ordered positions, write their units.
 // Thread tid owns float4 positions base + tid + 256*j (j < J) of every row;
 // their LDS positions and group parameters are looked up once for all R
 // rows.  The first batch of rows is loaded before the partial maxima are
-// reduced, so the two latencies overlap.  Groups of 1-bit sign codes, and
-// rows of fewer than four values, take the per-element quantizer (J = 0,
-// pos and seg by channel; J > 0: by piece, as row4).  Element by element a
-// 301 x 4091 batch took 46 us with its maxima; on pieces it fits the single
-// pass, 13 us.
+// reduced, so the two latencies overlap (J = 0: pos and seg by channel; J > 0:
+// by piece, as row4).
 // Dynamic LDS: R*Kp bytes.
 template <int R, int J>
 __device__ __forceinline__ void act_rows_load(const float* __restrict__ A, int64_t m0, int rows,
@@ -869,79 +868,6 @@ __device__ __forceinline__ void write_block_pieces(const uint8_t* codes, int ldc
       }
     }
     *reinterpret_cast<uint4*>(dst + (int64_t)(q * 8 * C + w) * 16) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
-  }
-}
-
-// ----------------------------------------------------------- k_act_blk16 --
-// RB rows (8 or 16, aligned to a 16-row block) per workgroup, no sign-code
-// group: the rows go through in batches of four, the next
-// batch's loads in flight while the current one is quantized into LDS; the
-// partial maxima are reduced once; the rows' packed units are then written
-// as whole 16-byte pieces (each 16-channel group's units of these rows are
-// contiguous).  Rows past M are clamped to row M-1 (in bounds) and their
-// units land in padding rows, which no consumer reads.
-// Dynamic LDS: RB*Kp bytes.
-template <int J, int RB>
-__global__ __launch_bounds__(256) void k_act_blk16(const float* __restrict__ A, int64_t M,
-                                                   int64_t K, int64_t lda,
-                                                   const int32_t* __restrict__ pos,
-                                                   const uint8_t* __restrict__ seg, ActPlan ap,
-                                                   const float* __restrict__ partial, int nparts,
-                                                   float* __restrict__ s_a_out,
-                                                   uint8_t* __restrict__ packed) {
-  static_assert(RB == 8 || RB == 16, "row batch");
-  extern __shared__ __align__(16) uint8_t codes[];
-  __shared__ float red[8];
-  const int64_t m0 = (int64_t)blockIdx.x * RB;
-  const int rows = (int)min((int64_t)RB, M - m0);
-  const int tid = threadIdx.x;
-  const int K4 = (int)((K + 3) / 4);
-  int4 p[J];
-  uchar4 g[J];
-  float4 va[4][J], vb[4][J];
-  // batch b holds rows 4b..4b+3 (clamped into the valid rows)
-  auto load = [&](float4 (&v)[4][J], int b) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int k4 = min(tid + 256 * j, K4 - 1);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        v[r][j] = ld4(A + (m0 + min(4 * b + r, rows - 1)) * lda + row4(k4, (int)K));
-    }
-  };
-  load(va, 0);
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int k4 = min(tid + 256 * j, K4 - 1);
-    p[j] = reinterpret_cast<const int4*>(pos)[k4];
-    g[j] = reinterpret_cast<const uchar4*>(seg)[k4];
-  }
-  load(vb, 1);
-  uint32_t* codes32 = reinterpret_cast<uint32_t*>(codes);
-  for (int i = tid; i < RB * ap.Kp / 4; i += 256) codes32[i] = 0;
-  float s0, s1;
-  scales_from_partials(partial, nparts, ap, red, s0, s1, s_a_out);  // syncs
-  const QElem q0 = qelem(s0, ap.q[0], ap.zp[0]), q1 = qelem(s1, ap.q[1], ap.zp[1]);
-  act_rows_quant<4, J>(codes, ap.Kp, 4, K4, tid, p, g, va, q0, q1);
-  if constexpr (RB == 16) load(va, 2);
-  act_rows_quant<4, J>(codes + 4 * ap.Kp, ap.Kp, 4, K4, tid, p, g, vb, q0, q1);
-  if constexpr (RB == 16) {
-    load(vb, 3);
-    act_rows_quant<4, J>(codes + 8 * ap.Kp, ap.Kp, 4, K4, tid, p, g, va, q0, q1);
-    act_rows_quant<4, J>(codes + 12 * ap.Kp, ap.Kp, 4, K4, tid, p, g, vb, q0, q1);
-  }
-  __syncthreads();
-  const int r0 = (int)(m0 % kBlk);
-  for (int gi = 0; gi < ap.S; ++gi) {
-    const int c = gi ? ap.c[1] : ap.c[0];
-    const int ng = gi ? ap.ng[1] : ap.ng[0];
-    const int gbase = gi ? ap.kpad[0] : 0;
-    uint8_t* dst = packed + (gi ? ap.seg_off[1] : ap.seg_off[0]) +
-                   (m0 / kBlk) * (gi ? ap.mblk_bytes[1] : ap.mblk_bytes[0]);
-    if (c == 8) write_block_pieces<8, RB>(codes, ap.Kp, gbase, ng, r0, dst);
-    else if (c == 4) write_block_pieces<4, RB>(codes, ap.Kp, gbase, ng, r0, dst);
-    else if (c == 2) write_block_pieces<2, RB>(codes, ap.Kp, gbase, ng, r0, dst);
-    else write_block_pieces<1, RB>(codes, ap.Kp, gbase, ng, r0, dst);
   }
 }
 
@@ -1641,6 +1567,136 @@ void k_act_coop(const float* __restrict__ A, int64_t M, int K, int64_t lda, int 
     else { SONIQ_PIECES(16); }
 #undef SONIQ_PIECES
   }
+}
+
+// ------------------------------------------------------------- k_act_blk --
+// The two-pass form's second pass: four rows per workgroup (a quarter of a
+// 16-row block), quantized with the partial maxima's scales (as the single
+// pass: codes without the zero point, applied when the units are packed)
+// and written as whole unit pieces.  BF: rows of a producer's stored bf16
+// outputs instead of fp32.
+//
+// Bound by instruction issue (about 15 operations an element) and by how
+// many rows are in flight.  Four rows, against 8 and 16: 6.6, 7.0, 8.9 us at
+// 4096 x 768, 12.4, 13.7, 18.3 at 4096 x 3072, 7.2, 10.7 at 301 x 4091 (an
+// empty launch 1.8): fewer rows give more workgroups and more of them per
+// CU, and the four workgroups of a block run on one XCD (workgroup i goes
+// to XCD i mod 8), whose L2 joins their pieces of the same lines.  J: one
+// float4 a row and thread keeps the registers low (2304 values: 14.4 us
+// against 18.1 with two); rows past 4096 values take four (8192 x 8192: 64
+// against 74).  Dynamic LDS: 4*Kp bytes.
+template <bool BF, int J>
+__global__ __launch_bounds__(256) void k_act_blk(const void* __restrict__ src, int64_t M, int K,
+                                                 int64_t lda, const int4* __restrict__ pos4,
+                                                 ActPlan ap, const float* __restrict__ partial,
+                                                 int nparts, float* __restrict__ s_a_out,
+                                                 uint8_t* __restrict__ packed) {
+  constexpr int RB = 4;
+  extern __shared__ __align__(16) uint8_t codes[];
+  __shared__ float red[8];
+  const int64_t x = blockIdx.x & 7, jb = blockIdx.x >> 3;
+  const int64_t m0 = RB * (4 * ((jb >> 2) * 8 + x) + (jb & 3));
+  if (m0 >= M) return;
+  const int rows = (int)min((int64_t)RB, M - m0);
+  const int tid = threadIdx.x, K4 = (K + 3) / 4, kp0 = ap.kpad[0];
+  using raw = typename std::conditional<BF, uint2, float4>::type;
+  raw v[RB][J];
+  int4 p[J];
+  auto load = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int k4 = min(base + 256 * j, K4 - 1);
+      p[j] = pos4[k4];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const int64_t row = (m0 + min(r, rows - 1)) * lda;
+        if constexpr (BF)
+          v[r][j] = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(src) + row + 4 * k4);
+        else
+          v[r][j] = ld4(static_cast<const float*>(src) + row + row4(k4, K));
+      }
+    }
+  };
+  load(tid);  // ahead of the partial maxima, so the two latencies overlap
+  {
+    // codes start as each group's zero point, which packs to a stored zero
+    uint32_t* codes32 = reinterpret_cast<uint32_t*>(codes);
+    const int kw = ap.Kp / 4, kw0 = kp0 / 4;
+    const uint32_t z0 = 0x01010101u * (uint32_t)ap.zp[0], z1 = 0x01010101u * (uint32_t)ap.zp[1];
+    for (int r = 0; r < RB; ++r)
+      for (int i = tid; i < kw; i += 256) codes32[r * kw + i] = i < kw0 ? z0 : z1;
+  }
+  float s0, s1;
+  scales_from_partials(partial, nparts, ap, red, s0, s1, s_a_out);  // syncs
+  const float hi0 = (float)ap.q[0].hi, hi1 = (float)ap.q[1].hi;
+  const float lo0 = (float)ap.q[0].lo, lo1 = (float)ap.q[1].lo;
+  const bool fast = fast_ok(s0) && (ap.S == 1 || fast_ok(s1));
+  const float rs0 = fast ? __builtin_amdgcn_rcpf(s0) : 0.0f;
+  const float rs1 = fast && ap.S == 2 ? __builtin_amdgcn_rcpf(s1) : 0.0f;
+  auto each = [&](auto&& f) __attribute__((always_inline)) {
+    for (int base = tid; base < K4; base += 256 * J) {
+      if (base != tid) load(base);
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (base + 256 * j >= K4) break;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          float4 e;
+          if constexpr (BF)
+            e = make_float4(__uint_as_float(v[r][j].x << 16), __uint_as_float(v[r][j].x & 0xFFFF0000u),
+                            __uint_as_float(v[r][j].y << 16), __uint_as_float(v[r][j].y & 0xFFFF0000u));
+          else
+            e = v[r][j];
+          if (r < rows) f(e, p[j], codes + r * ap.Kp);
+        }
+      }
+    }
+  };
+  if (!fast)
+    each([&](const float4& e, int4 q, uint8_t* row) __attribute__((always_inline)) {
+      qcodes4_exact(e, q, kp0, s0, s1, lo0, lo1, hi0, hi1, row);
+    });
+  else if (ap.q[0].lo < 0)
+    each([&](const float4& e, int4 q, uint8_t* row) __attribute__((always_inline)) {
+      qcodes4<true>(e, q, kp0, rs0, rs1, s0, s1, hi0, hi1, row);
+    });
+  else
+    each([&](const float4& e, int4 q, uint8_t* row) __attribute__((always_inline)) {
+      qcodes4<false>(e, q, kp0, rs0, rs1, s0, s1, hi0, hi1, row);
+    });
+  __syncthreads();
+  const int r0 = (int)(m0 % kBlk);
+  for (int gi = 0; gi < ap.S; ++gi) {
+    const int c = gi ? ap.c[1] : ap.c[0];
+    const int ng = gi ? ap.ng[1] : ap.ng[0];
+    const int gbase = gi ? ap.kpad[0] : 0;
+    uint8_t* dst = packed + (gi ? ap.seg_off[1] : ap.seg_off[0]) +
+                   (m0 / kBlk) * (gi ? ap.mblk_bytes[1] : ap.mblk_bytes[0]);
+    const uint32_t zx = 0x01010101u * (uint32_t)(gi ? ap.zp[1] : ap.zp[0]);
+    if (c == 8) write_block_pieces<8, RB>(codes, ap.Kp, gbase, ng, r0, dst, zx);
+    else if (c == 4) write_block_pieces<4, RB>(codes, ap.Kp, gbase, ng, r0, dst, zx);
+    else write_block_pieces<2, RB>(codes, ap.Kp, gbase, ng, r0, dst, zx);
+  }
+}
+
+// Whether k_act_blk takes rows of this plan (no sign group), and its launch.
+bool act_blk_takes(const ActPlan& ap) {
+  return !ap.q[0].sign1 && !(ap.S == 2 && ap.q[1].sign1) && 4 * (int64_t)ap.Kp <= 64 * 1024;
+}
+template <bool BF>
+hipError_t launch_act_blk(const void* src, int64_t M, int64_t K, int64_t lda, const ActPlan& ap,
+                          const int32_t* pos4, const float* partial, int nparts, float* s_a,
+                          uint8_t* packed, hipStream_t stream) {
+  const dim3 grid((unsigned)((M + 127) / 128 * 32));
+  const size_t lds = 4 * (size_t)ap.Kp;
+  const int4* p4 = reinterpret_cast<const int4*>(pos4);
+  if (K <= 4096)
+    hipLaunchKernelGGL((k_act_blk<BF, 1>), grid, dim3(256), lds, stream, src, M, (int)K, lda, p4, ap,
+                       partial, nparts, s_a, packed);
+  else
+    hipLaunchKernelGGL((k_act_blk<BF, 4>), grid, dim3(256), lds, stream, src, M, (int)K, lda, p4, ap,
+                       partial, nparts, s_a, packed);
+  return hipGetLastError();
 }
 
 // ----------------------------------------------------------- k_act_batch --
@@ -4280,6 +4336,7 @@ __global__ __launch_bounds__(256) void k_gemv_mm(GemmArgs a) {
 // SONIQ_ACT_COOP=0 turns the path off for measurement; results do not
 // depend on it.
 constexpr int64_t kCoopMinElems = (int64_t)1 << 20;
+constexpr int64_t kCoopFromElems = (int64_t)8 << 20;  // without sub-group scales
 
 template <int T, int TL, bool GRP>
 int coop_capacity(size_t lds) {
@@ -5407,29 +5464,38 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
     if (ximg_done) *ximg_done = ximg != nullptr;
     return launch_act_batch<false>(A, M, K, lda, ap, pos4_dev, s_a, packed, stream, ximg, (size_t)ap.Kp);
   }
-  if (vec && !sign && M * K >= kCoopMinElems) {
+  // The single pass reads the rows once but waits for its grid to meet
+  // (about 5 us); two passes read them twice, the second time from the L2s
+  // (32 MB).  Single against two passes, us: 10.9, 10.3 at 4096 x 768,
+  // 13.3, 9.8 at 301 x 4091, 8.9, 6.9 at 1024 x 1024; 21.4, 21.6 at 4096 x
+  // 3072, 24.6, 25.0 at 6272 x 2304.  SONIQ_COOP_SPINS (the single pass's
+  // spin limit) asks for it from kCoopMinElems on.
+  const int64_t coop_min = getenv("SONIQ_COOP_SPINS") ? kCoopMinElems : kCoopFromElems;
+  if (vec && !sign && M * K >= coop_min) {
     hipError_t e = hipSuccess;
     if (launch_act_coop(A, M, K, lda, ap, pos4_dev, counter, s_a, packed, stream, e))
       return e;
   }
   int nparts;
   if (vec && M <= 16 * (int64_t)kAbsmaxBlocks) {
-    // 8 (or 16) rows per workgroup keep the grid within the partial buffer
+    // rows per workgroup: enough workgroups for the CUs, within the partial
+    // buffer (2 rows 2.7 us against 3.5 with 8 at 301 x 4091; 4 rows 3.8
+    // against 5.2 with 2 at 4096 x 768)
     const int K4 = (int)((K + 3) / 4);
-    const int RB = M <= 8 * (int64_t)kAbsmaxBlocks ? 8 : 16;
-    const int64_t blocks = (M + RB - 1) / RB;
-    nparts = (int)blocks;
-    const int J = K4 <= 256 ? 1 : K4 <= 512 ? 2 : K4 <= 768 ? 3 : 4;
+    const int RB = M <= 512 ? 2 : M <= 4 * (int64_t)kAbsmaxBlocks ? 4 : M <= 8 * (int64_t)kAbsmaxBlocks ? 8 : 16;
+    nparts = (int)((M + RB - 1) / RB);
     const uchar4* s4 = reinterpret_cast<const uchar4*>(seg4_dev);
-#define SONIQ_ABSMAX(J_, RB_)                                                                   \
-  hipLaunchKernelGGL((k_absmax_blk<J_, RB_>), dim3((unsigned)blocks), dim3(256), 0, stream, A, M, \
+#define SONIQ_ABSMAX(J_, RB_)                                                                      \
+  hipLaunchKernelGGL((k_absmax_blk<J_, RB_>), dim3((unsigned)nparts), dim3(256), 0, stream, A, M,  \
                      (int)K, lda, s4, partial)
-    if (RB == 8) {
-      if (J == 1) SONIQ_ABSMAX(1, 8); else if (J == 2) SONIQ_ABSMAX(2, 8);
-      else if (J == 3) SONIQ_ABSMAX(3, 8); else SONIQ_ABSMAX(4, 8);
+    if (RB == 2) {
+      SONIQ_ABSMAX(4, 2);
+    } else if (RB == 4) {
+      if (K4 <= 256) SONIQ_ABSMAX(1, 4); else if (K4 <= 512) SONIQ_ABSMAX(2, 4); else SONIQ_ABSMAX(4, 4);
+    } else if (RB == 8) {
+      if (K4 <= 256) SONIQ_ABSMAX(1, 8); else if (K4 <= 512) SONIQ_ABSMAX(2, 8); else SONIQ_ABSMAX(4, 8);
     } else {
-      if (J == 1) SONIQ_ABSMAX(1, 16); else if (J == 2) SONIQ_ABSMAX(2, 16);
-      else SONIQ_ABSMAX(2, 16);
+      if (K4 <= 256) SONIQ_ABSMAX(1, 16); else SONIQ_ABSMAX(2, 16);
     }
 #undef SONIQ_ABSMAX
   } else {
@@ -5440,10 +5506,8 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // groups of 1-bit sign codes, and rows of fewer than four values, take the
-  // per-element quantizer (J = 0); otherwise J float4 positions per thread
-  const int K4 = (int)((K + 3) / 4);
-  const int J = (sign || !vec) ? 0 : K4 <= 256 ? 1 : K4 <= 512 ? 2 : K4 <= 768 ? 3 : 4;
+  if (vec && act_blk_takes(ap))
+    return launch_act_blk<false>(A, M, K, lda, ap, pos4_dev, partial, nparts, s_a, packed, stream);
 #define SONIQ_ACT_ROWS(R_, J_)                                                                  \
   hipLaunchKernelGGL((k_act_rows<R_, J_>),                                                      \
                      dim3((unsigned)(R_ == 4 ? ((M + 127) / 128) * 32 : (M + R_ - 1) / R_)),    \
@@ -5451,37 +5515,12 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
                      (size_t)R_ * ap.Kp, stream, A, M, K, lda, J_ ? pos4_dev : pos_dev,         \
                      J_ ? seg4_dev : seg_dev, ap, partial,                                      \
                      nparts, s_a, packed, ximg)
-  // whole 8- or 16-row block slices per workgroup for larger batches
-  // 16 rows per workgroup once that still gives ~1.5 workgroups per CU,
-  // else 8 (more workgroups in flight)
-  const int rbk = M >= 6144 ? 16 : 8;
-  if (J > 0 && J <= 3 && M >= 1024 && rbk * (int64_t)ap.Kp <= 64 * 1024) {
-    const size_t lds = (size_t)rbk * ap.Kp;
-#define SONIQ_BLK(J_, RB_)                                                                       \
-  hipLaunchKernelGGL((k_act_blk16<J_, RB_>), dim3((unsigned)((M + RB_ - 1) / RB_)), dim3(256), lds, \
-                     stream, A, M, K, lda, pos4_dev, seg4_dev, ap, partial, nparts, s_a, packed)
-    if (rbk == 8) {
-      if (J == 1) SONIQ_BLK(1, 8); else if (J == 2) SONIQ_BLK(2, 8); else SONIQ_BLK(3, 8);
-    } else {
-      if (J == 1) SONIQ_BLK(1, 16); else if (J == 2) SONIQ_BLK(2, 16); else SONIQ_BLK(3, 16);
-    }
-#undef SONIQ_BLK
-  } else if (4 * (int64_t)ap.Kp <= 64 * 1024) {
-    switch (J) {
-      case 0: SONIQ_ACT_ROWS(4, 0); break;
-      case 1: SONIQ_ACT_ROWS(4, 1); break;
-      case 2: SONIQ_ACT_ROWS(4, 2); break;
-      case 3: SONIQ_ACT_ROWS(4, 3); break;
-      default: SONIQ_ACT_ROWS(4, 4); break;
-    }
-  } else {
-    switch (J) {
-      case 0: SONIQ_ACT_ROWS(1, 0); break;
-      default: SONIQ_ACT_ROWS(1, 4); break;
-    }
-  }
+  if (vec && !sign) SONIQ_ACT_ROWS(1, 4);
+  else if (4 * (int64_t)ap.Kp <= 64 * 1024) SONIQ_ACT_ROWS(4, 0);
+  else SONIQ_ACT_ROWS(1, 0);
 #undef SONIQ_ACT_ROWS
-  // a single row never takes the block form (M >= 1024)
+  // k_act_blk leaves no image: a single row of up to 16384 values was taken
+  // by the small-batch launch, a longer one exceeds four rows in LDS
   if (ximg_done) *ximg_done = ximg != nullptr;
   return hipGetLastError();
 }
@@ -5834,32 +5873,27 @@ hipError_t launch_act_bf16(const uint16_t* Y, int64_t M, int64_t K, int64_t ldy,
   // groups of 1-bit sign codes take the per-element quantizer, as in
   // launch_act_quant
   const bool sign = ap.q[0].sign1 || (ap.S == 2 && ap.q[1].sign1);
+  // the tiles' maxima are there and the rows fit: four rows per workgroup
+  if (aligned && nslot > 0 && act_blk_takes(ap))
+    return launch_act_blk<true>(Y, M, K, ldy, ap, pos_dev, slots, nslot, s_a, packed, stream);
   const int64_t K4 = K / 4;
   const int J = (sign || !aligned) ? 0 : K4 <= 256 ? 1 : K4 <= 512 ? 2 : K4 <= 768 ? 3 : 4;
-  // four rows per workgroup, or one row (small batches, whose workgroups
-  // each reduce the whole batch's maxima; or rows too long for four)
-  const bool four = M > 8 && 4 * (int64_t)ap.Kp <= 64 * 1024;
+  // otherwise one row (small batches, whose workgroups each reduce the whole
+  // batch's maxima; rows too long for four) or, per element, four
   uint8_t* xi = M == 1 ? ximg : nullptr;
 #define SONIQ_BF16(R_, J_)                                                                          \
   hipLaunchKernelGGL((k_act_bf16<R_, J_>), dim3((unsigned)((M + R_ - 1) / R_)), dim3(256),          \
                      (size_t)R_ * ap.Kp, stream, Y, M, K, ldy, pos_dev, seg_dev, ap, slots, nslot, s_a, \
                      packed, xi)
-  if (four) {
-    switch (J) {
-      case 0: SONIQ_BF16(4, 0); break;
-      case 1: SONIQ_BF16(4, 1); break;
-      case 2: SONIQ_BF16(4, 2); break;
-      case 3: SONIQ_BF16(4, 3); break;
-      default: SONIQ_BF16(4, 4); break;
-    }
-  } else {
-    switch (J) {
-      case 0: SONIQ_BF16(1, 0); break;
-      case 1: SONIQ_BF16(1, 1); break;
-      case 2: SONIQ_BF16(1, 2); break;
-      case 3: SONIQ_BF16(1, 3); break;
-      default: SONIQ_BF16(1, 4); break;
-    }
+  switch (J) {
+    case 0:
+      if (M > 8 && 4 * (int64_t)ap.Kp <= 64 * 1024) SONIQ_BF16(4, 0);
+      else SONIQ_BF16(1, 0);
+      break;
+    case 1: SONIQ_BF16(1, 1); break;
+    case 2: SONIQ_BF16(1, 2); break;
+    case 3: SONIQ_BF16(1, 3); break;
+    default: SONIQ_BF16(1, 4); break;
   }
 #undef SONIQ_BF16
   return hipGetLastError();

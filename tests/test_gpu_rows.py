@@ -65,3 +65,22 @@ def test_rows(c):
     np.testing.assert_array_equal(acc.cpu().numpy(), racc)
     np.testing.assert_array_equal(Y.view(torch.int16).cpu().numpy().view(np.uint16),
                                   oracle.epilogue_replay(racc, rs, s_w))
+
+
+@pytest.mark.parametrize("M", [63, 129, 513, 4097, 8193])
+def test_two_pass_rows_per_workgroup(M):
+    """Each row count of the first pass's workgroups (2, 4, 8, 16), with
+    batches that end inside a workgroup and inside a 16-row block."""
+    case = workloads.generic(M, 32, 1100, a_lo=3, a_hi=8, a_frac_lo=0.6, w_lo=2, w_hi=4, w_frac_lo=0.5,
+                             a_signed=False, a_abs=True, seed=M, name="two_pass")
+    print(f"[gpu] two pass M={M}", flush=True)
+    case["A"][M - 1, 7] = 9.0  # the last row holds both maxima
+    case["A"][M - 1, 8] = 9.5
+    w = sq.soniq_pack_weights(torch.from_numpy(case["W"]).cuda(), case["w_bits"], case["a_bits"], False)
+    act = sq.soniq_act_create(w, M)
+    sq.soniq_quantize_act(act, torch.from_numpy(case["A"]).cuda())
+    torch.cuda.synchronize()
+    q_a, s_a = sq.soniq_act_unpack_debug(act)
+    r = oracle.run(case["A"][:], case["W"][:1], case["a_bits"], case["w_bits"][:1], False)
+    np.testing.assert_array_equal(s_a, r["s_a"])
+    np.testing.assert_array_equal(q_a, r["q_a"])
