@@ -1974,7 +1974,9 @@ struct GemmArgs {
   uint16_t* Y;
   int64_t ldy;
   int32_t* acc;
-  int xcd_tiles;  // GEMM: give each XCD a contiguous range of tiles
+  // GEMM: give each XCD a contiguous range of tiles, row block by row block
+  // (1) or column block by column block (2)
+  int xcd_tiles;
   // the dense weight copy (k_gemv_dense) and its two widths
   const uint8_t* dense;
   int db_lo, db_hi;
@@ -2413,14 +2415,14 @@ __device__ __forceinline__ void gemm_group_fast(uint8_t* lds, const uint8_t* aba
 // short K.  A granule of a BM x 128 tile holds BM*8*CA activation bytes and
 // 1024*CB weight bytes; each side's stage region is a whole number of
 // 4 KB load rounds (256 lanes x 16 bytes).
-constexpr int wide_loads(int chunks) { return (chunks + 255) / 256; }
-constexpr int wide_bytes(int WFM, int CA, int CB, int g) {
-  return 4096 * (wide_loads(16 * WFM * g * CA) + wide_loads(64 * g * CB));
+constexpr int wide_loads(int chunks, int KS = 1) { return (chunks + 256 * KS - 1) / (256 * KS); }
+constexpr int wide_bytes(int WFM, int CA, int CB, int g, int KS = 1) {
+  return 4096 * KS * (wide_loads(16 * WFM * g * CA, KS) + wide_loads(64 * g * CB, KS));
 }
-constexpr int wide_gps(int WFM, int CA, int CB, int slot) {
+constexpr int wide_gps(int WFM, int CA, int CB, int slot, int KS = 1) {
   int best = 2;
   for (int g = 4; g <= 8; g += 2)
-    if (wide_bytes(WFM, CA, CB, g) <= slot) best = g;
+    if (wide_bytes(WFM, CA, CB, g, KS) <= slot) best = g;
   return best;
 }
 
@@ -2464,7 +2466,7 @@ __device__ __forceinline__ void wide_mma(v4i (&acc)[WFM][4], raw_t<CB> (&rb)[4],
 // alternate at compile time and no branch joins values of reads still in
 // flight (a join would let the register allocator copy such a register
 // before its wait).
-template <int CA, int CB, int WFM, int GPS, int R, int KK>
+template <int CA, int CB, int WFM, int GPS, int R, int KK, int KS>
 __device__ __forceinline__ void wide_granules(v4i (&acc)[WFM][4], raw_t<CB> (&b0)[4],
                                               raw_t<CA> (&a0)[WFM], raw_t<CB> (&b1)[4],
                                               raw_t<CA> (&a1)[WFM], uint32_t a_addr,
@@ -2472,8 +2474,8 @@ __device__ __forceinline__ void wide_granules(v4i (&acc)[WFM][4], raw_t<CB> (&b0
   if constexpr (KK < R) {
     constexpr bool odd = (KK & 1) != 0;
     if constexpr (KK + 1 < R) {
-      if constexpr (odd) wide_read<CA, CB, WFM, GPS, KK + 1>(b0, a0, a_addr, b_addr);
-      else wide_read<CA, CB, WFM, GPS, KK + 1>(b1, a1, a_addr, b_addr);
+      if constexpr (odd) wide_read<CA, CB, WFM, GPS, KS * (KK + 1)>(b0, a0, a_addr, b_addr);
+      else wide_read<CA, CB, WFM, GPS, KS * (KK + 1)>(b1, a1, a_addr, b_addr);
       lds_wait_n<4 + WFM>();
     } else {
       lds_wait();
@@ -2484,26 +2486,26 @@ __device__ __forceinline__ void wide_granules(v4i (&acc)[WFM][4], raw_t<CB> (&b0
     // keep these products ahead of the next granule's wait
     __builtin_amdgcn_sched_barrier(0);
 #endif
-    wide_granules<CA, CB, WFM, GPS, R, KK + 1>(acc, b0, a0, b1, a1, a_addr, b_addr);
+    wide_granules<CA, CB, WFM, GPS, R, KK + 1, KS>(acc, b0, a0, b1, a1, a_addr, b_addr);
   }
 }
 
-template <int CA, int CB, int WFM, int GPS, int R>
+template <int CA, int CB, int WFM, int GPS, int R, int KS>
 __device__ __forceinline__ void wide_stage(v4i (&acc)[WFM][4], uint32_t a_addr, uint32_t b_addr) {
   raw_t<CB> b0[4], b1[4];
   raw_t<CA> a0[WFM], a1[WFM];
   wide_read<CA, CB, WFM, GPS, 0>(b0, a0, a_addr, b_addr);
-  wide_granules<CA, CB, WFM, GPS, R, 0>(acc, b0, a0, b1, a1, a_addr, b_addr);
+  wide_granules<CA, CB, WFM, GPS, R, 0, KS>(acc, b0, a0, b1, a1, a_addr, b_addr);
 }
 
 // A stage with rem valid granules (rem >= GPS: a full one); each count is
 // its own straight-line body.
-template <int CA, int CB, int WFM, int GPS, int R = GPS>
+template <int CA, int CB, int WFM, int GPS, int R, int KS>
 __device__ __forceinline__ void wide_stage_rem(v4i (&acc)[WFM][4], uint32_t a_addr, uint32_t b_addr,
                                                int rem) {
   if constexpr (R >= 1) {
-    if (rem >= R) wide_stage<CA, CB, WFM, GPS, R>(acc, a_addr, b_addr);
-    else wide_stage_rem<CA, CB, WFM, GPS, R - 1>(acc, a_addr, b_addr, rem);
+    if (rem >= R) wide_stage<CA, CB, WFM, GPS, R, KS>(acc, a_addr, b_addr);
+    else wide_stage_rem<CA, CB, WFM, GPS, R - 1, KS>(acc, a_addr, b_addr, rem);
   }
 }
 
@@ -2514,20 +2516,21 @@ __device__ __forceinline__ void wide_stage_rem(v4i (&acc)[WFM][4], uint32_t a_ad
 // B stage (block j, granule kk at (j*GPS + kk)*128*CB).  Loads go through
 // buffer resources; chunks past the group's data, and lanes past a stage's
 // chunks, read as zero (their products vanish).
-template <int CA, int CB, int WFM, int NST, int SLOT>
+template <int CA, int CB, int WFM, int NST, int SLOT, int KS = 1>
 __device__ __forceinline__ void gemm_group_wide(uint8_t* lds, const uint8_t* abase, int64_t mstride,
                                                 int ng, const uint8_t* wtile, int wbytes, int ngt,
                                                 int qbase, v4i (&acc)[WFM][4], int tid, int lane,
-                                                int wid, int wm, int wn) {
+                                                int wid, int wm, int wn, int ks = 0) {
 #if defined(__HIP_DEVICE_COMPILE__)  // GPU builtins; the host pass never runs it
   constexpr int BM = 32 * WFM;
-  constexpr int GPS = wide_gps(WFM, CA, CB, SLOT);
+  constexpr int GPS = wide_gps(WFM, CA, CB, SLOT, KS);
   constexpr int CHA = 16 * WFM * GPS * CA;  // A chunks per stage
   constexpr int CHB = 64 * GPS * CB;        // B chunks per stage
-  constexpr int LA = wide_loads(CHA), LB = wide_loads(CHB);
+  constexpr int LA = wide_loads(CHA, KS), LB = wide_loads(CHB, KS);
+  constexpr int T = 256 * KS;
   constexpr int L = LA + LB;
-  constexpr int ABYTES = 4096 * LA;
-  static_assert(4096 * (LA + LB) <= SLOT, "a wide stage fits its slot");
+  constexpr int ABYTES = 4096 * KS * LA;
+  static_assert(4096 * KS * (LA + LB) <= SLOT, "a wide stage fits its slot");
   static_assert((GPS - 1 + 3 * GPS) * 128 * CB + ABYTES < 65536 && (WFM * GPS) * 128 * CA < 65536,
                 "ds offsets");
   const int nst = (ng + GPS - 1) / GPS;
@@ -2543,13 +2546,13 @@ __device__ __forceinline__ void gemm_group_wide(uint8_t* lds, const uint8_t* aba
   uint32_t aoff[LA], boff[LB];
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
-    const int ci = i * 256 + tid;
+    const int ci = i * T + tid;
     const int mb = ci / (GPS * 8 * CA), w = ci - mb * (GPS * 8 * CA);
     aoff[i] = ci < CHA ? (uint32_t)(mb * mstride + w * 16) : kOOB;
   }
 #pragma unroll
   for (int i = 0; i < LB; ++i) {
-    const int ci = i * 256 + tid;
+    const int ci = i * T + tid;
     const int j = ci / (GPS * 8 * CB), w = ci - j * (GPS * 8 * CB);
     boff[i] = ci < CHB ? (uint32_t)(j * ngt * 128 * CB + qbase * 128 * CB + w * 16) : kOOB;
   }
@@ -2562,22 +2565,22 @@ __device__ __forceinline__ void gemm_group_wide(uint8_t* lds, const uint8_t* aba
     const uint32_t ldsb = lds_off(lds) + (uint32_t)(slot * SLOT);
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
-      const int q = ((i * 256 + tid) % (GPS * 8 * CA)) / (8 * CA);  // granule in the stage
+      const int q = ((i * T + tid) % (GPS * 8 * CA)) / (8 * CA);  // granule in the stage
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          ar, (__attribute__((address_space(3))) void*)(uintptr_t)(ldsb + (i * 256 + wid * 64) * 16), 16,
+          ar, (__attribute__((address_space(3))) void*)(uintptr_t)(ldsb + (i * T + wid * 64) * 16), 16,
           rem >= GPS || q < rem ? aoff[i] : kOOB, st * GPS * 128 * CA, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
-      const int q = ((i * 256 + tid) % (GPS * 8 * CB)) / (8 * CB);
+      const int q = ((i * T + tid) % (GPS * 8 * CB)) / (8 * CB);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          br, (__attribute__((address_space(3))) void*)(uintptr_t)(ldsb + ABYTES + (i * 256 + wid * 64) * 16),
+          br, (__attribute__((address_space(3))) void*)(uintptr_t)(ldsb + ABYTES + (i * T + wid * 64) * 16),
           16, rem >= GPS || q < rem ? boff[i] : kOOB, st * GPS * 128 * CB, 0, 0);
     }
   };
 
-  const uint32_t b_lds = lds_off(lds) + (uint32_t)(ABYTES + wn * 4 * GPS * 128 * CB + lane * 2 * CB);
-  const uint32_t a_lds = lds_off(lds) + (uint32_t)(wm * WFM * GPS * 128 * CA + lane * 2 * CA);
+  const uint32_t b_lds = lds_off(lds) + (uint32_t)(ABYTES + wn * 4 * GPS * 128 * CB + ks * 128 * CB + lane * 2 * CB);
+  const uint32_t a_lds = lds_off(lds) + (uint32_t)(wm * WFM * GPS * 128 * CA + ks * 128 * CA + lane * 2 * CA);
 
   int issued = 0;
   for (; issued < NST - 1 && issued < nst; ++issued) issue(issued, issued);
@@ -2600,11 +2603,12 @@ __device__ __forceinline__ void gemm_group_wide(uint8_t* lds, const uint8_t* aba
   const int nfull = ng / GPS;
   for (int st = 0; st < nfull; ++st) {
     const uint32_t soff = ready(st);
-    wide_stage<CA, CB, WFM, GPS, GPS>(acc, a_lds + soff, b_lds + soff);
+    wide_stage<CA, CB, WFM, GPS, GPS / KS, KS>(acc, a_lds + soff, b_lds + soff);
   }
   if (nfull < nst) {
     const uint32_t soff = ready(nfull);
-    wide_stage_rem<CA, CB, WFM, GPS, GPS - 1>(acc, a_lds + soff, b_lds + soff, ng - nfull * GPS);
+    wide_stage_rem<CA, CB, WFM, GPS, KS == 1 ? GPS - 1 : GPS / KS, KS>(
+        acc, a_lds + soff, b_lds + soff, (ng - nfull * GPS - ks + KS - 1) / KS);
   }
   // Everyone is done reading the ring before the next group refills it.
   bar_nofence();
@@ -2759,20 +2763,21 @@ __device__ __forceinline__ void gemm_group_any(uint8_t* lds, const uint8_t* abas
 // (tid/16)%4, row tid%16) loads its unit of every granule of a stage into
 // registers while the previous stage is multiplied, then writes them into
 // the stage's ring slot in the fragment-major layout the products read.
-template <int CA, int CB, int NST, int SLOT>
+template <int CA, int CB, int NST, int SLOT, int KS>
 __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img, int rowbytes,
                                                 int cpad, int H, int W, int64_t M, int64_t m0,
                                                 int ng, const uint8_t* wtile, int wbytes, int ngt,
                                                 int qbase, v4i (&acc)[2][4], int tid, int lane,
-                                                int wid, int wm, int wn) {
+                                                int wid, int wm, int wn, int ks) {
 #if defined(__HIP_DEVICE_COMPILE__)
   constexpr int WFM = 2;
-  constexpr int GPS = wide_gps(WFM, CA, CB, SLOT);
+  constexpr int GPS = wide_gps(WFM, CA, CB, SLOT, KS);
+  constexpr int T = 256 * KS;
   constexpr int CHB = 64 * GPS * CB;
-  constexpr int LA = wide_loads(16 * WFM * GPS * CA), LB = wide_loads(CHB);
-  constexpr int ABYTES = 4096 * LA;
+  constexpr int LA = wide_loads(16 * WFM * GPS * CA, KS), LB = wide_loads(CHB, KS);
+  constexpr int ABYTES = 4096 * KS * LA;
   static_assert(NST == 2, "two ring slots");
-  static_assert(4096 * (LA + LB) <= SLOT, "a stage fits its slot");
+  static_assert(4096 * KS * (LA + LB) <= SLOT, "a stage fits its slot");
   const int nst = (ng + GPS - 1) / GPS;
 
   const __amdgpu_buffer_rsrc_t br =
@@ -2780,7 +2785,7 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
   uint32_t boff[LB];
 #pragma unroll
   for (int i = 0; i < LB; ++i) {
-    const int ci = i * 256 + tid;
+    const int ci = i * T + tid;
     const int j = ci / (GPS * 8 * CB), w = ci - j * (GPS * 8 * CB);
     boff[i] = ci < CHB ? (uint32_t)(j * ngt * 128 * CB + qbase * 128 * CB + w * 16) : kOOB;
   }
@@ -2789,51 +2794,62 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
     const uint32_t ldsb = lds_off(lds) + (uint32_t)(slot * SLOT) + ABYTES;
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
-      const int q = ((i * 256 + tid) % (GPS * 8 * CB)) / (8 * CB);
+      const int q = ((i * T + tid) % (GPS * 8 * CB)) / (8 * CB);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          br, (__attribute__((address_space(3))) void*)(uintptr_t)(ldsb + (i * 256 + wid * 64) * 16),
+          br, (__attribute__((address_space(3))) void*)(uintptr_t)(ldsb + (i * T + wid * 64) * 16),
           16, rem >= GPS || q < rem ? boff[i] : kOOB, st * GPS * 128 * CB, 0, 0);
     }
   };
 
   // this thread's output pixel (rows past M repeat the last one; their
   // sums are never stored) and its haloed center
-  const int mb = (tid >> 4) & 3, r = tid & 15, kg = wid;
+  const int mb = (tid >> 4) & 3, r = tid & 15, kg = wid & 3;
   const int64_t P = min(m0 + 16 * mb + r, M - 1);
   const int HW = H * W;
   const int b = (int)(P / HW), rem0 = (int)(P - (int64_t)b * HW);
   const int y = rem0 / W, x = rem0 - y * W;
   const int Wp = W + 2;
   const int hp0 = (b * (H + 2) + y + 1) * Wp + x + 1;
-  const int kend = 9 * cpad;
-  raw_t<CA> ua[GPS];
-  auto load_a = [&](int st) __attribute__((always_inline)) {
+  // This wave's units: 16-channel group kg of granules ks, ks + KS, ...  The
+  // tap and unit of a wave are scalars stepped from granule to granule (a
+  // division per unit cost as much as the widening of its operands).
+  constexpr int QA = GPS / KS;
+  const int cu = cpad >> 4, kend = 9 * cu;  // units of a tap, of the group
+  int ku = __builtin_amdgcn_readfirstlane(4 * ks + kg);  // unit index
+  int tap = __builtin_amdgcn_readfirstlane(ku / cu);
+  int c16 = ku - tap * cu;
+  const uint8_t* img0 = img + (int64_t)hp0 * rowbytes;
+  raw_t<CA> ua[QA];
+  auto load_a = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < GPS; ++q) {
-      const int gq = st * GPS + q;
-      const int kq = gq * 64 + 16 * kg;
-      raw_t<CA> v{};
-      if (gq < ng && kq < kend) {
-        const int t = kq / cpad, c16 = (kq - t * cpad) >> 4;
-        const int tr = t / 3;
-        const int hp = hp0 + (tr - 1) * Wp + (t - 3 * tr - 1);
-        v = *reinterpret_cast<const raw_t<CA>*>(img + (int64_t)hp * rowbytes + c16 * 2 * CA);
+    for (int q = 0; q < QA; ++q) {
+      const int tr = tap >= 6 ? 2 : tap >= 3 ? 1 : 0;
+      const int dp = (tr - 1) * Wp + (tap - 3 * tr - 1);
+      // units past the group's end read the center pixel and count as zero
+      const bool in = ku < kend;
+      const raw_t<CA> v =
+          *reinterpret_cast<const raw_t<CA>*>(img0 + (in ? dp * rowbytes + c16 * 2 * CA : 0));
+      ua[q] = in ? v : raw_t<CA>{};
+      ku += 4 * KS;
+      c16 += 4 * KS;
+      while (c16 >= cu) {
+        c16 -= cu;
+        ++tap;
       }
-      ua[q] = v;
     }
   };
-  const int aw = (mb * GPS) * 128 * CA + (kg * 16 + r) * 2 * CA;
+  const int aw = (mb * GPS + ks) * 128 * CA + (kg * 16 + r) * 2 * CA;
   auto write_a = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < GPS; ++q)
-      *reinterpret_cast<raw_t<CA>*>(lds + slot * SLOT + aw + q * 128 * CA) = ua[q];
+    for (int q = 0; q < QA; ++q)
+      *reinterpret_cast<raw_t<CA>*>(lds + slot * SLOT + aw + q * KS * 128 * CA) = ua[q];
   };
 
-  const uint32_t b_lds = lds_off(lds) + (uint32_t)(ABYTES + wn * 4 * GPS * 128 * CB + lane * 2 * CB);
-  const uint32_t a_lds = lds_off(lds) + (uint32_t)(wm * WFM * GPS * 128 * CA + lane * 2 * CA);
+  const uint32_t b_lds = lds_off(lds) + (uint32_t)(ABYTES + wn * 4 * GPS * 128 * CB + ks * 128 * CB + lane * 2 * CB);
+  const uint32_t a_lds = lds_off(lds) + (uint32_t)(wm * WFM * GPS * 128 * CA + ks * 128 * CA + lane * 2 * CA);
 
   issue_b(0, 0);
-  load_a(0);
+  load_a();
   write_a(0);
   auto ready = [&](int st) __attribute__((always_inline)) {
     // this thread's unit writes and every wave's weight loads have landed
@@ -2841,19 +2857,20 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
     bar_nofence();
     if (st + 1 < nst) {
       issue_b(st + 1, (st + 1) & 1);
-      load_a(st + 1);
+      load_a();
     }
     return (uint32_t)((st & 1) * SLOT);
   };
   const int nfull = ng / GPS;
   for (int st = 0; st < nfull; ++st) {
     const uint32_t soff = ready(st);
-    wide_stage<CA, CB, WFM, GPS, GPS>(acc, a_lds + soff, b_lds + soff);
+    wide_stage<CA, CB, WFM, GPS, GPS / KS, KS>(acc, a_lds + soff, b_lds + soff);
     if (st + 1 < nst) write_a((st + 1) & 1);
   }
   if (nfull < nst) {
     const uint32_t soff = ready(nfull);
-    wide_stage_rem<CA, CB, WFM, GPS, GPS - 1>(acc, a_lds + soff, b_lds + soff, ng - nfull * GPS);
+    wide_stage_rem<CA, CB, WFM, GPS, KS == 1 ? GPS - 1 : GPS / KS, KS>(
+        acc, a_lds + soff, b_lds + soff, (ng - nfull * GPS - ks + KS - 1) / KS);
   }
   // Everyone is done reading the ring before the next group refills it.
   bar_nofence();
@@ -3051,14 +3068,28 @@ __device__ __forceinline__ void qn_store(const GemmArgs& a, const uint8_t* qs, i
         *reinterpret_cast<const uint4*>(qs + c * (BM + 16) + ch * 16);
 }
 
+// Row and column block of a tile: the tiles of one row block follow each
+// other, or, where the weights are the larger operand (xcd_tiles = 2), those
+// of one column block, so that an XCD reads its share of the weights once
+// (301 x 4099 x 4091: 23.5 against 19.6 us; 4096 x 2304 x 768, whose
+// activations are larger: 22.2 against 24.6 the other way).
+__device__ __forceinline__ int2 tile_at(const GemmArgs& a, int tile, int ntn) {
+  const bool cols = a.xcd_tiles == 2;
+  const int d = cols ? (int)gridDim.x / ntn : ntn;
+  const int q = tile / d, r = tile - q * d;
+  // kept in SGPRs: everything the K loop addresses with derives from them
+  return make_int2(__builtin_amdgcn_readfirstlane(cols ? r : q),
+                   __builtin_amdgcn_readfirstlane(cols ? q : r));
+}
+
 // (32*WFM) x 128 output tile per workgroup of four waves (2 x 2).  QN > 0:
 // the epilogue also quantizes every output for the next layer into qn_img
 // (and stores Y only when a.Y is set), with one static scale per
 // next-layer group (QN = 1) or per block of a next layer with sub-group
 // scales (QN = 2, asked to keep three waves per SIMD).
 template <int S, int CA0, int CA1, int CBL, int CBH, int WFM, int NST, int QN = 0, bool F = false,
-          bool CV = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
+          bool CV = false, int KS = 1>
+__global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS > 1 ? 2 : 
     QN == 2 ? 3 : WFM == 2 ? 3 : 2)))
 void k_gemm(GemmArgs a) {
   constexpr int BM = 32 * WFM;
@@ -3073,7 +3104,8 @@ void k_gemm(GemmArgs a) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wid >> 1, wn = wid & 1;
+  const int ks = KS == 1 ? 0 : wid >> 2;  // the wave set: granules ks, ks + KS, ... of a stage
+  const int wm = (wid >> 1) & 1, wn = wid & 1;
   const ActPlan& ap = a.ap;
   const int ntn = a.wp.Np / kGemmBN;
   // Workgroups go round-robin to the 8 XCDs (b mod 8), each with its own
@@ -3084,7 +3116,8 @@ void k_gemm(GemmArgs a) {
   // concurrent tiles share weight tiles across XCDs.
   const int G = (int)gridDim.x, x = (int)(blockIdx.x & 7), l = (int)(blockIdx.x >> 3);
   const int tile = a.xcd_tiles ? x * (G >> 3) + min(x, G & 7) + l : (int)blockIdx.x;
-  const int mt = tile / ntn, nt = tile - mt * ntn;
+  const int2 at = tile_at(a, tile, ntn);
+  const int mt = at.x, nt = at.y;
   const int64_t m0 = (int64_t)mt * BM;
   const int jb0 = nt * 8;
 
@@ -3141,13 +3174,13 @@ void k_gemm(GemmArgs a) {
       const int g = qbase ? 1 : 0;
       const uint8_t* img = a.img + a.cg.img_off[g];
       if (CBL == CBH || tile_lo)
-        gemm_group_conv<CA, CBL, NST, SLOT>(lds, img, a.cg.rowbytes[g], a.cg.cpad[g], a.cg.H,
-                                            a.cg.W, a.M, m0, ng, wtile, wbytes, a.wp.ngt, qbase,
-                                            acc, tid, lane, wid, wm, wn);
+        gemm_group_conv<CA, CBL, NST, SLOT, KS>(lds, img, a.cg.rowbytes[g], a.cg.cpad[g], a.cg.H,
+                                                a.cg.W, a.M, m0, ng, wtile, wbytes, a.wp.ngt,
+                                                qbase, acc, tid, lane, wid, wm, wn, ks);
       else
-        gemm_group_conv<CA, CBH, NST, SLOT>(lds, img, a.cg.rowbytes[g], a.cg.cpad[g], a.cg.H,
-                                            a.cg.W, a.M, m0, ng, wtile, wbytes, a.wp.ngt, qbase,
-                                            acc, tid, lane, wid, wm, wn);
+        gemm_group_conv<CA, CBH, NST, SLOT, KS>(lds, img, a.cg.rowbytes[g], a.cg.cpad[g], a.cg.H,
+                                                a.cg.W, a.M, m0, ng, wtile, wbytes, a.wp.ngt,
+                                                qbase, acc, tid, lane, wid, wm, wn, ks);
       return;
     }
     if constexpr (F && CA != 0 && CBL != 0 && CBH != 0) {
@@ -3184,11 +3217,11 @@ void k_gemm(GemmArgs a) {
     }
     if constexpr (CA != 0 && CBL != 0 && CBH != 0) {
       if (CBL == CBH || tile_lo)
-        gemm_group_wide<CA, CBL, WFM, NST, SLOT>(lds, abase, mstride, ng, wtile, wbytes, a.wp.ngt,
-                                                 qbase, acc, tid, lane, wid, wm, wn);
+        gemm_group_wide<CA, CBL, WFM, NST, SLOT, KS>(lds, abase, mstride, ng, wtile, wbytes,
+                                                     a.wp.ngt, qbase, acc, tid, lane, wid, wm, wn, ks);
       else
-        gemm_group_wide<CA, CBH, WFM, NST, SLOT>(lds, abase, mstride, ng, wtile, wbytes, a.wp.ngt,
-                                                 qbase, acc, tid, lane, wid, wm, wn);
+        gemm_group_wide<CA, CBH, WFM, NST, SLOT, KS>(lds, abase, mstride, ng, wtile, wbytes,
+                                                     a.wp.ngt, qbase, acc, tid, lane, wid, wm, wn, ks);
     } else {
       gemm_group_any<CA, CBL, CBH, WFM, NST, ASLOT, SLOT>(lds, abase, mstride, ca_rt, ng, wtile,
                                                           a.wp.ngt, bc, bpre, qbase, acc, tid,
@@ -3206,6 +3239,25 @@ void k_gemm(GemmArgs a) {
     run_group(std::integral_constant<int, CA1>{}, a.act + ap.seg_off[1] + (m0 / kBlk) * ap.mblk_bytes[1],
               ap.mblk_bytes[1], ap.c[1], ap.ng[1], ap.ng[0], acc1);
 
+  if constexpr (KS == 2) {
+    // the two sets' sums meet in LDS (the ring is free): set ks keeps rows
+    // block i = ks of its wave tile, gives the other one away and adds what
+    // it is given, so that both sets share the epilogue
+    static_assert(WFM == 2 && 8 * 4 * 1024 <= NST * SLOT, "exchange fits the ring");
+    v4i* ex = reinterpret_cast<v4i*>(lds);
+    auto swap = [&](v4i (&acc)[WFM][4]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) ex[(wid * 4 + jj) * 64 + lane] = ks ? acc[0][jj] : acc[WFM - 1][jj];
+      __syncthreads();
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        acc[0][jj] = (ks ? acc[WFM - 1][jj] : acc[0][jj]) + ex[((wid ^ 4) * 4 + jj) * 64 + lane];
+      __syncthreads();
+    };
+    swap(acc0);
+    if constexpr (S == 2) swap(acc1);
+  }
+  constexpr int EI = WFM / KS;  // 16-row blocks of this wave in the epilogue
   // Epilogue: exact int32 per group, fixed-order fp32 scaling, bf16.  The
   // tile is staged in LDS (the ring is free: gemm_group ended with a
   // barrier) with its columns in ascending original order, then stored so
@@ -3250,8 +3302,8 @@ void k_gemm(GemmArgs a) {
       const int add0s = add0 * (1 << sh0), add1s = S == 2 ? add1 * (1 << sh1) : 0;
       uint32_t* ycol = reinterpret_cast<uint32_t*>(ys + (WFM <= 2 ? crank[jj] : a.wd.colrank[pc]) * YT);
 #pragma unroll
-      for (int i = 0; i < WFM; ++i) {
-        const int row0 = (wm * WFM + i) * 16 + (lane >> 4) * 4;
+      for (int i = 0; i < EI; ++i) {
+        const int row0 = (wm * WFM + (KS > 1 ? ks : i)) * 16 + (lane >> 4) * 4;
         float y[4];
         if (scaled) [[likely]] {
 #pragma unroll
@@ -3319,7 +3371,7 @@ void k_gemm(GemmArgs a) {
       const int mrem = (int)min((int64_t)BM, a.M - m0);
       uint16_t* yout = a.Y + m0 * a.ldy + n;
       const uint32_t* yc = reinterpret_cast<const uint32_t*>(ys + (tid & (kGemmBN - 1)) * YT);
-      for (int row = 2 * (tid / kGemmBN); row < mrem; row += 512 / kGemmBN) {
+      for (int row = 2 * (tid / kGemmBN); row < mrem; row += 512 * KS / kGemmBN) {
         const uint32_t v = yc[row / 2];
         yout[(int64_t)row * a.ldy] = (uint16_t)(v & 0xFFFFu);
         if (row + 1 < mrem) yout[(int64_t)(row + 1) * a.ldy] = (uint16_t)(v >> 16);
@@ -4883,7 +4935,8 @@ void k_gemm_g(GemmArgs a) {
   const int ntn = a.wp.Np / kGemmBN;
   const int G = (int)gridDim.x, x = (int)(blockIdx.x & 7), l = (int)(blockIdx.x >> 3);
   const int tile = a.xcd_tiles ? x * (G >> 3) + min(x, G & 7) + l : (int)blockIdx.x;
-  const int mt = tile / ntn, nt = tile - mt * ntn;
+  const int2 at = tile_at(a, tile, ntn);
+  const int mt = at.x, nt = at.y;
   const int64_t m0 = (int64_t)mt * BM;
   const int jb0 = nt * 8;
 
@@ -5565,44 +5618,61 @@ static GemmArgs make_args(const uint8_t* act_packed, const float* s_a, const Act
   return a;
 }
 
-// Tile shapes: 3 = 128x128 (WFM 4, 2-deep ring, two workgroups per CU),
-// 7 = 64x128 (WFM 2, 2-deep, three per CU), 2 = 64x128 (WFM 2, 3-deep).
+// Tile shapes: 3 = 128x128 (WFM 4, two workgroups per CU), 7 = 64x128 (WFM
+// 2, three per CU), 8 = 64x128 with two sets of four waves that share the K
+// loop, 1 = 32x128; all through a 2-deep ring.
 template <int S, int CA0, int CA1, int CBL, int CBH>
 static void launch_gemm_t(const GemmArgs& a, int64_t M, int shape, hipStream_t stream) {
   const int ntn = a.wp.Np / kGemmBN;
   const dim3 blk(256);
-  constexpr bool FOK = CA0 != 0 && CBL != 0 && CBH != 0;
-  if (FOK && a.fa && shape != 2) {
+  constexpr bool KNOWN = CA0 != 0 && CBL != 0 && CBH != 0;
+  auto grid = [&](int bm) { return dim3((unsigned)((M + bm - 1) / bm * ntn)); };
+  if (KNOWN && a.fa) {
     // tiles with MFMA-native copies of the narrow operands
     if (shape == 3)
-      hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 4, 2, 0, FOK>),
-                         dim3((unsigned)(((M + 127) / 128) * ntn)), blk, 0, stream, a);
+      hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 4, 2, 0, KNOWN>), grid(128), blk, 0, stream, a);
     else
-      hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 2, 2, 0, FOK>),
-                         dim3((unsigned)(((M + 63) / 64) * ntn)), blk, 0, stream, a);
+      hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 2, 2, 0, KNOWN>), grid(64), blk, 0, stream, a);
     return;
   }
-  switch (shape) {
-    case 3:
-      hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 4, 2>), dim3((unsigned)(((M + 127) / 128) * ntn)), blk, 0, stream, a);
-      break;
-    case 2:
-      hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 2, 3>), dim3((unsigned)(((M + 63) / 64) * ntn)), blk, 0, stream, a);
-      break;
-    default:
-      hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 2, 2>), dim3((unsigned)(((M + 63) / 64) * ntn)), blk, 0, stream, a);
-      break;
-  }
+  if (shape == 3)
+    hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 4, 2>), grid(128), blk, 0, stream, a);
+  else if (KNOWN && shape == 8)
+    hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 2, 2, 0, false, false, KNOWN ? 2 : 1>), grid(64),
+                       dim3(KNOWN ? 512 : 256), 0, stream, a);
+  else if (KNOWN && shape == 1)
+    hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, KNOWN ? 1 : 2, 2>), grid(32), blk, 0, stream, a);
+  else
+    hipLaunchKernelGGL((k_gemm<S, CA0, CA1, CBL, CBH, 2, 2>), grid(64), blk, 0, stream, a);
 }
 
 // 128x128 tiles when there are enough of them to keep every CU busy for
-// several rounds; otherwise 64x128 tiles through a 2-deep ring, which hide
-// latency better on smaller problems.  SONIQ_GEMM_SHAPE (2, 3 or 7)
-// overrides the choice for measurement; results do not depend on it.
-static int gemm_shape(int64_t M, int ntn) {
+// several rounds; otherwise 64x128 tiles, three per CU, which hide latency
+// better on smaller problems.  Where those are at most one per CU, a wave
+// has its SIMD to itself and its widening and its products take turns
+// instead of overlapping: two wave sets then split each stage's granules
+// (6272 x 256 x 2304, 196 tiles: 14.0 against 12.7 us; 128 x 4096 x 4096, 66
+// tiles: 18.8 against 16.4; but 4096 x 768 x 3072, 448 tiles: 23.1 against
+// 27.8).  With few tiles and a short K the epilogue is the larger part:
+// 32-row tiles halve it (64 x 256 x 256: 6.6 against 5.0).
+// SONIQ_GEMM_SHAPE (1, 3, 7 or 8) overrides the choice for measurement;
+// results do not depend on it.
+static int gemm_shape(int64_t M, int ntn, int ngt) {
   if (const char* e = getenv("SONIQ_GEMM_SHAPE")) return atoi(e);
   if (((M + 127) / 128) * ntn >= 1024) return 3;
-  return 7;
+  const int64_t tiles = (M + 63) / 64 * ntn;
+  if (tiles <= 128 && ngt <= 16) return 1;
+  return tiles <= 256 ? 8 : 7;
+}
+static int gemm_rows(int shape) { return shape == 3 ? 128 : shape == 1 ? 32 : 64; }
+
+// How a launch orders its tiles (GemmArgs::xcd_tiles): long grids (more than
+// a few rounds of two workgroups per CU) keep the launch order.
+static int tile_order(int64_t tiles, int64_t a_bytes, int64_t w_bytes) {
+  return tiles > 2048 ? 0 : w_bytes > a_bytes ? 2 : 1;
+}
+static int64_t act_batch_bytes(const ActPlan& ap, int64_t M) {
+  return (M + kBlk - 1) / kBlk * (ap.mblk_bytes[0] + (ap.S == 2 ? ap.mblk_bytes[1] : 0));
 }
 
 hipError_t launch_mp_gemm(const uint8_t* act_packed, const float* s_a, const ActPlan& ap,
@@ -5617,9 +5687,13 @@ hipError_t launch_mp_gemm(const uint8_t* act_packed, const float* s_a, const Act
   }
   const int ca0 = ap.c[0], ca1 = ap.S == 2 ? ap.c[1] : 0;
   const int cl = wp.c_lo, ch = wp.c_hi;
-  const int shape = gemm_shape(M, wp.Np / kGemmBN);
-  const int64_t tiles = (shape == 3 ? (M + 127) / 128 : (M + 63) / 64) * (wp.Np / kGemmBN);
-  a.xcd_tiles = tiles <= 2048;  // a few rounds of two workgroups per CU
+  const bool known = ap.S == 2 && ca0 == 4 && ca1 == 8 &&
+                     ((cl == 4 && ch == 8) || (cl == 4 && ch == 4) || (cl == 2 && ch == 8) ||
+                      (cl == 1 && ch == 4) || (cl == 2 && ch == 4));
+  int shape = gemm_shape(M, wp.Np / kGemmBN, wp.ngt);
+  if ((!known || a.fa) && shape != 3) shape = 7;
+  const int64_t tiles = (M + gemm_rows(shape) - 1) / gemm_rows(shape) * (wp.Np / kGemmBN);
+  a.xcd_tiles = tile_order(tiles, act_batch_bytes(ap, M), (int64_t)wblk_off(wp, wp.nblk));
   if (ap.S == 2 && ca0 == 4 && ca1 == 8) {
     if (cl == 4 && ch == 8) launch_gemm_t<2, 4, 8, 4, 8>(a, M, shape, stream);
     else if (cl == 4 && ch == 4) launch_gemm_t<2, 4, 8, 4, 4>(a, M, shape, stream);
@@ -6183,9 +6257,12 @@ hipError_t launch_conv_img(const float* X, int64_t B, int64_t C, int64_t H, int6
 
 template <int CBL, int CBH>
 static void launch_gemm_conv_t(const GemmArgs& a, int64_t M, hipStream_t stream) {
-  const int ntn = a.wp.Np / kGemmBN;
-  hipLaunchKernelGGL((k_gemm<2, 4, 8, CBL, CBH, 2, 2, 0, false, true>),
-                     dim3((unsigned)(((M + 63) / 64) * ntn)), dim3(256), 0, stream, a);
+  // two wave sets where the tiles leave a wave its SIMD to itself, as gemm_shape
+  const dim3 grid((unsigned)(((M + 63) / 64) * (a.wp.Np / kGemmBN)));
+  if (grid.x <= 256)
+    hipLaunchKernelGGL((k_gemm<2, 4, 8, CBL, CBH, 2, 2, 0, false, true, 2>), grid, dim3(512), 0, stream, a);
+  else
+    hipLaunchKernelGGL((k_gemm<2, 4, 8, CBL, CBH, 2, 2, 0, false, true>), grid, dim3(256), 0, stream, a);
 }
 
 // One activation width in 4- or 8-bit containers: the tiles with S = 1.
