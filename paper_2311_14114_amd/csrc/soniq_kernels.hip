@@ -2093,6 +2093,14 @@ constexpr int gemm_slot(int S, int CA0, int CA1, int CBL, int CBH, int WFM) {
               : 128 * 16 * (CBH > CBL ? CBH : CBL));
 }
 
+// The implicit convolution with two wave sets and two activation widths:
+// two-granule stages, and as many of them as 64 KB hold.  Its units come
+// through registers, so a load one stage ahead is waited for at the stage's
+// end; three ahead, with four slots, they arrive in time (196 tiles of 6272 x
+// 256 x 2304: 19.4 against 17.0 us).
+constexpr int gemm_conv_slot(int CBH) { return CBH == 8 ? 24576 : 16384; }
+constexpr int gemm_conv_nst(int CBH) { return 65536 / gemm_conv_slot(CBH); }
+
 // Fragment reads from the LDS ring are issued as inline asm.  The ring is
 // filled by direct global->LDS loads whose completion each wave awaits with
 // an explicit vmcnt wait and a barrier; through plain C++ loads the
@@ -2776,7 +2784,8 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
   constexpr int CHB = 64 * GPS * CB;
   constexpr int LA = wide_loads(16 * WFM * GPS * CA, KS), LB = wide_loads(CHB, KS);
   constexpr int ABYTES = 4096 * KS * LA;
-  static_assert(NST == 2, "two ring slots");
+  constexpr int D = NST - 1;  // stages in flight ahead of the one in use
+  static_assert(D >= 1 && (LB + GPS / KS) * (D - 1) < 64, "vmcnt range");
   static_assert(4096 * KS * (LA + LB) <= SLOT, "a stage fits its slot");
   const int nst = (ng + GPS - 1) / GPS;
 
@@ -2818,18 +2827,27 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
   int ku = __builtin_amdgcn_readfirstlane(4 * ks + kg);  // unit index
   int tap = __builtin_amdgcn_readfirstlane(ku / cu);
   int c16 = ku - tap * cu;
-  const uint8_t* img0 = img + (int64_t)hp0 * rowbytes;
-  raw_t<CA> ua[QA];
-  auto load_a = [&]() __attribute__((always_inline)) {
+  // addressed from the haloed pixel up and left of the tile's first one
+  // (haloed indices grow with the pixel, so no offset is negative)
+  const int bt = (int)(m0 / HW), remt = (int)(m0 - (int64_t)bt * HW);
+  const int hpt = __builtin_amdgcn_readfirstlane((bt * (H + 2) + remt / W + 1) * Wp + remt % W + 1);
+  const __amdgpu_buffer_rsrc_t ir = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(img + (int64_t)(hpt - Wp - 1) * rowbytes), (short)0, (int)kOOB, 0x00020000);
+  const uint32_t ao = (uint32_t)((hp0 - hpt) * rowbytes);
+  raw_t<CA> ua[D][QA];
+  auto load_a = [&](raw_t<CA> (&dst)[QA]) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < QA; ++q) {
       const int tr = tap >= 6 ? 2 : tap >= 3 ? 1 : 0;
       const int dp = (tr - 1) * Wp + (tap - 3 * tr - 1);
-      // units past the group's end read the center pixel and count as zero
+      // units past the group's end read as zeros; a load either way, so that
+      // the waits below count the same loads in every stage
       const bool in = ku < kend;
-      const raw_t<CA> v =
-          *reinterpret_cast<const raw_t<CA>*>(img0 + (in ? dp * rowbytes + c16 * 2 * CA : 0));
-      ua[q] = in ? v : raw_t<CA>{};
+      const uint32_t vo = in ? ao : kOOB, so = (uint32_t)((dp + Wp + 1) * rowbytes + c16 * 2 * CA);
+      if constexpr (CA == 8)
+        dst[q] = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(ir, vo, in ? so : 0u, 0));
+      else
+        dst[q] = __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(ir, vo, in ? so : 0u, 0));
       ku += 4 * KS;
       c16 += 4 * KS;
       while (c16 >= cu) {
@@ -2839,39 +2857,48 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
     }
   };
   const int aw = (mb * GPS + ks) * 128 * CA + (kg * 16 + r) * 2 * CA;
-  auto write_a = [&](int slot) __attribute__((always_inline)) {
+  auto write_a = [&](int slot, const raw_t<CA> (&src)[QA]) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < QA; ++q)
-      *reinterpret_cast<raw_t<CA>*>(lds + slot * SLOT + aw + q * KS * 128 * CA) = ua[q];
+      *reinterpret_cast<raw_t<CA>*>(lds + slot * SLOT + aw + q * KS * 128 * CA) = src[q];
   };
 
   const uint32_t b_lds = lds_off(lds) + (uint32_t)(ABYTES + wn * 4 * GPS * 128 * CB + ks * 128 * CB + lane * 2 * CB);
   const uint32_t a_lds = lds_off(lds) + (uint32_t)(wm * WFM * GPS * 128 * CA + ks * 128 * CA + lane * 2 * CA);
 
-  issue_b(0, 0);
-  load_a();
-  write_a(0);
-  auto ready = [&](int st) __attribute__((always_inline)) {
-    // this thread's unit writes and every wave's weight loads have landed
-    __builtin_amdgcn_s_waitcnt(0);
+  // Stages past the last are issued and read as zeros (the weights' chunks
+  // are out of range, the units past the group's end), so the waits count
+  // the same loads in every iteration.
+#pragma unroll
+  for (int s = 0; s < D; ++s) {
+    issue_b(s, s);
+    load_a(ua[s]);
+  }
+  write_a(0, ua[0]);
+  // Iteration st: its weights have landed (at most the later stages' loads
+  // are in flight) and every wave's units are in LDS; stage st + D is
+  // requested into the slot that stage st - 1 has left, and the units of
+  // stage st + 1 go to LDS while this stage's products run.
+  auto stage = [&](int st, raw_t<CA> (&next)[QA], raw_t<CA> (&refill)[QA]) __attribute__((always_inline)) {
+    wait_vm<(LB + QA) * (D - 1)>();
+    __builtin_amdgcn_s_waitcnt(SONIQ_LGKMCNT0_IMM);
     bar_nofence();
-    if (st + 1 < nst) {
-      issue_b(st + 1, (st + 1) & 1);
-      load_a();
-    }
-    return (uint32_t)((st & 1) * SLOT);
-  };
-  const int nfull = ng / GPS;
-  for (int st = 0; st < nfull; ++st) {
-    const uint32_t soff = ready(st);
+    issue_b(st + D, (st + D) % NST);
+    load_a(refill);
+    const uint32_t soff = (uint32_t)((st % NST) * SLOT);
     wide_stage<CA, CB, WFM, GPS, GPS / KS, KS>(acc, a_lds + soff, b_lds + soff);
-    if (st + 1 < nst) write_a((st + 1) & 1);
+    write_a((st + 1) % NST, next);
+    asm volatile("" ::: "memory");  // a stage's loads stay between its barriers
+  };
+  for (int st0 = 0; st0 < nst; st0 += D) {
+#pragma unroll
+    for (int k = 0; k < D; ++k)
+      if (st0 + k < nst) stage(st0 + k, ua[(k + 1) % D], ua[k]);
   }
-  if (nfull < nst) {
-    const uint32_t soff = ready(nfull);
-    wide_stage_rem<CA, CB, WFM, GPS, KS == 1 ? GPS - 1 : GPS / KS, KS>(
-        acc, a_lds + soff, b_lds + soff, (ng - nfull * GPS - ks + KS - 1) / KS);
-  }
+  // the loads issued past the last stage have landed before the ring and
+  // their registers are used again
+  wait_vm<0>();
+  __builtin_amdgcn_s_waitcnt(SONIQ_LGKMCNT0_IMM);
   // Everyone is done reading the ring before the next group refills it.
   bar_nofence();
 #endif
@@ -3098,7 +3125,8 @@ void k_gemm(GemmArgs a) {
   // operands get wide stages (gemm_group_wide).
   constexpr bool KNOWN = CA0 != 0 && (S == 1 || CA1 != 0) && CBL != 0 && CBH != 0;
   constexpr int SLOT0 = gemm_slot(S, CA0, CA1, CBL, CBH, WFM);
-  constexpr int SLOT = KNOWN && WFM == 2 && SLOT0 < 24576 ? 24576 : SLOT0;
+  constexpr int SLOT = CV && KS > 1 ? gemm_conv_slot(CBH)
+                       : KNOWN && WFM == 2 && SLOT0 < 24576 ? 24576 : SLOT0;
   constexpr int ASLOT = gemm_aslot(S, CA0, CA1, CBL, CBH, WFM);
   __shared__ __align__(16) uint8_t lds[NST * SLOT];
   const int tid = threadIdx.x;
@@ -6197,39 +6225,72 @@ __global__ __launch_bounds__(256) void k_conv_img(const float* __restrict__ X, i
                                                   ActPlan ap, ConvGeo cg, uint8_t* __restrict__ img,
                                                   float* __restrict__ s_a_out) {
   __shared__ float red[8];
-  float s0, s1;
-  scales_from_partials(partial, nparts, ap, red, s0, s1, s_a_out);  // syncs
-  const ActQ aq = make_actq(ap, s0, s1);
   const int u0 = cg.cpad[0] / 16, u1 = ap.S == 2 ? cg.cpad[1] / 16 : 0;
   const int n0 = HP * u0, total = n0 + HP * u1;
   const int Wp = W + 2, HPi = (H + 2) * Wp;
-  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < total; i += (int)(gridDim.x * 256)) {
-    const int g = i >= n0 ? 1 : 0;
+  int g = 0, u = 0, hp = 0;
+  bool halo = false;
+  int cc[16];
+  float xv[16];
+  // every load unconditional and in bounds (a halo pixel or a padding rank
+  // reads pixel (0, 0) of channel 0 and discards it; items past the end the
+  // last one's), so all 16 are in flight at once
+  auto load = [&](int i) __attribute__((always_inline)) {
+    i = min(i, total - 1);
+    g = i >= n0 ? 1 : 0;
     const int j = g ? i - n0 : i;
-    const int u = j / HP, hp = j - u * HP;
+    u = j / HP;
+    hp = j - u * HP;
     const int b = hp / HPi, rem = hp - b * HPi;
     const int yh = rem / Wp, xh = rem - yh * Wp;
-    const bool halo = yh == 0 || yh == H + 1 || xh == 0 || xh == W + 1;
-    // every load unconditional and in bounds (a halo pixel or a padding
-    // rank reads pixel (0, 0) of channel 0 and discards it), so all 16 are
-    // in flight at once
+    halo = yh == 0 || yh == H + 1 || xh == 0 || xh == W + 1;
     const int64_t pix = halo ? 0 : (int64_t)(yh - 1) * W + (xh - 1);
-    int cc[16];
-    float xv[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) cc[e] = chan[g * cg.chan_ld + 16 * u + e];
 #pragma unroll
     for (int e = 0; e < 16; ++e) xv[e] = X[((int64_t)b * C + max(cc[e], 0)) * H * W + pix];
-    uint32_t d[4] = {0u, 0u, 0u, 0u};
+  };
+  const int step = (int)(gridDim.x * 256);
+  int i = (int)(blockIdx.x * 256 + threadIdx.x);
+  load(i);  // ahead of the partial maxima, so the latencies overlap
+  float s0, s1;
+  scales_from_partials(partial, nparts, ap, red, s0, s1, s_a_out);  // syncs
+  const bool ok0 = fast_ok(s0), ok1 = fast_ok(s1);
+  const float rs0 = ok0 ? __builtin_amdgcn_rcpf(s0) : 0.0f, rs1 = ok1 ? __builtin_amdgcn_rcpf(s1) : 0.0f;
+  const bool sgn = ap.q[0].lo < 0;  // one signedness for both groups
+  while (i < total) {
+    // the single pass's codes (qcodes4): rounded by one fma, without the
+    // zero point, which the packing's XOR applies; a padding rank starts as
+    // the zero point and packs to a stored zero
+    const float sc = g ? s1 : s0, rs = g ? rs1 : rs0;
+    const bool ok = g ? ok1 : ok0;
+    const float hi = g ? (float)ap.q[1].hi : (float)ap.q[0].hi;
+    const uint32_t zp = (uint32_t)(g ? ap.zp[1] : ap.zp[0]);
+    uint32_t cd[16];
+    float dm = 0.0f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      // padding rank: stored 0; halo: the code of 0.0
-      const uint32_t byte = cc[e] < 0 ? 0u : store_code(halo ? 0.0f : xv[e], g, aq);
-      d[e >> 2] |= byte << (8 * (e & 3));
+      const float x = halo ? 0.0f : xv[e];
+      const float t = __builtin_fmaf(x, rs, kShift);
+      cd[e] = __float_as_uint(sgn ? t : fmaxf(t, kShift)) & 0xFFu;
+      dm = fmaxf(dm, fabsf(__builtin_fmaf(x, rs, kShift - t)));
     }
+    if (!ok || dm >= 0.5f - kTieBand) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float x = halo ? 0.0f : xv[e];
+        cd[e] = (uint32_t)qexact(x, sgn ? -hi : 0.0f, hi, 0.0f, sc) & 0xFFu;
+      }
+    }
+    uint32_t d[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int e = 0; e < 16; ++e) d[e >> 2] |= (cc[e] < 0 ? zp : cd[e]) << (8 * (e & 3));
+    const uint32_t zx = 0x01010101u * zp;
     const int c = ap.c[g];
     uint8_t* dst = img + cg.img_off[g] + (int64_t)hp * cg.rowbytes[g] + u * 2 * c;
-    store_unit(dst, pack_unit(d[0], d[1], d[2], d[3], c), c);
+    store_unit(dst, pack_unit(d[0] ^ zx, d[1] ^ zx, d[2] ^ zx, d[3] ^ zx, c), c);
+    i += step;
+    if (i < total) load(i);
   }
 }
 
@@ -6260,7 +6321,8 @@ static void launch_gemm_conv_t(const GemmArgs& a, int64_t M, hipStream_t stream)
   // two wave sets where the tiles leave a wave its SIMD to itself, as gemm_shape
   const dim3 grid((unsigned)(((M + 63) / 64) * (a.wp.Np / kGemmBN)));
   if (grid.x <= 256)
-    hipLaunchKernelGGL((k_gemm<2, 4, 8, CBL, CBH, 2, 2, 0, false, true, 2>), grid, dim3(512), 0, stream, a);
+    hipLaunchKernelGGL((k_gemm<2, 4, 8, CBL, CBH, 2, gemm_conv_nst(CBH), 0, false, true, 2>), grid,
+                       dim3(512), 0, stream, a);
   else
     hipLaunchKernelGGL((k_gemm<2, 4, 8, CBL, CBH, 2, 2, 0, false, true>), grid, dim3(256), 0, stream, a);
 }
