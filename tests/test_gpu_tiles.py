@@ -64,3 +64,35 @@ def test_conv_wave_sets(B, C, H, W, N):
     r = oracle.run(case["A"], case["W"], case["a_bits"], case["w_bits"], False)
     np.testing.assert_array_equal(acc.cpu().numpy(), r["acc"])
     np.testing.assert_array_equal(Y.view(torch.int16).cpu().numpy().view(np.uint16), r["y_replay"])
+
+
+@pytest.mark.parametrize("with_acc", [True, False], ids=["acc", "y"])
+@pytest.mark.parametrize("c", [  # (M, N, K, a_frac, w_lo, w_hi, group bits, input scale)
+    (70, 200, 1000, 0.8, 2, 8, 512, 1.0),      # 13 + 4 granules: an odd narrow group
+    (40, 130, 600, 0.2, 2, 4, 512, 1.0),       # 2 + 8
+    (40, 130, 64, 1.0, 1, 4, 512, 1.0),        # one granule, sign weights
+    (40, 130, 3000, 0.7, 4, 8, 1024, 1.0),     # blocks of four and two granules
+    (40, 130, 700, 0.7, 2, 4, 512, 2.0 ** -104),  # scales too small for the folded shift
+], ids=lambda c: "x".join(map(str, c[:3])) + f"_w{c[4]}{c[5]}_g{c[6]}")
+def test_block_tiles(c, with_acc):
+    """The tiles with sub-group scales: the 512-bit folds, the general hook,
+    and both with accumulators asked for."""
+    M, N, K, fa, wlo, whi, gbits, scale = c
+    case = workloads.generic(M, N, K, a_lo=4, a_hi=8, a_frac_lo=fa, w_lo=wlo, w_hi=whi, w_frac_lo=0.6,
+                             seed=M + N + K, name="block_tiles")
+    A = case["A"] * np.float32(scale)
+    print(f"[gpu] block tiles {c} acc={with_acc}", flush=True)
+    w = sq.soniq_pack_weights(torch.from_numpy(case["W"]).cuda(), case["w_bits"], case["a_bits"], True,
+                              act_group_bits=gbits)
+    act = sq.soniq_act_create(w, M)
+    sq.soniq_quantize_act(act, torch.from_numpy(A).cuda())
+    acc = torch.empty((w.S, M, N), dtype=torch.int32, device="cuda") if with_acc else None
+    Y = sq.soniq_mp_gemm(act, w, acc=acc)
+    torch.cuda.synchronize()
+    q_w, s_w = oracle.quantize_weights(case["W"], case["w_bits"])
+    q_a, s_a, _, sub_of = oracle.quantize_act_grouped(A, case["a_bits"], True, gbits)
+    racc = oracle.mac(q_a, q_w, sub_of, len(s_a))
+    if with_acc:
+        np.testing.assert_array_equal(acc.cpu().numpy(), racc)
+    np.testing.assert_array_equal(Y.view(torch.int16).cpu().numpy().view(np.uint16),
+                                  oracle.epilogue_replay(racc, s_a, s_w))
