@@ -4591,26 +4591,46 @@ __global__ __launch_bounds__(256) void k_pack_img_split(const uint8_t* __restric
   }
 }
 
-// Every other case (the GEMV forms' row-major image, a 1-bit group, the
-// last block of a batch): R rows per workgroup from block row blk0*R on go
-// to LDS as rows of planned positions and out as units.  Workgroup 0 also
-// stores the static scales (when s_a is set).  Dynamic LDS: R*Kp bytes.
+// The GEMV forms' row-major image (M <= 8 rows): one thread per 16-channel
+// unit, straight from the image to the packed rows (and, for one row, its
+// contiguous image).  Through LDS, a row per workgroup, one row of 11008
+// took 4.5 us in a captured step; this takes 3.9.  The first thread also
+// stores the static scales (when s_a is set).
+__global__ __launch_bounds__(256) void k_pack_rows(const uint8_t* __restrict__ img, int64_t ld, int M,
+                                                   ActPlan ap, float s0, float s1,
+                                                   float* __restrict__ s_a,
+                                                   uint8_t* __restrict__ packed,
+                                                   uint8_t* __restrict__ ximg) {
+  const int per = ap.Kp / 16, i = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (s_a && i == 0) {
+    s_a[0] = s0;
+    s_a[1] = s1;
+  }
+  if (i >= M * per) return;
+  const int m = i / per, u = i - m * per;
+  const int u0 = ap.ng[0] * 4, g = u >= u0 ? 1 : 0, v = g ? u - u0 : u;
+  const int c = g ? ap.c[1] : ap.c[0];
+  const uint4 d = *reinterpret_cast<const uint4*>(img + m * ld + 16 * u);
+  const uint4 w = pack_unit(d.x, d.y, d.z, d.w, c);
+  store_unit(packed + (g ? ap.seg_off[1] : ap.seg_off[0]) + (v >> 2) * 128 * c + ((v & 3) * 16 + m) * 2 * c,
+             w, c);
+  if (ximg != nullptr && c == (g ? 8 : 4)) store_unit(ximg + (g ? ap.ng[0] * 32 : 0) + v * 2 * c, w, c);
+}
+
+// Every other case (a 1-bit group, the last block of a batch): R rows per
+// workgroup from block row blk0*R on go to LDS as rows of planned positions
+// and out as units.  Workgroup 0 also stores the static scales (when s_a is
+// set).  Dynamic LDS: R*Kp bytes.
 template <int R>
 __global__ __launch_bounds__(256) void k_pack_img(const uint8_t* __restrict__ img, int64_t ld,
-                                                  bool blocked, int64_t blk0, int64_t M, ActPlan ap,
-                                                  float s0, float s1, float* __restrict__ s_a,
+                                                  int64_t blk0, int64_t M, ActPlan ap, float s0,
+                                                  float s1, float* __restrict__ s_a,
                                                   uint8_t* __restrict__ packed,
                                                   uint8_t* __restrict__ ximg) {
   extern __shared__ __align__(16) uint8_t codes[];
   const int64_t m0 = (blk0 + blockIdx.x) * R;
   const int rows = (int)min((int64_t)R, M - m0);
-  if (!blocked) {
-    for (int r = 0; r < rows; ++r) {
-      const uint4* src = reinterpret_cast<const uint4*>(img + (m0 + r) * ld);
-      for (int i = threadIdx.x; i < ap.Kp / 16; i += 256)
-        reinterpret_cast<uint4*>(codes + r * ap.Kp)[i] = src[i];
-    }
-  } else if (R == kBlk && rows == kBlk) {
+  if (R == kBlk && rows == kBlk) {
     img_block_rows(img + (m0 / kBlk) * ld, 0, ap.Kp / 4, codes);
   } else {
     // the last block of a batch, or one row: only its rows' bytes
@@ -5911,11 +5931,17 @@ hipError_t launch_mp_gemm_qnext(const uint8_t* act_packed, const float* s_a, con
                        s1, s_out, conv->img);
     return hipGetLastError();
   }
+  if (gemv_form) {
+    hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)((M * (ap2.Kp / 16) + 255) / 256)), dim3(256), 0,
+                       stream, img, a.qn_ld, (int)M, ap2, s0, s1, s_out, packed2,
+                       M == 1 ? ximg2 : nullptr);
+    return hipGetLastError();
+  }
   // Full 16-row blocks of the GEMM tiles' image (no 1-bit group) spread
-  // over about a thousand workgroups; the rest (the GEMV forms' rows, a
-  // 1-bit group, a last partial block) one block (or row) per workgroup.
+  // over about a thousand workgroups; the rest (a 1-bit group, a last
+  // partial block) one block (or row) per workgroup.
   const bool one_bit = ap2.c[0] == 1 || (ap2.S == 2 && ap2.c[1] == 1);
-  const int64_t nfull = !gemv_form && !one_bit ? M / kBlk : 0;
+  const int64_t nfull = !one_bit ? M / kBlk : 0;
   if (nfull > 0) {
     const int ngr = ap2.Kp / kGran;
     // at least enough parts to keep a part's LDS within 64 KB (64 granules)
@@ -5930,11 +5956,11 @@ hipError_t launch_mp_gemm_qnext(const uint8_t* act_packed, const float* s_a, con
   if (rest > 0) {
     if (kBlk * (size_t)ap2.Kp <= 64 * 1024)
       hipLaunchKernelGGL(k_pack_img<kBlk>, dim3((unsigned)((rest + kBlk - 1) / kBlk)), dim3(256),
-                         kBlk * (size_t)ap2.Kp, stream, img, a.qn_ld, !gemv_form, nfull, M, ap2, s0,
-                         s1, s_out, packed2, M == 1 ? ximg2 : nullptr);
+                         kBlk * (size_t)ap2.Kp, stream, img, a.qn_ld, nfull, M, ap2, s0, s1, s_out,
+                         packed2, M == 1 ? ximg2 : nullptr);
     else
       hipLaunchKernelGGL(k_pack_img<1>, dim3((unsigned)rest), dim3(256), (size_t)ap2.Kp, stream, img,
-                         a.qn_ld, !gemv_form, nfull * kBlk, M, ap2, s0, s1, s_out, packed2,
+                         a.qn_ld, nfull * kBlk, M, ap2, s0, s1, s_out, packed2,
                          M == 1 ? ximg2 : nullptr);
   }
   return hipGetLastError();
