@@ -3772,7 +3772,7 @@ __device__ __forceinline__ void gemv_store_x(const GemmArgs& a, int u0,
   const int total = (int)a.M * d;
 #pragma unroll
   for (int i = 0; i < gemv_xr<MT>(); ++i) {
-    const int u = u0 + i * 256 + (int)threadIdx.x;
+    const int u = u0 + i * (int)blockDim.x + (int)threadIdx.x;
     if (u < total) {
       const int m = gemv_row_of<MT>(u, d), rest = u - m * d;
       if (rest < d0 && NIB) {
@@ -3830,13 +3830,13 @@ __device__ __forceinline__ void gemv_store_out(const GemmArgs& a, int p, int64_t
 
 // FJ > 0 (batch of one row only): the fused form, which quantizes the fp32
 // row itself (FJ float4 per thread) instead of staging packed units.
-template <int CW, bool NIB, int FJ = 0>
+template <int CW, bool NIB, int T, int FJ = 0>
 __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int blk,
-                                            int (&red)[4][4][kBlk][2][1]) {
+                                            int (&red)[T / 64][4][kBlk][2][1]) {
   constexpr int MT = 1;
   constexpr int U = 8 / CW;
   constexpr int CPG = 8 * CW;    // chunks per granule
-  constexpr int QS = 256 / CPG;  // granules per slot of the workgroup
+  constexpr int QS = T / CPG;  // granules per slot of the workgroup
   // load slots per batch for the two activation groups (sized so a 4096-
   // channel row with a dominant narrow group needs one batch)
   constexpr int NB0 = CW == 1 ? 2 : CW == 2 ? 4 : CW == 4 ? 8 : 8;
@@ -3869,12 +3869,12 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
 #pragma unroll
     for (int mm = 0; mm < MT; ++mm) acc0[u][mm] = acc1[u][mm] = 0;
 
-  // Group-0 slot b of batch i holds chunk tid + 256*(i*NB0 + b), group-1
-  // slot b of batch i chunk tid + 256*(i*NB1 + b) past the group-0 chunks.
+  // Group-0 slot b of batch i holds chunk tid + T*(i*NB0 + b), group-1
+  // slot b of batch i chunk tid + T*(i*NB1 + b) past the group-0 chunks.
   auto issue0 = [&](int s0, uint4 (&raw)[NB0]) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < NB0; ++b) {
-      const int c = tid + 256 * (s0 + b);
+      const int c = tid + T * (s0 + b);
       raw[b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
                                              wr, c < nch0 ? (uint32_t)c * 16 : kOOB, 0, 0));
     }
@@ -3882,7 +3882,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
   auto issue1 = [&](int s0, uint4 (&raw)[NB1]) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < NB1; ++b) {
-      const int c = tid + 256 * (s0 + b);
+      const int c = tid + T * (s0 + b);
       raw[b] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
                                              wr, c < nch1 ? (uint32_t)(nch0 + c) * 16 : kOOB, 0, 0));
     }
@@ -3919,7 +3919,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
       }
 #pragma unroll
       for (int b = 0; b < NB0; ++b) {
-        if (256 * (s0 + b) >= nch0) break;  // the same for the whole workgroup
+        if (T * (s0 + b) >= nch0) break;  // the same for the whole workgroup
 #pragma unroll
         for (int mm = 0; mm < MT; ++mm) {
           if (mm < M) {
@@ -3934,16 +3934,16 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     } else {
 #pragma unroll
       for (int b = 0; b < NB0; ++b) {
-        if (256 * (s0 + b) >= nch0) break;  // the same for the whole workgroup
-        bytes_into(acc0, raw[b], min(q0 + QS * (s0 + b), ng0 - 1), tid + 256 * (s0 + b) < nch0);
+        if (T * (s0 + b) >= nch0) break;  // the same for the whole workgroup
+        bytes_into(acc0, raw[b], min(q0 + QS * (s0 + b), ng0 - 1), tid + T * (s0 + b) < nch0);
       }
     }
   };
   auto consume1 = [&](int s0, const uint4 (&raw)[NB1]) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < NB1; ++b) {
-      if (256 * (s0 + b) >= nch1) break;  // the same for the whole workgroup
-      bytes_into(acc1, raw[b], ng0 + min(q0 + QS * (s0 + b), ng1 - 1), tid + 256 * (s0 + b) < nch1);
+      if (T * (s0 + b) >= nch1) break;  // the same for the whole workgroup
+      bytes_into(acc1, raw[b], ng0 + min(q0 + QS * (s0 + b), ng1 - 1), tid + T * (s0 + b) < nch1);
     }
   };
 
@@ -3960,7 +3960,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     int4 p[FJ];
 #pragma unroll
     for (int j = 0; j < FJ; ++j) {
-      const int k4 = min(tid + 256 * j, K4 - 1);  // repeats change no max
+      const int k4 = min(tid + T * j, K4 - 1);  // repeats change no max
       const uint2 pq = reinterpret_cast<const uint2*>(a.apos16)[k4];  // half the bytes of int32
       p[j] = make_int4((int)(pq.x & 0xFFFFu), (int)(pq.x >> 16), (int)(pq.y & 0xFFFFu), (int)(pq.y >> 16));
       v[j] = reinterpret_cast<const float4*>(a.a32)[k4];
@@ -3970,7 +3970,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     issue1(0, raw1);
     uint8_t* codes = xs + a.xs_bytes;
     uint32_t* codes32 = reinterpret_cast<uint32_t*>(codes);
-    for (int i = tid; i < ap.Kp / 4; i += 256) codes32[i] = 0;
+    for (int i = tid; i < ap.Kp / 4; i += T) codes32[i] = 0;
     float mx0 = 0.0f, mx1 = 0.0f;
 #pragma unroll
     for (int j = 0; j < FJ; ++j)
@@ -3988,7 +3988,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     const QPair q = qpair(qelem(s0, ap.q[0], ap.zp[0]), qelem(s1, ap.q[1], ap.zp[1]));
 #pragma unroll
     for (int j = 0; j < FJ; ++j)
-      if (tid + 256 * j < K4) {
+      if (tid + T * j < K4) {
         const bool h[4] = {p[j].x >= kp0, p[j].y >= kp0, p[j].z >= kp0, p[j].w >= kp0};
         qstore4g(v[j], h, q, codes, p[j]);
       }
@@ -3996,7 +3996,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     bar_nofence();
     // unit u = planned positions 16u .. 16u + 15 (granule u / 4, group u % 4
     // of 16), staged as gemv_store_x stages the packed unit
-    for (int u = tid; u < 4 * ngt; u += 256) {
+    for (int u = tid; u < 4 * ngt; u += T) {
       const uint4 d = *reinterpret_cast<const uint4*>(codes + 16 * u);
       const bool g0 = u < 4 * ng0;
       const uint4 pk = pack_unit(d.x, d.y, d.z, d.w, 4);
@@ -4034,7 +4034,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     auto load_x = [&](int u0) __attribute__((always_inline)) {
 #pragma unroll
       for (int i = 0; i < gemv_xr<MT>(); ++i) {
-        const int u = u0 + i * 256 + tid;
+        const int u = u0 + i * T + tid;
         uint32_t off = (uint32_t)u * 16;
         if (!cx) {
           // unit rest = 4q + kg of row m: at rest*128 + 8m (4-bit group) or
@@ -4053,7 +4053,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
       if (cx) {
 #pragma unroll
         for (int i = 0; i < gemv_xr<MT>(); ++i) {
-          const int c = u0 + i * 256 + tid;
+          const int c = u0 + i * T + tid;
           if (c < total_x) {
             if (NIB) {
               *reinterpret_cast<uint4*>(xs + 16 * c) = xl[i];
@@ -4071,12 +4071,12 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     };
     load_x(0);
     uint4 raw0[NB0], raw1[NB1];
-    const bool more_x = total_x > 256 * gemv_xr<MT>();
+    const bool more_x = total_x > T * gemv_xr<MT>();
     if (more_x) {
       // rows too long for one round: stage them all before the chunk loads
       // (waits inside the staging loop would otherwise drain the chunks)
       store_x(0);
-      for (int u0 = 256 * gemv_xr<MT>(); u0 < total_x; u0 += 256 * gemv_xr<MT>()) {
+      for (int u0 = T * gemv_xr<MT>(); u0 < total_x; u0 += T * gemv_xr<MT>()) {
         load_x(u0);
         store_x(u0);
       }
@@ -4093,12 +4093,12 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
     consume0(0, raw0);
     if (nch1 > 0) consume1(0, raw1);
   }
-  for (int s0 = NB0; 256 * s0 < nch0; s0 += NB0) {
+  for (int s0 = NB0; T * s0 < nch0; s0 += NB0) {
     uint4 raw[NB0];
     issue0(s0, raw);
     consume0(s0, raw);
   }
-  for (int s0 = NB1; 256 * s0 < nch1; s0 += NB1) {
+  for (int s0 = NB1; T * s0 < nch1; s0 += NB1) {
     uint4 raw[NB1];
     issue1(s0, raw);
     consume1(s0, raw);
@@ -4126,7 +4126,7 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
   if (tid < kBlk * M && eci.n >= 0) {
     int s0 = 0, s1 = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
+    for (int w = 0; w < T / 64; ++w)
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
         s0 += red[w][h][er][0][em];
@@ -4147,16 +4147,19 @@ __device__ __forceinline__ void gemv4_block(const GemmArgs& a, uint8_t* xs, int 
   }
 }
 
+// T threads per block.  256 leave the most blocks per CU; few blocks of a
+// long row take 512, which need half the rounds of loads (gemv_threads).
 // Dynamic LDS: the staged row (see gemv_lds).
-__global__ __launch_bounds__(256) void k_gemv(GemmArgs a) {
+template <int T>
+__global__ __launch_bounds__(T) void k_gemv(GemmArgs a) {
   extern __shared__ __align__(16) uint8_t xs[];
-  __shared__ int red[4][4][kBlk][2][1];
+  __shared__ int red[T / 64][4][kBlk][2][1];
   const int blk = blockIdx.x;
   const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv4_block<2, true>(a, xs, blk, red);
-  else if (c == 4) gemv4_block<4, true>(a, xs, blk, red);
-  else if (c == 8) gemv4_block<8, false>(a, xs, blk, red);
-  else gemv4_block<1, false>(a, xs, blk, red);
+  if (c == 2) gemv4_block<2, true, T>(a, xs, blk, red);
+  else if (c == 4) gemv4_block<4, true, T>(a, xs, blk, red);
+  else if (c == 8) gemv4_block<8, false, T>(a, xs, blk, red);
+  else gemv4_block<1, false, T>(a, xs, blk, red);
 }
 
 // Batch of one row, quantized inside the GEMV: every workgroup computes
@@ -4164,16 +4167,16 @@ __global__ __launch_bounds__(256) void k_gemv(GemmArgs a) {
 // chunks stream in; workgroup 0 also leaves the packed row, its image and
 // the scales in the handle.  Dynamic LDS: the staged row (xs_bytes), then
 // Kp code bytes.
-template <int J>
-__global__ __launch_bounds__(256) void k_gemv_fused(GemmArgs a) {
+template <int J, int T>
+__global__ __launch_bounds__(T) void k_gemv_fused(GemmArgs a) {
   extern __shared__ __align__(16) uint8_t xs[];
-  __shared__ int red[4][4][kBlk][2][1];
+  __shared__ int red[T / 64][4][kBlk][2][1];
   const int blk = blockIdx.x;
   const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv4_block<2, true, J>(a, xs, blk, red);
-  else if (c == 4) gemv4_block<4, true, J>(a, xs, blk, red);
-  else if (c == 8) gemv4_block<8, false, J>(a, xs, blk, red);
-  else gemv4_block<1, false, J>(a, xs, blk, red);
+  if (c == 2) gemv4_block<2, true, T, J>(a, xs, blk, red);
+  else if (c == 4) gemv4_block<4, true, T, J>(a, xs, blk, red);
+  else if (c == 8) gemv4_block<8, false, T, J>(a, xs, blk, red);
+  else gemv4_block<1, false, T, J>(a, xs, blk, red);
 }
 
 // ------------------------------------------------------------- k_gemv_mm --
@@ -6098,6 +6101,16 @@ static bool gemv_nibble_plan(const ActPlan& ap) {
   return ap.c[0] == 4 && (ap.S == 1 || ap.c[1] == 8);
 }
 
+// Threads of a one-row GEMV's workgroups: 512 where the blocks are at most
+// two per CU and the row is longer than `granules` (4096 blocks' columns x
+// 11008: 7.1 against 6.4 us; 2048 x 8192, 4/8-bit weights: 7.0, 5.7; but 4096
+// x 4096: 3.7, 3.9, and 11008 x 4096: 5.7, 6.2).  With the row quantized in
+// the launch the line is lower, 32 granules: half as many values a thread
+// (4096 x 4096: 6.3 against 5.9; 11008 x 4096: 9.1, 10.5).
+static int gemv_threads(const WPlan& wp, int granules) {
+  return wp.nblk <= 512 && wp.ngt > granules ? 512 : 256;
+}
+
 // The staged row of k_gemv: Kp bytes as bytes, or 32*ng0 + 64*ng1 where
 // every weight block takes the nibble path (2- and 4-bit containers).
 static size_t gemv_lds(const ActPlan& ap, const WPlan& wp) {
@@ -6123,8 +6136,11 @@ static void launch_gemv_form(const GemmArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)a.wp.nblk), blk(256);
   if (a.ap.gsub[0] > 0)
     hipLaunchKernelGGL(k_gemv_mm<true>, grid, blk, gemv_mm_lds(a.M, a.ap), stream, a);
-  else if (a.M == 1 && gemv_lds(a.ap, a.wp) + (size_t)2048 * 8 <= 64 * 1024)
-    hipLaunchKernelGGL(k_gemv, grid, blk, gemv_lds(a.ap, a.wp), stream, a);
+  else if (a.M == 1 && gemv_lds(a.ap, a.wp) + (size_t)2048 * 8 <= 64 * 1024) {
+    const size_t lds = gemv_lds(a.ap, a.wp);
+    if (gemv_threads(a.wp, 96) == 512) hipLaunchKernelGGL(k_gemv<512>, grid, dim3(512), lds, stream, a);
+    else hipLaunchKernelGGL(k_gemv<256>, grid, blk, lds, stream, a);
+  }
   else
     hipLaunchKernelGGL(k_gemv_mm<false>, grid, blk, gemv_mm_lds(a.M, a.ap), stream, a);
 }
@@ -6154,9 +6170,11 @@ hipError_t launch_gemv_fused(const float* A, int64_t K, const uint16_t* pos16_de
   a.xs_bytes = (int)((gemv_lds(ap, wp) + 15) / 16 * 16);
   const dim3 grid((unsigned)wp.nblk);
   const size_t lds = gemv_fused_lds(ap, wp);
-  if (a.K4 <= 256) hipLaunchKernelGGL(k_gemv_fused<1>, grid, dim3(256), lds, stream, a);
-  else if (a.K4 <= 512) hipLaunchKernelGGL(k_gemv_fused<2>, grid, dim3(256), lds, stream, a);
-  else hipLaunchKernelGGL(k_gemv_fused<4>, grid, dim3(256), lds, stream, a);
+  if (a.K4 <= 256) hipLaunchKernelGGL((k_gemv_fused<1, 256>), grid, dim3(256), lds, stream, a);
+  else if (a.K4 <= 512) hipLaunchKernelGGL((k_gemv_fused<2, 256>), grid, dim3(256), lds, stream, a);
+  else if (gemv_threads(wp, 32) == 512)
+    hipLaunchKernelGGL((k_gemv_fused<2, 512>), grid, dim3(512), lds, stream, a);
+  else hipLaunchKernelGGL((k_gemv_fused<4, 256>), grid, dim3(256), lds, stream, a);
   return hipGetLastError();
 }
 
