@@ -468,7 +468,7 @@ soniq_status run_gemm(soniq_act_s& act, uint16_t* Y_dev, int64_t ldy, int32_t* a
   else if (w->act_group_bits)
     HIP_TRY(launch_mp_gemm_grouped(act.packed, act.s_a, act.ap, w->dev(), w->wp, M, w->N, Y_dev, ldy,
                                    acc_dev, st));
-  else if (w->dense && gemv_dense_fits(M, act.ap))
+  else if (w->dense && gemv_dense_takes(M, act.ap, w->wp, w->dense_bytes))
     HIP_TRY(launch_mp_gemv_dense(act.packed, act.s_a, act.ap, w->dev(), w->wp, w->dense, w->wb[0],
                                  w->nw == 2 ? w->wb[1] : w->wb[0], M, w->N, Y_dev, ldy, acc_dev, st));
   else if (gemv)

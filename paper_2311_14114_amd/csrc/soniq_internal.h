@@ -359,6 +359,7 @@ hipError_t launch_dense_pack(const uint8_t* packed, const WPlan& wp, int b_lo, i
 // The GEMV forms on the dense copy: batches of at most 8 rows (when
 // gemv_dense_fits), results as launch_mp_gemv's.
 bool gemv_dense_fits(int64_t M, const ActPlan& ap);
+bool gemv_dense_takes(int64_t M, const ActPlan& ap, const WPlan& wp, int64_t dense_bytes);
 hipError_t launch_mp_gemv_dense(const uint8_t* act_packed, const float* s_a, const ActPlan& ap,
                                 const WDev& wd, const WPlan& wp, const uint8_t* dense, int b_lo,
                                 int b_hi, int64_t M, int64_t N, uint16_t* Y, int64_t ldy,

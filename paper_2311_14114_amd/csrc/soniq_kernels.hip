@@ -6905,6 +6905,19 @@ bool gemv_dense_fits(int64_t M, const ActPlan& ap) {
   return M >= 1 && M <= 8 && lds <= 64 * 1024 && gemv_dense_xbytes64(ap) < ((int64_t)1 << 31);
 }
 
+// Whether a batch is better off on the dense copy than on the containers.
+// Plans with nibbles have k_gemv_mm: from 5 rows on it is at least level
+// whatever the dense copy saves (8 x 11008 x 4096, 3/6-bit weights: 10.4
+// against 11.4 us from HBM, 4096 x 4096 5.8 against 9.2), and with fewer rows
+// where it saves nothing, as at 2 and 4 bits (1 x 11008 x 4096: 5.2 against 6.2;
+// 4 rows 5.6 against 7.7).  With 3/6-bit weights and up to 4 rows the dense
+// copy's fewer bytes decide (1 x 11008 x 4096: 8.4 against 7.6).
+bool gemv_dense_takes(int64_t M, const ActPlan& ap, const WPlan& wp, int64_t dense_bytes) {
+  if (!gemv_dense_fits(M, ap)) return false;
+  if (!gemv_nibble_plan(ap) || !gemv_fits(M, ap, wp)) return true;
+  return M <= 4 && 20 * dense_bytes < 19 * (int64_t)wblk_off(wp, wp.nblk);
+}
+
 hipError_t launch_mp_gemv_dense(const uint8_t* act_packed, const float* s_a, const ActPlan& ap,
                                 const WDev& wd, const WPlan& wp, const uint8_t* dense, int b_lo,
                                 int b_hi, int64_t M, int64_t N, uint16_t* Y, int64_t ldy,
