@@ -4228,9 +4228,13 @@ __host__ __device__ inline int gemv_mm_chunks(int ng0, int ng1) { return (ng0 + 
 __host__ __device__ inline int gemv_mm_ld(int nch) { return (nch + 3) / 8 * 8 + 4; }
 constexpr int kMmRow = 8 * 16 + 4;  // words of one row's partial sums
 
-template <int CW, bool GB>
+// SHORT: fewer slots per round, for a K that they hold in one.
+constexpr int kMmShort0 = 3, kMmShort1 = 2;
+
+template <int CW, bool GB, bool SHORT>
 __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* red) {
-  constexpr int C0 = CW == 8 ? 4 : 7, C1 = 4;  // chunks in flight per round
+  // chunks in flight per round
+  constexpr int C0 = SHORT ? kMmShort0 : CW == 8 ? 4 : 7, C1 = SHORT ? kMmShort1 : 4;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const ActPlan& ap = a.ap;
@@ -4402,15 +4406,15 @@ __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* r
   }
 }
 
-template <bool GB>
+template <bool GB, bool SHORT>
 __global__ __launch_bounds__(256) void k_gemv_mm(GemmArgs a) {
   extern __shared__ __align__(16) int mred[];
   const int blk = blockIdx.x;
   const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv_mm_block<2, GB>(a, blk, mred);
-  else if (c == 4) gemv_mm_block<4, GB>(a, blk, mred);
-  else if (c == 8) gemv_mm_block<8, GB>(a, blk, mred);
-  else gemv_mm_block<1, GB>(a, blk, mred);
+  if (c == 2) gemv_mm_block<2, GB, SHORT>(a, blk, mred);
+  else if (c == 4) gemv_mm_block<4, GB, SHORT>(a, blk, mred);
+  else if (c == 8) gemv_mm_block<8, GB, SHORT>(a, blk, mred);
+  else gemv_mm_block<1, GB, SHORT>(a, blk, mred);
 }
 
 // ------------------------------------------------- single-pass quantize --
@@ -6132,17 +6136,31 @@ static size_t gemv_mm_lds(int64_t M, const ActPlan& ap) {
 // leave the dot products less than the MFMA form's narrower ones (4.7
 // against 5.2 us at 1 x 11008 x 4096, 3.0 against 3.3 at 1 x 4096 x 4096,
 // 5.5 against 6.4 at 1 x 4096 x 11008); k_gemv_mm otherwise.
+// Whether every chunk of a row has its slot in a wave's short round.  A slot
+// costs its two loads' issue also where it holds no granule (4 x 13029 x 1700,
+// 4/8-bit weights: 6.2 us with long rounds, 4.3 with short; 4 x 7272 x 1052, 2/8
+// bits: 4.0, 3.1), and a second short round costs more than empty slots.
+static bool gemv_mm_short(const ActPlan& ap, int ngt) {
+  const int ng0 = ap.ng[0], ng1 = ngt - ng0;
+  return (ng0 + 1) / 2 <= 4 * kMmShort0 && ng1 <= 4 * kMmShort1;
+}
+
 static void launch_gemv_form(const GemmArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)a.wp.nblk), blk(256);
-  if (a.ap.gsub[0] > 0)
-    hipLaunchKernelGGL(k_gemv_mm<true>, grid, blk, gemv_mm_lds(a.M, a.ap), stream, a);
-  else if (a.M == 1 && gemv_lds(a.ap, a.wp) + (size_t)2048 * 8 <= 64 * 1024) {
+  const size_t mm = gemv_mm_lds(a.M, a.ap);
+  const bool shrt = gemv_mm_short(a.ap, a.wp.ngt);
+  if (a.ap.gsub[0] > 0) {
+    if (shrt) hipLaunchKernelGGL((k_gemv_mm<true, true>), grid, blk, mm, stream, a);
+    else hipLaunchKernelGGL((k_gemv_mm<true, false>), grid, blk, mm, stream, a);
+  } else if (a.M == 1 && gemv_lds(a.ap, a.wp) + (size_t)2048 * 8 <= 64 * 1024) {
     const size_t lds = gemv_lds(a.ap, a.wp);
     if (gemv_threads(a.wp, 96) == 512) hipLaunchKernelGGL(k_gemv<512>, grid, dim3(512), lds, stream, a);
     else hipLaunchKernelGGL(k_gemv<256>, grid, blk, lds, stream, a);
+  } else if (shrt) {
+    hipLaunchKernelGGL((k_gemv_mm<false, true>), grid, blk, mm, stream, a);
+  } else {
+    hipLaunchKernelGGL((k_gemv_mm<false, false>), grid, blk, mm, stream, a);
   }
-  else
-    hipLaunchKernelGGL(k_gemv_mm<false>, grid, blk, gemv_mm_lds(a.M, a.ap), stream, a);
 }
 
 bool gemv_fused_fits(const float* A, int64_t K, const ActPlan& ap, const WPlan& wp) {

@@ -21,6 +21,13 @@ CASES = [  # (M, N, K, a_lo, a_hi, a_frac, w_lo, w_hi, signed, group bits)
     (4, 40, 3712, 4, 4, 1.0, 2, 4, True, 0),          # 58: the second wave's only extra granule
     (2, 40, 3840, 4, 4, 1.0, 2, 8, True, 0),          # 60: each wave has one
     (7, 40, 1100, 4, 8, 0.02, 3, 6, True, 0),         # 17 wide granules: past a round's 16
+    (4, 40, 1536, 4, 4, 1.0, 2, 4, True, 0),          # 24 narrow granules: a full short round
+    (8, 40, 1600, 4, 4, 1.0, 4, 8, True, 0),          # and 25
+    (3, 40, 560, 4, 8, 0.05, 1, 8, True, 0),          # 9 wide granules; 8 below
+    (6, 40, 530, 4, 8, 0.05, 2, 8, False, 0),
+    (5, 40, 1530, 4, 4, 1.0, 2, 8, True, 512),
+    (2, 40, 1660, 4, 4, 1.0, 4, 4, True, 512),
+    (7, 40, 530, 4, 8, 0.05, 3, 6, True, 512),
     (8, 33, 11008, 4, 8, 0.8, 2, 4, True, 0),         # three rounds
     (1, 33, 60000, 4, 8, 0.8, 4, 8, True, 0),         # a row too long to stage
     (1, 40, 700, 4, 8, 0.8, 1, 4, True, 512),
