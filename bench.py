@@ -83,17 +83,16 @@ def sign_nibbles(case) -> bool:
 
 
 def uses_gemv(case) -> bool:
-    # batches of at most 8 rows run a GEMV form (with sub-group scales the
-    # block-sum GEMV)
+    # batches of at most 8 rows run a GEMV form
     return case["M"] <= 8
 
 
 def gemv_kernel(case) -> str:
     if case.get("act_group_bits", 0):
-        return "k_gemv_g"
-    if case.get("dense"):
+        return "k_gemv_mm"
+    if case.get("dense") and case["M"] <= 4:
         return "k_gemv_dense"
-    return "k_gemv" if case["M"] == 1 else "k_gemv_mfma"
+    return "k_gemv" if case["M"] == 1 else "k_gemv_mm"
 
 
 def run_gpu(case, steps, warmup, rotate=True, graph=True, conv_input=False, f8f6f4=False,
