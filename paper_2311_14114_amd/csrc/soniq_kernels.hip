@@ -2300,6 +2300,10 @@ __device__ __forceinline__ void mma_stage(v4i (&acc)[WFM][4], uint32_t a_addr,
 // fixed for the group and a scalar stage offset advances them (per lane on
 // the mixed-width tile); chunks past the data read as zero, which also
 // zeroes the second granule of a final half stage, so its products vanish.
+// B loads per stage at the larger container CB: 128 rows of 2*CB 16-byte
+// chunks, 256 of them a load (one container of 1 bit fills half of it).
+constexpr int fast_b_loads(int CB) { return CB >= 2 ? CB / 2 : 1; }
+
 template <int CA, int CBL, int CBH, int WFM, int NST, int ASLOT, int SLOT, int GP = 0,
           class Hook = NoGranuleHook>
 __device__ __forceinline__ void gemm_group_fast(uint8_t* lds, const uint8_t* abase,
@@ -2311,9 +2315,12 @@ __device__ __forceinline__ void gemm_group_fast(uint8_t* lds, const uint8_t* aba
 #if defined(__HIP_DEVICE_COMPILE__)  // GPU builtins; the host pass never runs it
   static_assert(CA == 4 || CA == 8, "activation container");
   constexpr int BM = 32 * WFM;
-  static_assert(ASLOT >= BM * 16 * CA && SLOT - ASLOT >= 128 * 16 * CBH, "ring slot holds a stage");
-  constexpr int LA = BM * CA / 256;                      // A loads per stage
-  constexpr int LB = CBH >= 2 ? CBH / 2 : 1;             // B loads per stage
+  constexpr int LA = BM * CA / 256;  // A loads per stage
+  constexpr int LB = fast_b_loads(CBH);
+  // A load writes 16 bytes for each of the 256 lanes whatever the lane's
+  // range (zeros past a stage's chunks), so a region holds whole loads.
+  static_assert(ASLOT >= BM * 16 * CA && ASLOT >= 4096 * LA && SLOT - ASLOT >= 4096 * LB,
+                "ring slot holds a stage's loads");
   constexpr int L = LA + LB;
   constexpr bool UNI = CBL == CBH;
   const int nst = (ng + 1) >> 1;
@@ -5109,8 +5116,10 @@ void k_gemm_g(GemmArgs a) {
     // GP = 2 ends a block at its second granule, which an odd group lacks
     auto end2 = [&](v4i (&ac)[WFM][4], int q) __attribute__((always_inline)) { end(ac, GP == 2 ? q - 1 : q); };
     if constexpr (CA != 0 && CBL != 0 && CBH != 0) {
-      // slots of the group's own stage size: as many in flight as fit
-      constexpr int AB = BM * 16 * CA, SL = AB + 128 * 16 * CBL, SH = AB + 128 * 16 * CBH;
+      // slots of the group's own stage size, in whole loads: as many in
+      // flight as fit
+      constexpr int AB = BM * 16 * CA;
+      constexpr int SL = AB + 4096 * fast_b_loads(CBL), SH = AB + 4096 * fast_b_loads(CBH);
       constexpr int NL = NST * SLOT / SL < 6 ? NST * SLOT / SL : 6;
       constexpr int NH = NST * SLOT / SH < 6 ? NST * SLOT / SH : 6;
       auto run = [&](auto&& h) __attribute__((always_inline)) {

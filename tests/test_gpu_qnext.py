@@ -240,8 +240,24 @@ def test_chain_from_sub_group_scales(c):
     tiles carry the epilogue): the next layer's codes come from the fp32
     value (sum over blocks of f(ACC_j) s_a[j]) s_w, and its GEMM matches the
     oracle; Y and the producer's per-block sums match too."""
+    chain_from_blocks(c)
+
+
+@pytest.mark.parametrize("with_acc", [True, False], ids=["acc", "y"])
+@pytest.mark.parametrize("c", [
+    (37, 450, 130, 64, 512, 0, (4, 8), True),         # 5 + 3 producer granules: three and two stages
+    (150, 2300, 300, 70, 512, 512, (4, 8), True),     # 22 + 15: more stages than ring slots
+    (150, 2240, 300, 70, 1024, 0, (4, 8), False),     # 21 + 14
+], ids=lambda c: f"M{c[0]}_K{c[1]}_g{c[4]}_next{c[5]}")
+def test_chain_from_sub_group_scales_sign_weights(c, with_acc):
+    """1- and 4-bit producer weights: a stage of a sign-weight tile is
+    smaller than one load of the workgroup."""
+    chain_from_blocks(c, w1=(1, 4), with_acc=with_acc)
+
+
+def chain_from_blocks(c, w1=(2, 8), with_acc=True):
     M, K1, N1, N2, g1, g2, a2, signed2 = c
-    l1 = workloads.generic(M, N1, K1, a_lo=4, a_hi=8, a_frac_lo=0.6, w_lo=2, w_hi=8,
+    l1 = workloads.generic(M, N1, K1, a_lo=4, a_hi=8, a_frac_lo=0.6, w_lo=w1[0], w_hi=w1[1],
                            w_frac_lo=0.7, a_signed=True, seed=M + K1, name="gp1")
     l2 = workloads.generic(M, N2, N1, a_lo=a2[0], a_hi=a2[1], a_frac_lo=0.7, w_lo=2, w_hi=4,
                            w_frac_lo=0.5, a_signed=signed2, seed=M + N2, name="gp2")
@@ -272,12 +288,13 @@ def test_chain_from_sub_group_scales(c):
     h1, h2 = sq.soniq_act_create(wh1, M), sq.soniq_act_create(wh2, M)
     sq.soniq_quantize_act(h1, torch.from_numpy(l1["A"]).cuda())
     Y1 = torch.empty((M, N1), dtype=torch.bfloat16, device="cuda")
-    acc1_g = torch.empty((wh1.S, M, N1), dtype=torch.int32, device="cuda")
+    acc1_g = torch.empty((wh1.S, M, N1), dtype=torch.int32, device="cuda") if with_acc else None
     sq.soniq_mp_gemm_quantize_next(h1, wh1, h2, s2, out=Y1, acc=acc1_g)
     acc2_g = torch.empty((wh2.S, M, N2), dtype=torch.int32, device="cuda")
     Y2 = sq.soniq_mp_gemm(h2, wh2, acc=acc2_g)
     torch.cuda.synchronize()
-    np.testing.assert_array_equal(acc1_g.cpu().numpy(), acc1)
+    if with_acc:
+        np.testing.assert_array_equal(acc1_g.cpu().numpy(), acc1)
     np.testing.assert_array_equal(_bf16_bits(Y1), oracle.epilogue_replay(acc1, s_a1, s_w1))
     g_q, g_s = sq.soniq_act_unpack_debug(h2)
     np.testing.assert_array_equal(g_s, s2)

@@ -71,6 +71,12 @@ def test_conv_wave_sets(B, C, H, W, N):
     (70, 200, 1000, 0.8, 2, 8, 512, 1.0),      # 13 + 4 granules: an odd narrow group
     (40, 130, 600, 0.2, 2, 4, 512, 1.0),       # 2 + 8
     (40, 130, 64, 1.0, 1, 4, 512, 1.0),        # one granule, sign weights
+    # sign weights, whose stage is smaller than one load of the workgroup:
+    # loads past it must stay in their own ring slot
+    (37, 130, 450, 0.5, 1, 4, 512, 1.0),       # 4 + 4 granules: two stages a group
+    (150, 300, 2300, 0.6, 1, 4, 512, 1.0),     # 22 + 15: more stages than slots, an odd wide granule
+    (150, 300, 2240, 0.6, 1, 4, 1024, 1.0),    # 21 + 14: an odd narrow granule
+    (70, 300, 2300, 0.6, 1, 1, 512, 1.0),      # no compiled pair: run-time containers
     (40, 130, 3000, 0.7, 4, 8, 1024, 1.0),     # blocks of four and two granules
     (40, 130, 700, 0.7, 2, 4, 512, 2.0 ** -104),  # scales too small for the folded shift
 ], ids=lambda c: "x".join(map(str, c[:3])) + f"_w{c[4]}{c[5]}_g{c[6]}")
