@@ -1390,9 +1390,10 @@ soniq_status soniq_mp_gemm_quantize_next_max(soniq_act act, soniq_weights w, son
                             nslot, next->s_a, next->qn_img, st));
     next->ximg_ok = false;
   } else {
+    bool ximg = false;
     HIP_TRY(launch_act_bf16(Y_dev, M, w2->K, ldy, next->ap, w2->pos, w2->seg, ymax, nslot,
-                            next->s_a, next->packed, next->ximg, st));
-    next->ximg_ok = M == 1 && next->ximg != nullptr;
+                            next->s_a, next->packed, st, next->ximg, &ximg));
+    next->ximg_ok = ximg;
   }
   next->M = M;
   return SONIQ_OK;

@@ -320,7 +320,8 @@ hipError_t launch_conv_img(const float* X, int64_t B, int64_t C, int64_t H, int6
 // groups, as above) as one float pair per tile into slots; then
 // launch_act_bf16 quantizes the next layer's activations from the stored
 // bf16 Y exactly as launch_act_quant would from float(Y), with the maxima
-// of nslot pairs (nslot = 0: reduced from the batch itself).
+// of nslot pairs (nslot = 0: reduced from the batch itself); ximg (null:
+// none) and *ximg_done as launch_act_quant's.
 // (pimg, pcg: an implicit convolution's code image and geometry as the
 // producer's input.)
 hipError_t launch_mp_gemm_ymax(const uint8_t* act_packed, const float* s_a, const ActPlan& ap,
@@ -330,8 +331,8 @@ hipError_t launch_mp_gemm_ymax(const uint8_t* act_packed, const float* s_a, cons
                                const ConvGeo* pcg = nullptr);
 hipError_t launch_act_bf16(const uint16_t* Y, int64_t M, int64_t K, int64_t ldy, const ActPlan& ap,
                            const int32_t* pos_dev, const uint8_t* seg_dev, const float* slots,
-                           int nslot, float* s_a, uint8_t* packed, uint8_t* ximg,
-                           hipStream_t stream);
+                           int nslot, float* s_a, uint8_t* packed, hipStream_t stream,
+                           uint8_t* ximg, bool* ximg_done);
 // The same into a next implicit convolution (ap and conv describe it): the
 // blocked byte image bimg from Y with posn (each of the N producer
 // columns' rank-space position), then its haloed code image conv.img.

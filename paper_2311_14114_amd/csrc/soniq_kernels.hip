@@ -6061,20 +6061,23 @@ hipError_t launch_img_bf16(const uint16_t* Y, int64_t M, int N, int64_t ldy, con
 
 hipError_t launch_act_bf16(const uint16_t* Y, int64_t M, int64_t K, int64_t ldy, const ActPlan& ap,
                            const int32_t* pos_dev, const uint8_t* seg_dev, const float* slots,
-                           int nslot, float* s_a, uint8_t* packed, uint8_t* ximg,
-                           hipStream_t stream) {
+                           int nslot, float* s_a, uint8_t* packed, hipStream_t stream,
+                           uint8_t* ximg, bool* ximg_done) {
+  // the row image is written by k_act_bf16, for one row
+  uint8_t* xi = M == 1 ? ximg : nullptr;
+  *ximg_done = xi != nullptr;
   const bool aligned = K % 4 == 0 && ldy % 4 == 0 && (reinterpret_cast<uintptr_t>(Y) & 7) == 0;
   // groups of 1-bit sign codes take the per-element quantizer, as in
   // launch_act_quant
   const bool sign = ap.q[0].sign1 || (ap.S == 2 && ap.q[1].sign1);
   // the tiles' maxima are there and the rows fit: four rows per workgroup
-  if (aligned && nslot > 0 && act_blk_takes(ap))
+  // (which leaves no image)
+  if (aligned && nslot > 0 && xi == nullptr && act_blk_takes(ap))
     return launch_act_blk<true>(Y, M, K, ldy, ap, pos_dev, slots, nslot, s_a, packed, stream);
   const int64_t K4 = K / 4;
   const int J = (sign || !aligned) ? 0 : K4 <= 256 ? 1 : K4 <= 512 ? 2 : K4 <= 768 ? 3 : 4;
   // otherwise one row (small batches, whose workgroups each reduce the whole
   // batch's maxima; rows too long for four) or, per element, four
-  uint8_t* xi = M == 1 ? ximg : nullptr;
 #define SONIQ_BF16(R_, J_)                                                                          \
   hipLaunchKernelGGL((k_act_bf16<R_, J_>), dim3((unsigned)((M + R_ - 1) / R_)), dim3(256),          \
                      (size_t)R_ * ap.Kp, stream, Y, M, K, ldy, pos_dev, seg_dev, ap, slots, nslot, s_a, \

@@ -702,3 +702,48 @@ def test_conv_chain_batch_max_smaller_batch_and_graph():
         g.replay()
         torch.cuda.synchronize()
         np.testing.assert_array_equal(_bf16_bits(Y2), eager)
+
+
+@pytest.mark.parametrize("N1", [96, 70, 1100, 5000])
+def test_single_pixel_conv_into_linear(N1):
+    """An implicit convolution of one 1x1 image (one row, through the tiles)
+    into a linear layer, whose GEMV reads a contiguous image of the row: the
+    next layer's product follows the handle's last writer, in both orders of
+    the two-pass form, the static form and a plain quantization of the handle."""
+    C1, N2 = 48, 200
+    l1 = workloads.conv3x3(1, C1, 1, 1, N1, w_lo=2, w_hi=4, seed=N1, name="pixel1")
+    l2 = workloads.generic(1, N2, N1, a_lo=4, a_hi=8, a_frac_lo=0.6, w_lo=2, w_hi=4, w_frac_lo=0.5,
+                           a_signed=True, seed=N1 + 1, name="pixel2")
+    print(f"[gpu] single pixel conv N1={N1}", flush=True)
+    r1 = oracle.run(l1["A"], l1["W"], l1["a_bits"], l1["w_bits"], False)
+    y1 = oracle.epilogue_replay_f32(r1["acc"], r1["s_a"], r1["s_w"])
+    q_w2, s_w2 = oracle.quantize_weights(l2["W"], l2["w_bits"])
+    S2, _, seg_of2 = oracle.segments(l2["a_bits"])
+    q_max, s_max, _, _ = oracle.quantize_act(bf16_to_f32(r1["y_replay"]), l2["a_bits"], True)
+    q_row, s_row, _, _ = oracle.quantize_act(l2["A"], l2["a_bits"], True)
+    s_static = (s_max * np.float32(1.25)).astype(np.float32)
+    q_static = oracle.quantize_act_static(y1, l2["a_bits"], True, s_static)
+    want = {"max": (q_max, s_max), "row": (q_row, s_row), "static": (q_static, s_static)}
+    W1 = torch.from_numpy(np.ascontiguousarray(l1["W"].reshape(N1, C1, 3, 3))).cuda()
+    wh1 = sq.soniq_pack_weights_conv3x3(W1, l1["w_bits"], l1["a_bits"][::9], False)
+    wh2 = sq.soniq_pack_weights(torch.from_numpy(l2["W"]).cuda(), l2["w_bits"], l2["a_bits"], True)
+    act1, act2 = sq.soniq_act_create_conv3x3(wh1, 1, 1, 1), sq.soniq_act_create(wh2, 1)
+    sq.soniq_quantize_act_conv3x3(act1, torch.from_numpy(l1["X"]).cuda())
+    A2 = torch.from_numpy(l2["A"]).cuda()
+    for writer in ("max", "row", "max", "static", "max", "row", "static"):
+        if writer == "max":
+            sq.soniq_mp_gemm_quantize_next_max(act1, wh1, act2)
+        elif writer == "static":
+            sq.soniq_mp_gemm_quantize_next(act1, wh1, act2, s_static)
+        else:
+            sq.soniq_quantize_act(act2, A2)
+        acc = torch.empty((S2, 1, N2), dtype=torch.int32, device="cuda")
+        Y2 = sq.soniq_mp_gemm(act2, wh2, acc=acc)
+        torch.cuda.synchronize()
+        q, s = want[writer]
+        g_q, g_s = sq.soniq_act_unpack_debug(act2)
+        np.testing.assert_array_equal(g_s, s[:S2])
+        np.testing.assert_array_equal(g_q, q)
+        racc = oracle.mac(q, q_w2, seg_of2, S2)
+        np.testing.assert_array_equal(acc.cpu().numpy(), racc)
+        np.testing.assert_array_equal(_bf16_bits(Y2), oracle.epilogue_replay(racc, s[:S2], s_w2))
