@@ -4430,10 +4430,15 @@ __global__ __launch_bounds__(256) void k_gemv_mm(GemmArgs a) {
 // the choice wasting the fewest register slots), T float4 per thread, and
 // at most as many workgroups as can be resident at once (by the occupancy
 // of k_act_coop<T> with this LDS size, times the CU count).
-// SONIQ_ACT_COOP=0 turns the path off for measurement; results do not
-// depend on it.
+// SONIQ_ACT_COOP overrides the choice (0: never; 1: also for the smaller
+// batches without sub-group scales); results do not depend on it.
 constexpr int64_t kCoopMinElems = (int64_t)1 << 20;
 constexpr int64_t kCoopFromElems = (int64_t)8 << 20;  // without sub-group scales
+
+int act_coop_env() {  // -1: not set
+  const char* env = getenv("SONIQ_ACT_COOP");
+  return env ? atoi(env) : -1;
+}
 
 template <int T, int TL, bool GRP>
 int coop_capacity(size_t lds) {
@@ -4482,8 +4487,7 @@ bool coop_launch(const float* A, int64_t M, int64_t K, int64_t lda, int RB, cons
 bool launch_act_coop(const float* A, int64_t M, int64_t K, int64_t lda, const ActPlan& ap,
                      const int32_t* pos_dev, unsigned* bar, float* s_a,
                      uint8_t* packed, hipStream_t stream, hipError_t& e, bool grp = false) {
-  if (const char* env = getenv("SONIQ_ACT_COOP"))
-    if (atoi(env) == 0) return false;
+  if (act_coop_env() == 0) return false;
   const int64_t K4 = (K + 3) / 4;
   // direct global -> LDS row slots (T = 9) take 16-byte aligned rows
   const bool aligned = K % 4 == 0 && lda % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
@@ -5635,9 +5639,8 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
   // (about 5 us); two passes read them twice, the second time from the L2s
   // (32 MB).  Single against two passes, us: 10.9, 10.3 at 4096 x 768,
   // 13.3, 9.8 at 301 x 4091, 8.9, 6.9 at 1024 x 1024; 21.4, 21.6 at 4096 x
-  // 3072, 24.6, 25.0 at 6272 x 2304.  SONIQ_COOP_SPINS (the single pass's
-  // spin limit) asks for it from kCoopMinElems on.
-  const int64_t coop_min = getenv("SONIQ_COOP_SPINS") ? kCoopMinElems : kCoopFromElems;
+  // 3072, 24.6, 25.0 at 6272 x 2304.
+  const int64_t coop_min = act_coop_env() == 1 ? kCoopMinElems : kCoopFromElems;
   if (vec && !sign && M * K >= coop_min) {
     hipError_t e = hipSuccess;
     if (launch_act_coop(A, M, K, lda, ap, pos4_dev, counter, s_a, packed, stream, e))

@@ -361,35 +361,41 @@ def test_api_errors_on_device():
 
 
 # Batches of at least 2^20 elements that fit the registers of one resident
-# grid are quantized in one pass (rows per workgroup RB and float4 per
-# thread T chosen from K); each case below lands on a different (RB, T),
-# with a ragged last workgroup.  Both the single pass and the two-pass
-# path (SONIQ_ACT_COOP=0) must match the oracle.
-COOP = [  # (M, K, a_lo, a_hi, a_signed)      RB, T
+# grid can be quantized in one pass (rows per workgroup RB and float4 per
+# thread T chosen from K), which SONIQ_ACT_COOP=1 asks for at these sizes;
+# each case below lands on a different (RB, T) or row alignment, with a
+# ragged last workgroup.  Both the single pass and the two-pass path
+# (SONIQ_ACT_COOP=0) must match the oracle.
+COOP = [  # (M, K, a_lo, a_hi, a_signed[, lda pad])  RB, T
     (8200, 128, 4, 8, True),                # 16, 6 (K4 = 32: 8 rows per 256-step)
-    (1400, 768, 4, 8, False),               # 16, 12
+    (1400, 768, 4, 8, False),               # 8, 6
     (343, 3072, 2, 4, True),                # 4, 12 (2-bit pieces of 4 rows)
-    (460, 2304, 4, 8, False),               # 8, 18 (the conv row length)
-    (1100, 1000, 4, 8, True),               # 4, 6 (K4 = 250 < 256)
+    (460, 2304, 4, 8, False),               # 4, 9 (the conv row length)
+    (1100, 1000, 4, 8, True),               # 8, 9 (K4 = 250 < 256)
     (4100, 260, 2, 8, False),               # 16, 6 (K4 = 65: three rows per step)
+    (250, 4400, 4, 8, True),                # 4, 18
+    (1101, 999, 3, 6, False),               # 4, 6, rows of no alignment, ending inside a piece
+    (361, 3071, 4, 8, True, 2),             # 4, 12, the same
+    (950, 1150, 2, 8, True, 1),             # 16, 18, the same
+    (1400, 768, 4, 8, True, 1),             # 8, 6, whole pieces at 4-byte alignment
 ]
 
 
 @pytest.mark.parametrize("coop", [True, False], ids=["single_pass", "two_pass"])
 @pytest.mark.parametrize("shape", COOP, ids=lambda s: f"{s[0]}x{s[1]}_a{s[2]}{s[3]}{'s' if s[4] else 'u'}")
 def test_single_pass_quantize(shape, coop, monkeypatch):
-    M, K, alo, ahi, sgn = shape
-    if not coop:
-        monkeypatch.setenv("SONIQ_ACT_COOP", "0")
+    M, K, alo, ahi, sgn, *pad = shape
+    monkeypatch.setenv("SONIQ_ACT_COOP", "1" if coop else "0")
     case = workloads.generic(M, 64, K, a_lo=alo, a_hi=ahi, a_frac_lo=0.6, w_lo=2, w_hi=4,
                              w_frac_lo=0.5, a_signed=sgn, a_abs=not sgn, seed=M + K,
                              name="coop")
-    compare_full(gpu_run(case), oracle_run(case))
+    compare_full(gpu_run(case, lda_pad=sum(pad)), oracle_run(case))
 
 
-def test_single_pass_repeat_calls():
+def test_single_pass_repeat_calls(monkeypatch):
     """The grid barrier's counters reset themselves: repeated calls, a
     smaller grid after a larger one and new data all stay bit-exact."""
+    monkeypatch.setenv("SONIQ_ACT_COOP", "1")
     big = workloads.generic(1400, 64, 768, a_lo=4, a_hi=8, a_frac_lo=0.5, w_lo=2, w_hi=4,
                             w_frac_lo=0.5, seed=21, name="coop-repeat")
     W = torch.from_numpy(big["W"]).cuda()
@@ -409,22 +415,31 @@ def test_single_pass_repeat_calls():
     assert sq.soniq_act_wait_timeouts(act) == 0  # the grid was resident every time
 
 
-@pytest.mark.parametrize("M,K", [(1400, 768), (460, 2304)])
-def test_single_pass_wait_timeout(M, K, monkeypatch):
+@pytest.mark.parametrize("shape", COOP, ids=lambda s: f"{s[0]}x{s[1]}_a{s[2]}{s[3]}{'s' if s[4] else 'u'}")
+def test_single_pass_wait_timeout(shape, monkeypatch):
     """With a spin limit of zero every workgroup but the grid's last arrival
     gives up waiting and takes the maxima from the whole batch itself; the
-    codes, scales and outputs are the same, and the next call (normal
-    limit) finds the grid state clean."""
-    case = workloads.generic(M, 64, K, a_lo=4, a_hi=8, a_frac_lo=0.6, w_lo=2, w_hi=4,
-                             w_frac_lo=0.5, a_signed=False, a_abs=True, seed=M * 3 + K,
+    codes, scales and outputs are the same, and the next call on the handle
+    (normal limit) finds the grid state clean.  The counts also show that
+    every shape takes the single pass."""
+    M, K, alo, ahi, sgn, *pad = shape
+    case = workloads.generic(M, 64, K, a_lo=alo, a_hi=ahi, a_frac_lo=0.6, w_lo=2, w_hi=4,
+                             w_frac_lo=0.5, a_signed=sgn, a_abs=not sgn, seed=M * 3 + K,
                              name="coop-timeout")
     ref = oracle_run(case)
+    monkeypatch.setenv("SONIQ_ACT_COOP", "1")
     monkeypatch.setenv("SONIQ_COOP_SPINS", "0")
-    g = gpu_run(case)
+    g = gpu_run(case, lda_pad=sum(pad))
     compare_full(g, ref)
     # the workgroup that arrived first polled before the last arrival
-    assert sq.soniq_act_wait_timeouts(g["act"]) >= 1
+    stalls = sq.soniq_act_wait_timeouts(g["act"])
+    assert stalls >= 1
     monkeypatch.delenv("SONIQ_COOP_SPINS")
-    g = gpu_run(case)
-    compare_full(g, ref)
-    assert sq.soniq_act_wait_timeouts(g["act"]) == 0
+    A = torch.zeros((M, K + sum(pad)), dtype=torch.float32, device="cuda")[:, :K]
+    A.copy_(torch.from_numpy(case["A"]) * 2)
+    sq.soniq_quantize_act(g["act"], A)
+    torch.cuda.synchronize()
+    q_a, s_a = sq.soniq_act_unpack_debug(g["act"])
+    np.testing.assert_array_equal(s_a, ref["s_a"] * 2)
+    np.testing.assert_array_equal(q_a, ref["q_a"])
+    assert sq.soniq_act_wait_timeouts(g["act"]) == stalls
