@@ -2823,24 +2823,25 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
   // this thread's output pixel (rows past M repeat the last one; their
   // sums are never stored) and its haloed center
   const int mb = (tid >> 4) & 3, r = tid & 15, kg = wid & 3;
-  const int64_t P = min(m0 + 16 * mb + r, M - 1);
-  const int HW = H * W;
-  const int b = (int)(P / HW), rem0 = (int)(P - (int64_t)b * HW);
+  // (pixels of an image fit 31 bits)
+  const uint32_t P = (uint32_t)min(m0 + 16 * mb + r, M - 1), HW = (uint32_t)(H * W);
+  const int b = (int)(P / HW), rem0 = (int)(P - (uint32_t)b * HW);
   const int y = rem0 / W, x = rem0 - y * W;
   const int Wp = W + 2;
   const int hp0 = (b * (H + 2) + y + 1) * Wp + x + 1;
   // This wave's units: 16-channel group kg of granules ks, ks + KS, ...  The
-  // tap and unit of a wave are scalars stepped from granule to granule (a
-  // division per unit cost as much as the widening of its operands).
+  // tap and unit of a wave are scalars, the tap by one multiplication with
+  // ceil(2^32 / cu) (exact: unit index times units of a tap < 2^32; a
+  // division per unit cost as much as the widening of its operands, and a
+  // loop that steps through taps of one unit, four a granule, 1.0 us of 23.7
+  // at 1568 tiles of K = 144).
   constexpr int QA = GPS / KS;
-  const int cu = cpad >> 4, kend = 9 * cu;  // units of a tap, of the group
-  int ku = __builtin_amdgcn_readfirstlane(4 * ks + kg);  // unit index
-  int tap = __builtin_amdgcn_readfirstlane(ku / cu);
-  int c16 = ku - tap * cu;
-  // addressed from the haloed pixel up and left of the tile's first one
-  // (haloed indices grow with the pixel, so no offset is negative)
-  const int bt = (int)(m0 / HW), remt = (int)(m0 - (int64_t)bt * HW);
-  const int hpt = __builtin_amdgcn_readfirstlane((bt * (H + 2) + remt / W + 1) * Wp + remt % W + 1);
+  const uint32_t cu = (uint32_t)(cpad >> 4), kend = 9 * cu;  // units of a tap, of the group
+  const uint32_t inv = __builtin_amdgcn_readfirstlane((int)(0xFFFFFFFFu / cu + 1u));  // 0: cu = 1
+  uint32_t ku = (uint32_t)__builtin_amdgcn_readfirstlane(4 * ks + kg);  // unit index
+  // addressed from the haloed pixel up and left of the tile's first one,
+  // lane 0's (haloed indices grow with the pixel, so no offset is negative)
+  const int hpt = __builtin_amdgcn_readfirstlane(hp0);
   const __amdgpu_buffer_rsrc_t ir = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(img + (int64_t)(hpt - Wp - 1) * rowbytes), (short)0, (int)kOOB, 0x00020000);
   const uint32_t ao = (uint32_t)((hp0 - hpt) * rowbytes);
@@ -2848,6 +2849,8 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
   auto load_a = [&](raw_t<CA> (&dst)[QA]) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < QA; ++q) {
+      const int tap = (int)(inv == 0u ? ku : __umulhi(ku, inv));
+      const uint32_t c16 = ku - (uint32_t)tap * cu;
       const int tr = tap >= 6 ? 2 : tap >= 3 ? 1 : 0;
       const int dp = (tr - 1) * Wp + (tap - 3 * tr - 1);
       // units past the group's end read as zeros; a load either way, so that
@@ -2859,11 +2862,6 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
       else
         dst[q] = __builtin_bit_cast(u32x2v, __builtin_amdgcn_raw_buffer_load_b64(ir, vo, in ? so : 0u, 0));
       ku += 4 * KS;
-      c16 += 4 * KS;
-      while (c16 >= cu) {
-        c16 -= cu;
-        ++tap;
-      }
     }
   };
   const int aw = (mb * GPS + ks) * 128 * CA + (kg * 16 + r) * 2 * CA;
@@ -2876,34 +2874,52 @@ __device__ __forceinline__ void gemm_group_conv(uint8_t* lds, const uint8_t* img
   const uint32_t b_lds = lds_off(lds) + (uint32_t)(ABYTES + wn * 4 * GPS * 128 * CB + ks * 128 * CB + lane * 2 * CB);
   const uint32_t a_lds = lds_off(lds) + (uint32_t)(wm * WFM * GPS * 128 * CA + ks * 128 * CA + lane * 2 * CA);
 
-  // Stages past the last are issued and read as zeros (the weights' chunks
-  // are out of range, the units past the group's end), so the waits count
-  // the same loads in every iteration.
+  // Iteration st: its weights have landed (at most the later stages' loads
+  // are in flight) and every wave's units are in LDS; stage st + D is
+  // requested into the slot that stage st - 1 has left, and the units of
+  // stage st + 1 go to LDS while this stage's products run.  With several
+  // stages in flight, those past the last are issued and read as zeros (the
+  // weights' chunks are out of range, the units past the group's end), so
+  // that the waits count the same loads in every iteration.
 #pragma unroll
   for (int s = 0; s < D; ++s) {
     issue_b(s, s);
     load_a(ua[s]);
   }
   write_a(0, ua[0]);
-  // Iteration st: its weights have landed (at most the later stages' loads
-  // are in flight) and every wave's units are in LDS; stage st + D is
-  // requested into the slot that stage st - 1 has left, and the units of
-  // stage st + 1 go to LDS while this stage's products run.
-  auto stage = [&](int st, raw_t<CA> (&next)[QA], raw_t<CA> (&refill)[QA]) __attribute__((always_inline)) {
+  auto begin = [&](int st, raw_t<CA> (&refill)[QA]) __attribute__((always_inline)) {
     wait_vm<(LB + QA) * (D - 1)>();
     __builtin_amdgcn_s_waitcnt(SONIQ_LGKMCNT0_IMM);
     bar_nofence();
-    issue_b(st + D, (st + D) % NST);
-    load_a(refill);
-    const uint32_t soff = (uint32_t)((st % NST) * SLOT);
+    if (D > 1 || st + D < nst) {
+      issue_b(st + D, (st + D) % NST);
+      load_a(refill);
+    }
+    return (uint32_t)((st % NST) * SLOT);
+  };
+  auto full = [&](int st, raw_t<CA> (&next)[QA], raw_t<CA> (&refill)[QA]) __attribute__((always_inline)) {
+    const uint32_t soff = begin(st, refill);
     wide_stage<CA, CB, WFM, GPS, GPS / KS, KS>(acc, a_lds + soff, b_lds + soff);
-    write_a((st + 1) % NST, next);
+    if (D > 1 || st + 1 < nst) write_a((st + 1) % NST, next);
     asm volatile("" ::: "memory");  // a stage's loads stay between its barriers
   };
-  for (int st0 = 0; st0 < nst; st0 += D) {
+  if constexpr (D == 1) {
+    // one stage ahead: the last stage multiplies the granules it has, and
+    // nothing is requested past it (1568 tiles of K = 144: 28.2 us with a
+    // full last stage and one past it, 24.5 so)
+    const int nfull = ng / GPS;
+    for (int st = 0; st < nfull; ++st) full(st, ua[0], ua[0]);
+    if (nfull < nst) {
+      const uint32_t soff = begin(nfull, ua[0]);
+      wide_stage_rem<CA, CB, WFM, GPS, KS == 1 ? GPS - 1 : GPS / KS, KS>(
+          acc, a_lds + soff, b_lds + soff, (ng - nfull * GPS - ks + KS - 1) / KS);
+    }
+  } else {
+    for (int st0 = 0; st0 < nst; st0 += D) {
 #pragma unroll
-    for (int k = 0; k < D; ++k)
-      if (st0 + k < nst) stage(st0 + k, ua[(k + 1) % D], ua[k]);
+      for (int k = 0; k < D; ++k)
+        if (st0 + k < nst) full(st0 + k, ua[(k + 1) % D], ua[k]);
+    }
   }
   // the loads issued past the last stage have landed before the ring and
   // their registers are used again
@@ -6445,9 +6461,12 @@ hipError_t launch_conv_img(const float* X, int64_t B, int64_t C, int64_t H, int6
 
 template <int CBL, int CBH>
 static void launch_gemm_conv_t(const GemmArgs& a, int64_t M, hipStream_t stream) {
-  // two wave sets where the tiles leave a wave its SIMD to itself, as gemm_shape
+  // two wave sets where the tiles leave a wave its SIMD to itself, as
+  // gemm_shape, and K is long enough to share: two sets against one, us: 8.6,
+  // 8.3 at 8 granules, 9.4, 9.0 at 12 (196 tiles); 10.2, 10.9 at 16, 15.3,
+  // 17.6 at 37
   const dim3 grid((unsigned)(((M + 63) / 64) * (a.wp.Np / kGemmBN)));
-  if (grid.x <= 256)
+  if (grid.x <= 256 && a.wp.ngt > 12)
     hipLaunchKernelGGL((k_gemm<2, 4, 8, CBL, CBH, 2, gemm_conv_nst(CBH), 0, false, true, 2>), grid,
                        dim3(512), 0, stream, a);
   else

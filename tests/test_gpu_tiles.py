@@ -47,10 +47,12 @@ def test_tile_shapes(c, shape, monkeypatch):
 
 
 @pytest.mark.parametrize("B,C,H,W,N", [(1, 16, 7, 9, 40), (2, 48, 8, 8, 130), (3, 112, 14, 14, 96),
-                                       (32, 64, 24, 24, 128), (33, 32, 24, 24, 128)])
+                                       (32, 64, 24, 24, 128), (33, 32, 24, 24, 128), (20, 16, 32, 32, 64),
+                                       (2, 64, 20, 20, 70), (2, 96, 20, 20, 70)])
 def test_conv_wave_sets(B, C, H, W, N):
-    """The implicit convolution below and above one tile per CU, with taps
-    of one to seven 16-channel units (a granule spans up to four taps)."""
+    """The implicit convolution below and above one tile per CU and the K
+    that two wave sets share, with taps of one to seven 16-channel units (a
+    granule spans up to four taps)."""
     case = workloads.conv3x3(B, C, H, W, N, seed=B * C + H, name="conv_sets")
     print(f"[gpu] conv wave sets {B}x{C}x{H}x{W} -> {N}", flush=True)
     Wt = torch.from_numpy(case["W"]).reshape(N, C, 3, 3).contiguous().cuda()
