@@ -4456,6 +4456,15 @@ int act_coop_env() {  // -1: not set
   return env ? atoi(env) : -1;
 }
 
+// Workgroups of four waves that a CU runs at once, at most: the occupancy
+// query grants eight to a kernel of 54 vector and 89 scalar registers, but a
+// CU starts seven (1792 of 1875 workgroups met at the barrier; scalar
+// registers are not in that query, and a wave's share of them allows no
+// eighth).  A larger grid waits for workgroups that start only when others
+// end, gives up after the spin limit and takes the maxima of the whole batch
+// in every workgroup: about 0.4 s a call instead of 30 us.
+constexpr int kCoopPerCu = 7;
+
 template <int T, int TL, bool GRP>
 int coop_capacity(size_t lds) {
   // resident workgroups per CU for this T and LDS size, cached per device
@@ -4474,7 +4483,7 @@ int coop_capacity(size_t lds) {
       return 0;
     cache.dev = dev;
     cache.lds = lds;
-    cache.per_cu = per_cu;
+    cache.per_cu = std::min(per_cu, kCoopPerCu);
     cache.cus = cus;
   }
   return cache.per_cu * cache.cus;

@@ -443,3 +443,31 @@ def test_single_pass_wait_timeout(shape, monkeypatch):
     np.testing.assert_array_equal(s_a, ref["s_a"] * 2)
     np.testing.assert_array_equal(q_a, ref["q_a"])
     assert sq.soniq_act_wait_timeouts(g["act"]) == stalls
+
+
+@pytest.mark.parametrize("M,gbits", [(28672, 0), (28688, 0), (32768, 512)])
+def test_single_pass_grid_is_resident(M, gbits, monkeypatch):
+    """Batches at and past the largest grid that a chip of 256 CUs runs at
+    once (7 workgroups of 16 rows a CU): no workgroup waits for one that has
+    not started.  The short spin limit bounds a wait that would fail."""
+    monkeypatch.setenv("SONIQ_ACT_COOP", "1")
+    monkeypatch.setenv("SONIQ_COOP_SPINS", "4000")
+    print(f"[gpu] single pass grid M={M} g={gbits}", flush=True)
+    rng = np.random.default_rng(M)
+    A_np = rng.standard_normal((M, 128)).astype(np.float32)
+    a_bits = np.where(rng.random(128) < 0.7, 4, 8).astype(np.uint8)
+    W = torch.from_numpy(rng.standard_normal((16, 128)).astype(np.float32)).cuda()
+    w = sq.soniq_pack_weights(W, np.full(16, 4, np.uint8), a_bits, True, act_group_bits=gbits)
+    act = sq.soniq_act_create(w, M)
+    A = torch.from_numpy(A_np).cuda()
+    for _ in range(2):
+        sq.soniq_quantize_act(act, A)
+    torch.cuda.synchronize()
+    q_a, s_a = sq.soniq_act_unpack_debug(act)
+    if gbits:
+        rq, rs, _, _ = oracle.quantize_act_grouped(A_np, a_bits, True, gbits)
+    else:
+        rq, rs, _, _ = oracle.quantize_act(A_np, a_bits, True)
+    np.testing.assert_array_equal(s_a, rs[:w.S])
+    np.testing.assert_array_equal(q_a, rq)
+    assert sq.soniq_act_wait_timeouts(act) == 0
