@@ -445,18 +445,18 @@ def test_single_pass_wait_timeout(shape, monkeypatch):
     assert sq.soniq_act_wait_timeouts(g["act"]) == stalls
 
 
-@pytest.mark.parametrize("M,gbits", [(28672, 0), (28688, 0), (32768, 512)])
-def test_single_pass_grid_is_resident(M, gbits, monkeypatch):
+@pytest.mark.parametrize("M,K,gbits", [(28672, 128, 0), (28688, 128, 0), (32768, 128, 512), (8192, 1088, 0)])
+def test_single_pass_grid_is_resident(M, K, gbits, monkeypatch):
     """Batches at and past the largest grid that a chip of 256 CUs runs at
-    once (7 workgroups of 16 rows a CU): no workgroup waits for one that has
+    once (7 workgroups of 16 or 4 rows a CU): no workgroup waits for one that has
     not started.  The short spin limit bounds a wait that would fail."""
     monkeypatch.setenv("SONIQ_ACT_COOP", "1")
     monkeypatch.setenv("SONIQ_COOP_SPINS", "4000")
-    print(f"[gpu] single pass grid M={M} g={gbits}", flush=True)
+    print(f"[gpu] single pass grid M={M} K={K} g={gbits}", flush=True)
     rng = np.random.default_rng(M)
-    A_np = rng.standard_normal((M, 128)).astype(np.float32)
-    a_bits = np.where(rng.random(128) < 0.7, 4, 8).astype(np.uint8)
-    W = torch.from_numpy(rng.standard_normal((16, 128)).astype(np.float32)).cuda()
+    A_np = rng.standard_normal((M, K)).astype(np.float32)
+    a_bits = np.where(rng.random(K) < 0.7, 4, 8).astype(np.uint8)
+    W = torch.from_numpy(rng.standard_normal((16, K)).astype(np.float32)).cuda()
     w = sq.soniq_pack_weights(W, np.full(16, 4, np.uint8), a_bits, True, act_group_bits=gbits)
     act = sq.soniq_act_create(w, M)
     A = torch.from_numpy(A_np).cuda()
