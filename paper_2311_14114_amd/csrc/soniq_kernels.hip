@@ -310,8 +310,24 @@ __device__ __forceinline__ void write_partial(float mx0, float mx1, float* red,
   }
 }
 
-// Rows of K >= 4 values at any stride.  Workgroup b takes RB consecutive
-// rows; thread tid owns float4 positions k4 = base + 256*j
+// First row of this workgroup's RB (2, 4, 8 or 16) where the passes over a
+// batch go by 16-row blocks: block b's workgroups all run on XCD b mod 8
+// (workgroup i goes to XCD i mod 8), so the second pass finds the rows the
+// first one read in its XCD's L2, and the pieces of one packed line meet
+// there.  Without that match the second pass re-read rows through the
+// Infinity Cache: 14.1 against 10.6 us at 4096 x 1536, 9.3 against 8.7 at
+// 4096 x 768 (both passes).  The grid is a multiple of 128 rows; workgroups
+// past the batch get rows past it.
+template <int RB>
+__device__ __forceinline__ int64_t xcd_row0() {
+  constexpr int PB = kBlk / RB;  // workgroups per block
+  const int64_t x = blockIdx.x & 7, jb = blockIdx.x >> 3;
+  return RB * (PB * ((jb / PB) * 8 + x) + jb % PB);
+}
+inline unsigned xcd_grid(int64_t M, int RB) { return (unsigned)((M + 127) / 128 * (128 / RB)); }
+
+// Rows of K >= 4 values at any stride.  Each workgroup takes RB consecutive
+// rows (xcd_row0); thread tid owns float4 positions k4 = base + 256*j
 // of every row, loads all RB rows of them at once, keeps their |max| over
 // the rows (one v_max per element) and folds them into the two group
 // maxima once per position batch.  Clamped rows and positions re-read
@@ -323,9 +339,9 @@ __global__ __launch_bounds__(256) void k_absmax_blk(const float* __restrict__ A,
                                                     float* __restrict__ partial) {
   __shared__ float red[8];
   const int tid = threadIdx.x;
-  const int64_t m0 = (int64_t)blockIdx.x * RB;
+  const int64_t m0 = xcd_row0<RB>();
   const int rows = (int)min((int64_t)RB, M - m0);
-  const int K4 = (K + 3) / 4;
+  const int K4 = rows > 0 ? (K + 3) / 4 : 0;
   float mx0 = 0.0f, mx1 = 0.0f;
   for (int base = 0; base < K4; base += 256 * J) {
     int k4[J];
@@ -614,15 +630,7 @@ __global__ __launch_bounds__(256) void k_act_rows(const float* __restrict__ A, i
                                                   uint8_t* __restrict__ ximg) {
   extern __shared__ __align__(16) uint8_t codes[];
   __shared__ float red[8];
-  // R = 4: the four workgroups of one 16-row block run on one XCD
-  // (workgroup i goes to XCD i mod 8), so its L2 joins their partial unit
-  // lines before they reach HBM; the grid is a multiple of 32 workgroups
-  int64_t wg = blockIdx.x;
-  if constexpr (R == 4) {
-    const int64_t x = wg & 7, j = wg >> 3;
-    wg = 4 * ((j >> 2) * 8 + x) + (j & 3);
-  }
-  const int64_t m0 = wg * R;
+  const int64_t m0 = R == 4 ? xcd_row0<R == 4 ? R : 4>() : (int64_t)blockIdx.x * R;
   if (m0 >= M) return;
   const int rows = (int)min((int64_t)R, M - m0);
   const int tid = threadIdx.x;
@@ -1580,8 +1588,8 @@ void k_act_coop(const float* __restrict__ A, int64_t M, int K, int64_t lda, int 
 // many rows are in flight.  Four rows, against 8 and 16: 6.6, 7.0, 8.9 us at
 // 4096 x 768, 12.4, 13.7, 18.3 at 4096 x 3072, 7.2, 10.7 at 301 x 4091 (an
 // empty launch 1.8): fewer rows give more workgroups and more of them per
-// CU, and the four workgroups of a block run on one XCD (workgroup i goes
-// to XCD i mod 8), whose L2 joins their pieces of the same lines.  J: one
+// CU.  The first pass read a block's rows on the XCD that they come from
+// here (xcd_row0).  J: one
 // float4 a row and thread keeps the registers low (2304 values: 14.4 us
 // against 18.1 with two); rows past 4096 values take four (8192 x 8192: 64
 // against 74).  Dynamic LDS: 4*Kp bytes.
@@ -1594,8 +1602,7 @@ __global__ __launch_bounds__(256) void k_act_blk(const void* __restrict__ src, i
   constexpr int RB = 4;
   extern __shared__ __align__(16) uint8_t codes[];
   __shared__ float red[8];
-  const int64_t x = blockIdx.x & 7, jb = blockIdx.x >> 3;
-  const int64_t m0 = RB * (4 * ((jb >> 2) * 8 + x) + (jb & 3));
+  const int64_t m0 = xcd_row0<RB>();
   if (m0 >= M) return;
   const int rows = (int)min((int64_t)RB, M - m0);
   const int tid = threadIdx.x, K4 = (K + 3) / 4, kp0 = ap.kpad[0];
@@ -1687,7 +1694,7 @@ template <bool BF>
 hipError_t launch_act_blk(const void* src, int64_t M, int64_t K, int64_t lda, const ActPlan& ap,
                           const int32_t* pos4, const float* partial, int nparts, float* s_a,
                           uint8_t* packed, hipStream_t stream) {
-  const dim3 grid((unsigned)((M + 127) / 128 * 32));
+  const dim3 grid(xcd_grid(M, 4));
   const size_t lds = 4 * (size_t)ap.Kp;
   const int4* p4 = reinterpret_cast<const int4*>(pos4);
   if (K <= 4096)
@@ -4441,19 +4448,37 @@ __global__ __launch_bounds__(256) void k_gemv_mm(GemmArgs a) {
 }
 
 // ------------------------------------------------- single-pass quantize --
-// Batches of at least kCoopMinElems elements whose rows fit the registers
-// of one resident grid take k_act_coop: RB rows per workgroup (4, 8 or 16,
+// Batches of at least kCoopMinElems elements (without sub-group scales, of
+// coop_from's) whose rows fit the registers of one resident grid take
+// k_act_coop: RB rows per workgroup (4, 8 or 16,
 // the choice wasting the fewest register slots), T float4 per thread, and
 // at most as many workgroups as can be resident at once (by the occupancy
 // of k_act_coop<T> with this LDS size, times the CU count).
 // SONIQ_ACT_COOP overrides the choice (0: never; 1: also for the smaller
 // batches without sub-group scales); results do not depend on it.
 constexpr int64_t kCoopMinElems = (int64_t)1 << 20;
-constexpr int64_t kCoopFromElems = (int64_t)8 << 20;  // without sub-group scales
 
 int act_coop_env() {  // -1: not set
   const char* env = getenv("SONIQ_ACT_COOP");
   return env ? atoi(env) : -1;
+}
+
+// Elements from which a batch without sub-group scales takes the single
+// pass.  It reads the rows once but waits for its grid to meet (about 5 us);
+// the two passes read them twice, the second time from the L2s (32 MB).
+// Quantize + GEMM with the single pass against the two, us: 31.1, 30.2 at
+// 4096 x 768 (N = 2304), 23.1, 22.4 at 6144 x 768, 33.1, 30.0 at 4096 x
+// 2048, 37.8, 36.1 at 7168 x 1536, 40.0, 36.9 at 2048 x 4096; 41.5, 40.6 at
+// 4096 x 3072, 39.8, 39.9 at 6272 x 2304.  Past 7168 rows the second pass
+// has more four-row workgroups than the chip runs at once (7 a CU), each
+// with the partial maxima to reduce before its rows, which weighs most on
+// short ones: 20.8, 22.7 at 8192 x 256, 23.7, 24.8 at 8192 x 512, 33.3,
+// 37.1 at 16384 x 384; 25.2, 25.5 at 8192 x 640, 35.7, 34.7 at 12288 x 640;
+// 30.8, 30.4 at 8192 x 1024, 33.3, 35.6 at 8192 x 1280, 36.2, 39.9 at 16000 x 530.
+int64_t coop_from(int64_t M, int64_t K) {
+  if (act_coop_env() == 1) return kCoopMinElems;
+  if (M <= 7168) return (int64_t)12 << 20;
+  return K <= 512 ? kCoopMinElems : (int64_t)8 << 20;
 }
 
 // Workgroups of four waves that a CU runs at once, at most: the occupancy
@@ -5660,25 +5685,21 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
     if (ximg_done) *ximg_done = ximg != nullptr;
     return launch_act_batch<false>(A, M, K, lda, ap, pos4_dev, s_a, packed, stream, ximg, (size_t)ap.Kp);
   }
-  // The single pass reads the rows once but waits for its grid to meet
-  // (about 5 us); two passes read them twice, the second time from the L2s
-  // (32 MB).  Single against two passes, us: 10.9, 10.3 at 4096 x 768,
-  // 13.3, 9.8 at 301 x 4091, 8.9, 6.9 at 1024 x 1024; 21.4, 21.6 at 4096 x
-  // 3072, 24.6, 25.0 at 6272 x 2304.
-  const int64_t coop_min = act_coop_env() == 1 ? kCoopMinElems : kCoopFromElems;
-  if (vec && !sign && M * K >= coop_min) {
+  if (vec && !sign && M * K >= coop_from(M, K)) {
     hipError_t e = hipSuccess;
     if (launch_act_coop(A, M, K, lda, ap, pos4_dev, counter, s_a, packed, stream, e))
       return e;
   }
   int nparts;
   if (vec && M <= 16 * (int64_t)kAbsmaxBlocks) {
-    // rows per workgroup: enough workgroups for the CUs, within the partial
-    // buffer (2 rows 2.7 us against 3.5 with 8 at 301 x 4091; 4 rows 3.8
-    // against 5.2 with 2 at 4096 x 768)
+    // rows per workgroup: enough workgroups for the CUs, and few partial
+    // maxima for the second pass's workgroups to reduce, at most the buffer's
+    // (both passes, us, with 2, 4 and 8 rows: 9.5, 9.7, 10.2 at 301 x 4091;
+    // 4 and 8: 7.0, 7.1 at 1024 x 1024, 12.7, 12.8 at 2000 x 4095, 7.7, 7.4
+    // at 2048 x 1024, 9.2, 8.7 at 4096 x 768)
     const int K4 = (int)((K + 3) / 4);
-    const int RB = M <= 512 ? 2 : M <= 4 * (int64_t)kAbsmaxBlocks ? 4 : M <= 8 * (int64_t)kAbsmaxBlocks ? 8 : 16;
-    nparts = (int)((M + RB - 1) / RB);
+    const int RB = M <= 512 ? 2 : M < 2048 ? 4 : M <= 8 * (int64_t)kAbsmaxBlocks ? 8 : 16;
+    nparts = (int)xcd_grid(M, RB);
     const uchar4* s4 = reinterpret_cast<const uchar4*>(seg4_dev);
 #define SONIQ_ABSMAX(J_, RB_)                                                                      \
   hipLaunchKernelGGL((k_absmax_blk<J_, RB_>), dim3((unsigned)nparts), dim3(256), 0, stream, A, M,  \
@@ -5705,7 +5726,7 @@ hipError_t launch_act_quant(const float* A, int64_t M, int64_t K, int64_t lda,
     return launch_act_blk<false>(A, M, K, lda, ap, pos4_dev, partial, nparts, s_a, packed, stream);
 #define SONIQ_ACT_ROWS(R_, J_)                                                                  \
   hipLaunchKernelGGL((k_act_rows<R_, J_>),                                                      \
-                     dim3((unsigned)(R_ == 4 ? ((M + 127) / 128) * 32 : (M + R_ - 1) / R_)),    \
+                     dim3(R_ == 4 ? xcd_grid(M, 4) : (unsigned)((M + R_ - 1) / R_)),            \
                      dim3(256),                                                                 \
                      (size_t)R_ * ap.Kp, stream, A, M, K, lda, J_ ? pos4_dev : pos_dev,         \
                      J_ ? seg4_dev : seg_dev, ap, partial,                                      \
@@ -6471,9 +6492,9 @@ hipError_t launch_conv_img(const float* X, int64_t B, int64_t C, int64_t H, int6
 template <int CBL, int CBH>
 static void launch_gemm_conv_t(const GemmArgs& a, int64_t M, hipStream_t stream) {
   // two wave sets where the tiles leave a wave its SIMD to itself, as
-  // gemm_shape, and K is long enough to share: two sets against one, us: 8.6,
-  // 8.3 at 8 granules, 9.4, 9.0 at 12 (196 tiles); 10.2, 10.9 at 16, 15.3,
-  // 17.6 at 37
+  // gemm_shape, and K is long enough to share: two sets against one, us, at
+  // 196 tiles: 8.6, 8.3 at 8 granules, 9.4, 9.0 at 12; 10.2, 10.3 at 16, 15.3,
+  // 16.5 at 37
   const dim3 grid((unsigned)(((M + 63) / 64) * (a.wp.Np / kGemmBN)));
   if (grid.x <= 256 && a.wp.ngt > 12)
     hipLaunchKernelGGL((k_gemm<2, 4, 8, CBL, CBH, 2, gemm_conv_nst(CBH), 0, false, true, 2>), grid,

@@ -26,9 +26,11 @@ CASES = [  # (M, N, K, a_lo, a_hi, signed, lda pad, first element, group bits)
     (9, 64, 7291, 4, 8, True, 0, 2, 0),
     (7, 48, 510, 1, 8, True, 1, 0, 0),        # a sign group
     (70, 48, 509, 1, 4, True, 0, 1, 0),
-    (301, 96, 4091, 3, 6, False, 0, 0, 0),    # single pass
-    (1100, 64, 1001, 4, 8, True, 3, 1, 0),
-    (1030, 32, 770, 4, 8, False, 1, 0, 0),    # two-pass 8-row blocks
+    (301, 96, 4091, 3, 6, False, 0, 0, 0),    # two passes, two rows a workgroup in the first
+    (1100, 64, 1001, 4, 8, True, 3, 1, 0),    # four rows
+    (1030, 32, 770, 4, 8, False, 1, 0, 0),
+    (2050, 32, 513, 4, 8, True, 1, 1, 0),     # eight rows
+    (7169, 32, 149, 4, 8, False, 0, 3, 0),    # many short rows: the single pass
     (1, 48, 1027, 4, 8, True, 0, 1, 512),
     (8, 48, 4099, 4, 8, True, 1, 1, 512),
     (33, 48, 1981, 4, 8, True, 0, 3, 512),
@@ -67,12 +69,13 @@ def test_rows(c):
                                   oracle.epilogue_replay(racc, rs, s_w))
 
 
-@pytest.mark.parametrize("M", [63, 129, 513, 4097, 8193])
-def test_two_pass_rows_per_workgroup(M):
+@pytest.mark.parametrize("M", [63, 129, 513, 2047, 2049, 4097, 7169, 8193])
+def test_two_pass_rows_per_workgroup(M, monkeypatch):
     """Each row count of the first pass's workgroups (2, 4, 8, 16), with
     batches that end inside a workgroup and inside a 16-row block."""
     case = workloads.generic(M, 32, 1100, a_lo=3, a_hi=8, a_frac_lo=0.6, w_lo=2, w_hi=4, w_frac_lo=0.5,
                              a_signed=False, a_abs=True, seed=M, name="two_pass")
+    monkeypatch.setenv("SONIQ_ACT_COOP", "0")
     print(f"[gpu] two pass M={M}", flush=True)
     case["A"][M - 1, 7] = 9.0  # the last row holds both maxima
     case["A"][M - 1, 8] = 9.5
