@@ -3154,6 +3154,7 @@ __device__ __forceinline__ void qn_store(const GemmArgs& a, const uint8_t* qs, i
 // of one column block, so that an XCD reads its share of the weights once
 // (301 x 4099 x 4091: 23.5 against 19.6 us; 4096 x 2304 x 768, whose
 // activations are larger: 22.2 against 24.6 the other way).
+template <int BM>
 __device__ __forceinline__ int2 tile_at(const GemmArgs& a, int tile, int ntn) {
   const bool cols = a.xcd_tiles == 2;
   const int d = cols ? (int)((a.M + BM - 1) / BM) : ntn;
@@ -3175,7 +3176,6 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(KS > 1
 void k_gemm(GemmArgs a) {
   constexpr int BM = 32 * WFM;
   // Instances whose containers are all known take at least 24 KB slots at
-template <int BM>
   // 64-row tiles (three workgroups per CU still fit LDS), so narrow
   // operands get wide stages (gemm_group_wide).
   constexpr bool KNOWN = CA0 != 0 && (S == 1 || CA1 != 0) && CBL != 0 && CBH != 0;
@@ -4438,11 +4438,6 @@ __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* r
         if (a.acc && ci.n >= 0) a.acc[((int64_t)j * a.M + m) * a.N + ci.n] = t;
         w[c0] = __float_as_int(__fmul_rn((float)t, a.s_a[j]));
       }
-    }
-    gemv_store_out(a, ep, em, ci.n, __fmul_rn(y, ci.s_w));
-  } else {
-    const int* rr = red + em * kMmRow + en;
-    int r0 = 0, r1 = 0;
       __syncthreads();
     }
   }
@@ -4458,6 +4453,11 @@ __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* r
       for (int u = 0; u < 4; ++u)
         if (j + u < ld / 4)
           y = __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(y, v[u].x), v[u].y), v[u].z), v[u].w);
+    }
+    gemv_store_out(a, ep, em, ci.n, __fmul_rn(y, ci.s_w));
+  } else {
+    const int* rr = red + em * kMmRow + en;
+    int r0 = 0, r1 = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       r0 += rr[32 * w];
@@ -7061,10 +7061,13 @@ bool gemv_dense_fits(int64_t M, const ActPlan& ap) {
 // against 11.4 us from HBM, 4096 x 4096 5.8 against 9.2), and with fewer rows
 // where it saves nothing, as at 2 and 4 bits (1 x 11008 x 4096: 5.2 against 6.2;
 // 4 rows 5.6 against 7.7).  With 3/6-bit weights and up to 4 rows the dense
-// copy's fewer bytes decide (1 x 11008 x 4096: 8.4 against 7.6).
+// copy's fewer bytes decide (1 x 11008 x 4096: 8.4 against 7.6), and for one
+// row of 1- and 8-bit weights its sign decoding does, given enough blocks (1 x
+// 11008 x 4096: 6.5 against 5.8, 1 x 4096 x 11008 8.1, 7.3; 157 blocks 4.3, 4.8).
 bool gemv_dense_takes(int64_t M, const ActPlan& ap, const WPlan& wp, int64_t dense_bytes) {
   if (!gemv_dense_fits(M, ap)) return false;
   if (!gemv_nibble_plan(ap) || !gemv_fits(M, ap, wp)) return true;
+  if (M == 1 && wp.c_lo == 1 && wp.c_hi == 8 && wp.nblk > 256) return true;
   return M <= 4 && 20 * dense_bytes < 19 * (int64_t)wblk_off(wp, wp.nblk);
 }
 
