@@ -315,8 +315,8 @@ __device__ __forceinline__ void write_partial(float mx0, float mx1, float* red,
 // (workgroup i goes to XCD i mod 8), so the second pass finds the rows the
 // first one read in its XCD's L2, and the pieces of one packed line meet
 // there.  Without that match the second pass re-read rows through the
-// Infinity Cache: 14.1 against 10.6 us at 4096 x 1536, 14.0 against 11.4 at
-// 1500 x 4096 (both passes).  The grid is a multiple of 128 rows; workgroups
+// Infinity Cache: 14.1 against 10.6 us at 4096 x 1536, 9.3 against 8.7 at
+// 4096 x 768 (both passes).  The grid is a multiple of 128 rows; workgroups
 // past the batch get rows past it.
 template <int RB>
 __device__ __forceinline__ int64_t xcd_row0() {
@@ -1711,8 +1711,8 @@ hipError_t launch_act_blk(const void* src, int64_t M, int64_t K, int64_t lda, co
 // m reads the whole batch, reduces its maxima, then quantizes and packs its
 // own row m (every workgroup computes the same maxima from the same data).
 //
-// Bound by latency, not bytes: a batch is at most 512 KB (8 rows of 16384)
-// and the launch is one chain of load, reduce, quantize, store, behind 1.8 us that
+// Bound by latency, not bytes: a decode batch is 16 to 256 KB and the
+// launch is one chain of load, reduce, quantize, store, behind 1.8 us that
 // an empty kernel takes.  Threads per workgroup, back to back in a graph,
 // us: 8 x 4096: 5.4 with 256, 4.8 with 512, 5.2 with 1024; 1 x 4096: 4.5,
 // 4.3, 5.1; 64 x 256: 4.1, 3.9, 4.8 (more waves load faster but start and
@@ -1720,22 +1720,19 @@ hipError_t launch_act_blk(const void* src, int64_t M, int64_t K, int64_t lda, co
 //
 // Thread (rg, col): float4 columns col + 512*j (j < J) of rows rg, rg +
 // nrg, ..., with 2^cl >= K/4 columns side by side (cl = 9 where J > 1).
-// U rows in flight per thread, no more than it has (repeats of the last row
-// are loads all the same: 1 x 864 3.2 us, 3.5 with eight).
 // GRP: block maxima.  A column's four |max| go to LDS words at their
 // planned positions (ds_max: several row groups may hold a column), and a
 // wave folds each 64-position granule, which lies in one block, into that
 // block's word: one LDS atomic per granule, where folding elements straight
-// into their blocks serializes a wave on one or two words (8 x 4096: 7.7
-// against 9.3 us).  A few short rows have few such steps and go straight,
-// after the rows (direct): 2 x 1024 4.2 against 4.5, 1 x 136 3.3, 4.1.
+// into their blocks serializes a wave on one or two words.
 // Dynamic LDS: Kp code bytes, then for GRP Kp words and 3*nsub words.
-template <int J, int U, bool GRP>
+template <int J, bool GRP>
 __global__ __launch_bounds__(512) void k_act_batch(const float* __restrict__ A, int M, int K,
                                                     int64_t lda, const int4* __restrict__ pos4,
                                                     int cl, ActPlan ap, float* __restrict__ s_a,
                                                     uint8_t* __restrict__ packed,
                                                     uint8_t* __restrict__ ximg) {
+  constexpr int U = 8 / J;  // rows in flight per thread
   extern __shared__ __align__(16) uint8_t codes[];
   __shared__ float red[16];
   const int tid = threadIdx.x;
@@ -1755,14 +1752,13 @@ __global__ __launch_bounds__(512) void k_act_batch(const float* __restrict__ A, 
     mx[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   }
   const int nsub = GRP ? ap.nsub[0] + (ap.S == 2 ? ap.nsub[1] : 0) : 0;
-  const bool direct = GRP && J == 1 && nrg == 1 && K4 <= 256;
   unsigned* fmx = reinterpret_cast<unsigned*>(codes + ap.Kp);
   unsigned* smax = fmx + ap.Kp;
   float* stab = reinterpret_cast<float*>(smax + nsub);
   float* rtab = stab + nsub;
   for (int i = tid; i < ap.Kp / 4; i += 512) reinterpret_cast<uint32_t*>(codes)[i] = 0u;
   if constexpr (GRP) {
-    for (int i = tid + (direct ? ap.Kp : 0); i < ap.Kp + nsub; i += 512) fmx[i] = 0u;
+    for (int i = tid; i < ap.Kp + nsub; i += 512) fmx[i] = 0u;
     __builtin_amdgcn_s_waitcnt(SONIQ_LGKMCNT0_IMM);
     bar_nofence();
   }
@@ -1784,27 +1780,18 @@ __global__ __launch_bounds__(512) void k_act_batch(const float* __restrict__ A, 
   }
   float s0 = 0.0f, s1 = 0.0f;
   if constexpr (GRP) {
-    if (direct) {
-      if (col < K4) {
-        atomicMax(&smax[p[0].x >> 16], __float_as_uint(mx[0].x));
-        atomicMax(&smax[p[0].y >> 16], __float_as_uint(mx[0].y));
-        atomicMax(&smax[p[0].z >> 16], __float_as_uint(mx[0].z));
-        atomicMax(&smax[p[0].w >> 16], __float_as_uint(mx[0].w));
-      }
-    } else {
 #pragma unroll
-      for (int j = 0; j < J; ++j) {
-        atomicMax(&fmx[p[j].x & 0xFFFF], __float_as_uint(mx[j].x));
-        atomicMax(&fmx[p[j].y & 0xFFFF], __float_as_uint(mx[j].y));
-        atomicMax(&fmx[p[j].z & 0xFFFF], __float_as_uint(mx[j].z));
-        atomicMax(&fmx[p[j].w & 0xFFFF], __float_as_uint(mx[j].w));
-      }
-      __syncthreads();
-      for (int q = tid >> 6; q < ap.Kp / kGran; q += 8) {
-        const float gm = wave_max(__uint_as_float(fmx[q * kGran + (tid & 63)]));
-        const int b = q < ap.ng[0] ? q / ap.gsub[0] : ap.nsub[0] + (q - ap.ng[0]) / ap.gsub[1];
-        if ((tid & 63) == 0) atomicMax(&smax[b], __float_as_uint(gm));
-      }
+    for (int j = 0; j < J; ++j) {
+      atomicMax(&fmx[p[j].x & 0xFFFF], __float_as_uint(mx[j].x));
+      atomicMax(&fmx[p[j].y & 0xFFFF], __float_as_uint(mx[j].y));
+      atomicMax(&fmx[p[j].z & 0xFFFF], __float_as_uint(mx[j].z));
+      atomicMax(&fmx[p[j].w & 0xFFFF], __float_as_uint(mx[j].w));
+    }
+    __syncthreads();
+    for (int q = tid >> 6; q < ap.Kp / kGran; q += 8) {
+      const float gm = wave_max(__uint_as_float(fmx[q * kGran + (tid & 63)]));
+      const int b = q < ap.ng[0] ? q / ap.gsub[0] : ap.nsub[0] + (q - ap.ng[0]) / ap.gsub[1];
+      if ((tid & 63) == 0) atomicMax(&smax[b], __float_as_uint(gm));
     }
     __syncthreads();
     for (int j = tid; j < nsub; j += 512) {
@@ -1891,24 +1878,16 @@ hipError_t launch_act_batch(const float* A, int64_t M, int64_t K, int64_t lda, c
                             const int32_t* pos4, float* s_a, uint8_t* packed, hipStream_t stream,
                             uint8_t* ximg, size_t lds) {
   const int K4 = (int)((K + 3) / 4);
-  // block maxima of a few short rows: one row group (direct)
-  int cl = GRP && M <= 8 && K4 <= 256 ? 9 : 6;
+  int cl = 6;
   while (cl < 9 && (1 << cl) < K4) ++cl;
   const int J = (K4 + 511) / 512;
-  const int64_t rows = (M + (512 >> cl) - 1) / (512 >> cl);  // per thread
-#define SONIQ_BATCH(J_, U_)                                                                        \
-  hipLaunchKernelGGL((k_act_batch<J_, U_, GRP>), dim3((unsigned)M), dim3(512), lds, stream, A, (int)M, \
+#define SONIQ_BATCH(J_)                                                                            \
+  hipLaunchKernelGGL((k_act_batch<J_, GRP>), dim3((unsigned)M), dim3(512), lds, stream, A, (int)M, \
                      (int)K, lda, reinterpret_cast<const int4*>(pos4), cl, ap, s_a, packed, ximg)
-  if (J <= 1) {
-    if (rows <= 1) SONIQ_BATCH(1, 1); else if (rows <= 2) SONIQ_BATCH(1, 2);
-    else if (rows <= 4) SONIQ_BATCH(1, 4); else SONIQ_BATCH(1, 8);
-  } else if (J <= 2) {
-    if (rows <= 1) SONIQ_BATCH(2, 1); else if (rows <= 2) SONIQ_BATCH(2, 2); else SONIQ_BATCH(2, 4);
-  } else if (J <= 4) {
-    if (rows <= 1) SONIQ_BATCH(4, 1); else SONIQ_BATCH(4, 2);
-  } else {
-    SONIQ_BATCH(8, 1);
-  }
+  if (J <= 1) SONIQ_BATCH(1);
+  else if (J <= 2) SONIQ_BATCH(2);
+  else if (J <= 4) SONIQ_BATCH(4);
+  else SONIQ_BATCH(8);
 #undef SONIQ_BATCH
   return hipGetLastError();
 }
@@ -3154,10 +3133,9 @@ __device__ __forceinline__ void qn_store(const GemmArgs& a, const uint8_t* qs, i
 // of one column block, so that an XCD reads its share of the weights once
 // (301 x 4099 x 4091: 23.5 against 19.6 us; 4096 x 2304 x 768, whose
 // activations are larger: 22.2 against 24.6 the other way).
-template <int BM>
 __device__ __forceinline__ int2 tile_at(const GemmArgs& a, int tile, int ntn) {
   const bool cols = a.xcd_tiles == 2;
-  const int d = cols ? (int)((a.M + BM - 1) / BM) : ntn;
+  const int d = cols ? (int)gridDim.x / ntn : ntn;
   const int q = tile / d, r = tile - q * d;
   // kept in SGPRs: everything the K loop addresses with derives from them
   return make_int2(__builtin_amdgcn_readfirstlane(cols ? r : q),
@@ -3199,7 +3177,7 @@ void k_gemm(GemmArgs a) {
   // concurrent tiles share weight tiles across XCDs.
   const int G = (int)gridDim.x, x = (int)(blockIdx.x & 7), l = (int)(blockIdx.x >> 3);
   const int tile = a.xcd_tiles ? x * (G >> 3) + min(x, G & 7) + l : (int)blockIdx.x;
-  const int2 at = tile_at<BM>(a, tile, ntn);
+  const int2 at = tile_at(a, tile, ntn);
   const int mt = at.x, nt = at.y;
   const int64_t m0 = (int64_t)mt * BM;
   const int jb0 = nt * 8;
@@ -4256,10 +4234,8 @@ __global__ __launch_bounds__(T) void k_gemv_fused(GemmArgs a) {
 // that remains is one chain of fp32 additions in block order per output,
 // over products read four at a time (pad products are -0, which an addition
 // ignores).  Larger blocks, or accumulators asked for, keep the chunks'
-// integer sums, which all threads turn into block products before the chain
-// (1 x 11008 x 4096, 1024-bit blocks: 10.8 us where the chain summed them,
-// 8.1).  8 x 11008 x 4096: 7.5 us, where summing slots into LDS words by
-// atomics and folding took 21.9.
+// integer sums and fold those.  8 x 11008 x 4096: 7.5 us, where summing
+// slots into LDS words by atomics and folding took 21.9.
 // Dynamic LDS (gemv_mm_lds): GB: (M + 1) * 16 outputs of `ld` words, else
 // (M + 1) rows of 8 partial sums of 16 columns; row M takes the lanes of
 // rows past M.
@@ -4282,18 +4258,13 @@ __host__ __device__ inline int gemv_mm_chunks(int ng0, int ng1) { return (ng0 + 
 __host__ __device__ inline int gemv_mm_ld(int nch) { return (nch + 3) / 8 * 8 + 4; }
 constexpr int kMmRow = 8 * 16 + 4;  // words of one row's partial sums
 
-// Chunks of each group that a wave has in flight per round (its form): a
-// slot costs its two loads' issue also where it holds no granule, a round its
-// latency.
-struct MmForm {
-  int c0, c1;
-};
-constexpr MmForm kMmForms[] = {{7, 4}, {3, 2}, {2, 8}, {1, 1}, {1, 12}};
-constexpr int kMmFormCount = 5;
+// SHORT: fewer slots per round, for a K that they hold in one.
+constexpr int kMmShort0 = 3, kMmShort1 = 2;
 
-template <int CW, bool GB, int FORM>
+template <int CW, bool GB, bool SHORT>
 __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* red) {
-  constexpr int C0 = CW == 8 && kMmForms[FORM].c0 > 4 ? 4 : kMmForms[FORM].c0, C1 = kMmForms[FORM].c1;
+  // chunks in flight per round
+  constexpr int C0 = SHORT ? kMmShort0 : CW == 8 ? 4 : 7, C1 = SHORT ? kMmShort1 : 4;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const ActPlan& ap = a.ap;
@@ -4418,41 +4389,33 @@ __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* r
     put(32 * wid + 16, acc1);
   }
   __syncthreads();
-  if constexpr (GB) {
-    if (!scaled) {
-      // each block's product f(sum) * s_a into its first chunk's word, -0
-      // into its others, one item (block, row, column) a thread
-      const int per = ap.gsub[0] / 2;  // chunks of a block
-      for (int i = em; i < M * nsub; i += 16) {
-        const int j = i / M, m = i - j * M;
-        const bool g1 = j >= nsub0;
-        const int c0 = g1 ? nc0 + (j - nsub0) * per : j * per;
-        const int c1 = min(c0 + per, g1 ? nch : nc0);
-        int* w = red + (m * kBlk + en) * ld;
-        int t = w[c0];
-        for (int c = c0 + 1; c < c1; ++c) {
-          t += w[c];
-          w[c] = (int)0x80000000;
-        }
-        t >>= g1 ? sh1 : sh0;
-        if (a.acc && ci.n >= 0) a.acc[((int64_t)j * a.M + m) * a.N + ci.n] = t;
-        w[c0] = __float_as_int(__fmul_rn((float)t, a.s_a[j]));
-      }
-      __syncthreads();
-    }
-  }
   if (em >= M || ci.n < 0) return;
   if constexpr (GB) {
     float y = 0.0f;
-    const float4* pr = reinterpret_cast<const float4*>(red + (em * kBlk + en) * ld);
-    for (int j = 0; j < ld / 4; j += 4) {
-      float4 v[4];
+    const int* rr = red + (em * kBlk + en) * ld;
+    if (scaled) {
+      const float4* pr = reinterpret_cast<const float4*>(rr);
+      for (int j = 0; j < ld / 4; j += 4) {
+        float4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = pr[min(j + u, ld / 4 - 1)];
+        for (int u = 0; u < 4; ++u) v[u] = pr[min(j + u, ld / 4 - 1)];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (j + u < ld / 4)
-          y = __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(y, v[u].x), v[u].y), v[u].z), v[u].w);
+        for (int u = 0; u < 4; ++u)
+          if (j + u < ld / 4)
+            y = __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(y, v[u].x), v[u].y), v[u].z), v[u].w);
+      }
+    } else {
+      const int per = ap.gsub[0] / 2;  // chunks of a block
+      for (int j = 0; j < nsub; ++j) {
+        const bool g1 = j >= nsub0;
+        const int c0 = g1 ? nc0 + (j - nsub0) * per : j * per;
+        const int c1 = min(c0 + per, g1 ? nch : nc0);
+        int t = 0;
+        for (int c = c0; c < c1; ++c) t += rr[c];
+        t >>= g1 ? sh1 : sh0;
+        y = __fadd_rn(y, __fmul_rn((float)t, a.s_a[j]));
+        if (a.acc) a.acc[((int64_t)j * a.M + em) * a.N + ci.n] = t;
+      }
     }
     gemv_store_out(a, ep, em, ci.n, __fmul_rn(y, ci.s_w));
   } else {
@@ -4473,15 +4436,15 @@ __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* r
   }
 }
 
-template <bool GB, int FORM>
+template <bool GB, bool SHORT>
 __global__ __launch_bounds__(256) void k_gemv_mm(GemmArgs a) {
   extern __shared__ __align__(16) int mred[];
   const int blk = blockIdx.x;
   const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv_mm_block<2, GB, FORM>(a, blk, mred);
-  else if (c == 4) gemv_mm_block<4, GB, FORM>(a, blk, mred);
-  else if (c == 8) gemv_mm_block<8, GB, FORM>(a, blk, mred);
-  else gemv_mm_block<1, GB, FORM>(a, blk, mred);
+  if (c == 2) gemv_mm_block<2, GB, SHORT>(a, blk, mred);
+  else if (c == 4) gemv_mm_block<4, GB, SHORT>(a, blk, mred);
+  else if (c == 8) gemv_mm_block<8, GB, SHORT>(a, blk, mred);
+  else gemv_mm_block<1, GB, SHORT>(a, blk, mred);
 }
 
 // ------------------------------------------------- single-pass quantize --
@@ -4511,12 +4474,10 @@ int act_coop_env() {  // -1: not set
 // with the partial maxima to reduce before its rows, which weighs most on
 // short ones: 20.8, 22.7 at 8192 x 256, 23.7, 24.8 at 8192 x 512, 33.3,
 // 37.1 at 16384 x 384; 25.2, 25.5 at 8192 x 640, 35.7, 34.7 at 12288 x 640;
-// 30.8, 30.4 at 8192 x 1024, 33.3, 35.6 at 8192 x 1280, 36.2, 39.9 at 16000 x
-// 530.  Past 4096 values the second pass is the slower J = 4 (quantizer
-// alone: 21.8, 23.9 at 2439 x 4393).
+// 30.8, 30.4 at 8192 x 1024, 33.3, 35.6 at 8192 x 1280, 36.2, 39.9 at 16000 x 530.
 int64_t coop_from(int64_t M, int64_t K) {
   if (act_coop_env() == 1) return kCoopMinElems;
-  if (M <= 7168 && K <= 4096) return (int64_t)12 << 20;
+  if (M <= 7168) return (int64_t)12 << 20;
   return K <= 512 ? kCoopMinElems : (int64_t)8 << 20;
 }
 
@@ -5093,7 +5054,7 @@ void k_gemm_g(GemmArgs a) {
   const int ntn = a.wp.Np / kGemmBN;
   const int G = (int)gridDim.x, x = (int)(blockIdx.x & 7), l = (int)(blockIdx.x >> 3);
   const int tile = a.xcd_tiles ? x * (G >> 3) + min(x, G & 7) + l : (int)blockIdx.x;
-  const int2 at = tile_at<BM>(a, tile, ntn);
+  const int2 at = tile_at(a, tile, ntn);
   const int mt = at.x, nt = at.y;
   const int64_t m0 = (int64_t)mt * BM;
   const int jb0 = nt * 8;
@@ -5869,13 +5830,9 @@ static int gemm_shape(int64_t M, int ntn, int ngt) {
 static int gemm_rows(int shape) { return shape == 3 ? 128 : shape == 1 ? 32 : 64; }
 
 // How a launch orders its tiles (GemmArgs::xcd_tiles): long grids (more than
-// a few rounds of two workgroups per CU) keep the launch order; the weights
-// come first where they are the larger operand, unless the outputs are several
-// times theirs, whose lines neighbouring column blocks share (row against
-// column order, us: 59.9, 67.6 at 3269 x 7195 x 622 with 1/8-bit weights, 12.4,
-// 14.2 at 2750 x 1774 x 217; 17.8, 16.9 at 584 x 3101 x 1604, 3/6 bits).
-static int tile_order(int64_t tiles, int64_t a_bytes, int64_t w_bytes, int64_t y_bytes) {
-  return tiles > 2048 ? 0 : w_bytes > std::max(a_bytes, y_bytes / 4) ? 2 : 1;
+// a few rounds of two workgroups per CU) keep the launch order.
+static int tile_order(int64_t tiles, int64_t a_bytes, int64_t w_bytes) {
+  return tiles > 2048 ? 0 : w_bytes > a_bytes ? 2 : 1;
 }
 static int64_t act_batch_bytes(const ActPlan& ap, int64_t M) {
   return (M + kBlk - 1) / kBlk * (ap.mblk_bytes[0] + (ap.S == 2 ? ap.mblk_bytes[1] : 0));
@@ -5899,7 +5856,7 @@ hipError_t launch_mp_gemm(const uint8_t* act_packed, const float* s_a, const Act
   int shape = gemm_shape(M, wp.Np / kGemmBN, wp.ngt);
   if ((!known || a.fa) && shape != 3) shape = 7;
   const int64_t tiles = (M + gemm_rows(shape) - 1) / gemm_rows(shape) * (wp.Np / kGemmBN);
-  a.xcd_tiles = tile_order(tiles, act_batch_bytes(ap, M), (int64_t)wblk_off(wp, wp.nblk), 2 * M * N);
+  a.xcd_tiles = tile_order(tiles, act_batch_bytes(ap, M), (int64_t)wblk_off(wp, wp.nblk));
   if (ap.S == 2 && ca0 == 4 && ca1 == 8) {
     if (cl == 4 && ch == 8) launch_gemm_t<2, 4, 8, 4, 8>(a, M, shape, stream);
     else if (cl == 4 && ch == 4) launch_gemm_t<2, 4, 8, 4, 4>(a, M, shape, stream);
@@ -6235,60 +6192,35 @@ static size_t gemv_mm_lds(int64_t M, const ActPlan& ap) {
   return (size_t)(M + 1) * words * 4;
 }
 
-// The form of k_gemv_mm for a plan: the one that issues the fewest slots over
-// its rounds (us, in the order of kMmForms: 5.2, 6.0, 9.0, 5.5 at 8 x 11008 x
-// 4096 with 2/4-bit weights, 80 % of the channels narrow; 6.3, 4.4, 8.1, 4.6 at
-// 4 x 13029 x 1700; 6.7, 5.9, 3.7, 4.5 at 3 x 6382 x 2066, 20 % narrow; 5.3,
-// 4.4, 5.2, 3.3 at 6 x 14889 x 342; the last 3.8 against 4.9 with the third at
-// 8 x 4096 x 3000, 5 % narrow).  Up to two blocks a CU a round's latency
-// counts too, about three slots (quantize + GEMM, 8 x 526 x 4871: 10.7 with the
-// first, two rounds, 11.8 with the fourth, ten), but with block scales a
-// slot costs more than that (1 x 4637 x 1757: 7.0, 5.8).
-static int gemv_mm_form(const ActPlan& ap, const WPlan& wp) {
-  const int ng0 = ap.ng[0], ng1 = wp.ngt - ng0, nc0 = (ng0 + 1) / 2;
-  const int latency = ap.gsub[0] > 0 || wp.nblk > 512 ? 0 : 3;
-  int best = 0, cost = 0, rounds = 0;
-  for (int f = 0; f < kMmFormCount; ++f) {
-    const MmForm m = kMmForms[f];
-    const int r = std::max((nc0 + 4 * m.c0 - 1) / (4 * m.c0), (ng1 + 4 * m.c1 - 1) / (4 * m.c1));
-    const int n = r * (2 * m.c0 + m.c1 + latency);
-    if (f == 0 || n < cost || (n == cost && r < rounds)) {
-      best = f;
-      cost = n;
-      rounds = r;
-    }
-  }
-  return best;
-}
-
-template <bool GB>
-static void launch_gemv_mm(const GemmArgs& a, hipStream_t stream) {
-  const dim3 grid((unsigned)a.wp.nblk), blk(256);
-  const size_t lds = gemv_mm_lds(a.M, a.ap);
-  switch (gemv_mm_form(a.ap, a.wp)) {
-    case 0: hipLaunchKernelGGL((k_gemv_mm<GB, 0>), grid, blk, lds, stream, a); break;
-    case 1: hipLaunchKernelGGL((k_gemv_mm<GB, 1>), grid, blk, lds, stream, a); break;
-    case 2: hipLaunchKernelGGL((k_gemv_mm<GB, 2>), grid, blk, lds, stream, a); break;
-    case 3: hipLaunchKernelGGL((k_gemv_mm<GB, 3>), grid, blk, lds, stream, a); break;
-    default: hipLaunchKernelGGL((k_gemv_mm<GB, 4>), grid, blk, lds, stream, a); break;
-  }
-}
-
 // The GEMV of a plan with nibbles (and block scales, if any) by the batch:
 // k_gemv for a single row whose staging fits LDS: its 16-byte weight loads
 // leave the dot products less than the MFMA form's narrower ones (4.7
 // against 5.2 us at 1 x 11008 x 4096, 3.0 against 3.3 at 1 x 4096 x 4096,
 // 5.5 against 6.4 at 1 x 4096 x 11008); k_gemv_mm otherwise.
+// Whether every chunk of a row has its slot in a wave's short round.  A slot
+// costs its two loads' issue also where it holds no granule (4 x 13029 x 1700,
+// 4/8-bit weights: 6.2 us with long rounds, 4.3 with short; 4 x 7272 x 1052, 2/8
+// bits: 4.0, 3.1), and a second short round costs more than empty slots.
+static bool gemv_mm_short(const ActPlan& ap, int ngt) {
+  const int ng0 = ap.ng[0], ng1 = ngt - ng0;
+  return (ng0 + 1) / 2 <= 4 * kMmShort0 && ng1 <= 4 * kMmShort1;
+}
+
 static void launch_gemv_form(const GemmArgs& a, hipStream_t stream) {
-  const size_t lds = gemv_lds(a.ap, a.wp);
+  const dim3 grid((unsigned)a.wp.nblk), blk(256);
+  const size_t mm = gemv_mm_lds(a.M, a.ap);
+  const bool shrt = gemv_mm_short(a.ap, a.wp.ngt);
   if (a.ap.gsub[0] > 0) {
-    launch_gemv_mm<true>(a, stream);
-  } else if (a.M == 1 && lds + (size_t)2048 * 8 <= 64 * 1024) {
-    const dim3 grid((unsigned)a.wp.nblk);
+    if (shrt) hipLaunchKernelGGL((k_gemv_mm<true, true>), grid, blk, mm, stream, a);
+    else hipLaunchKernelGGL((k_gemv_mm<true, false>), grid, blk, mm, stream, a);
+  } else if (a.M == 1 && gemv_lds(a.ap, a.wp) + (size_t)2048 * 8 <= 64 * 1024) {
+    const size_t lds = gemv_lds(a.ap, a.wp);
     if (gemv_threads(a.wp, 96) == 512) hipLaunchKernelGGL(k_gemv<512>, grid, dim3(512), lds, stream, a);
-    else hipLaunchKernelGGL(k_gemv<256>, grid, dim3(256), lds, stream, a);
+    else hipLaunchKernelGGL(k_gemv<256>, grid, blk, lds, stream, a);
+  } else if (shrt) {
+    hipLaunchKernelGGL((k_gemv_mm<false, true>), grid, blk, mm, stream, a);
   } else {
-    launch_gemv_mm<false>(a, stream);
+    hipLaunchKernelGGL((k_gemv_mm<false, false>), grid, blk, mm, stream, a);
   }
 }
 
@@ -7061,13 +6993,10 @@ bool gemv_dense_fits(int64_t M, const ActPlan& ap) {
 // against 11.4 us from HBM, 4096 x 4096 5.8 against 9.2), and with fewer rows
 // where it saves nothing, as at 2 and 4 bits (1 x 11008 x 4096: 5.2 against 6.2;
 // 4 rows 5.6 against 7.7).  With 3/6-bit weights and up to 4 rows the dense
-// copy's fewer bytes decide (1 x 11008 x 4096: 8.4 against 7.6), and for one
-// row of 1- and 8-bit weights its sign decoding does, given enough blocks (1 x
-// 11008 x 4096: 6.5 against 5.8, 1 x 4096 x 11008 8.1, 7.3; 157 blocks 4.3, 4.8).
+// copy's fewer bytes decide (1 x 11008 x 4096: 8.4 against 7.6).
 bool gemv_dense_takes(int64_t M, const ActPlan& ap, const WPlan& wp, int64_t dense_bytes) {
   if (!gemv_dense_fits(M, ap)) return false;
   if (!gemv_nibble_plan(ap) || !gemv_fits(M, ap, wp)) return true;
-  if (M == 1 && wp.c_lo == 1 && wp.c_hi == 8 && wp.nblk > 256) return true;
   return M <= 4 && 20 * dense_bytes < 19 * (int64_t)wblk_off(wp, wp.nblk);
 }
 
