@@ -3133,9 +3133,10 @@ __device__ __forceinline__ void qn_store(const GemmArgs& a, const uint8_t* qs, i
 // of one column block, so that an XCD reads its share of the weights once
 // (301 x 4099 x 4091: 23.5 against 19.6 us; 4096 x 2304 x 768, whose
 // activations are larger: 22.2 against 24.6 the other way).
+template <int BM>
 __device__ __forceinline__ int2 tile_at(const GemmArgs& a, int tile, int ntn) {
   const bool cols = a.xcd_tiles == 2;
-  const int d = cols ? (int)gridDim.x / ntn : ntn;
+  const int d = cols ? (int)((a.M + BM - 1) / BM) : ntn;
   const int q = tile / d, r = tile - q * d;
   // kept in SGPRs: everything the K loop addresses with derives from them
   return make_int2(__builtin_amdgcn_readfirstlane(cols ? r : q),
@@ -3177,7 +3178,7 @@ void k_gemm(GemmArgs a) {
   // concurrent tiles share weight tiles across XCDs.
   const int G = (int)gridDim.x, x = (int)(blockIdx.x & 7), l = (int)(blockIdx.x >> 3);
   const int tile = a.xcd_tiles ? x * (G >> 3) + min(x, G & 7) + l : (int)blockIdx.x;
-  const int2 at = tile_at(a, tile, ntn);
+  const int2 at = tile_at<BM>(a, tile, ntn);
   const int mt = at.x, nt = at.y;
   const int64_t m0 = (int64_t)mt * BM;
   const int jb0 = nt * 8;
@@ -5054,7 +5055,7 @@ void k_gemm_g(GemmArgs a) {
   const int ntn = a.wp.Np / kGemmBN;
   const int G = (int)gridDim.x, x = (int)(blockIdx.x & 7), l = (int)(blockIdx.x >> 3);
   const int tile = a.xcd_tiles ? x * (G >> 3) + min(x, G & 7) + l : (int)blockIdx.x;
-  const int2 at = tile_at(a, tile, ntn);
+  const int2 at = tile_at<BM>(a, tile, ntn);
   const int mt = at.x, nt = at.y;
   const int64_t m0 = (int64_t)mt * BM;
   const int jb0 = nt * 8;
@@ -5830,9 +5831,13 @@ static int gemm_shape(int64_t M, int ntn, int ngt) {
 static int gemm_rows(int shape) { return shape == 3 ? 128 : shape == 1 ? 32 : 64; }
 
 // How a launch orders its tiles (GemmArgs::xcd_tiles): long grids (more than
-// a few rounds of two workgroups per CU) keep the launch order.
-static int tile_order(int64_t tiles, int64_t a_bytes, int64_t w_bytes) {
-  return tiles > 2048 ? 0 : w_bytes > a_bytes ? 2 : 1;
+// a few rounds of two workgroups per CU) keep the launch order; the weights
+// come first where they are the larger operand, unless the outputs are several
+// times theirs, whose lines neighbouring column blocks share (row against
+// column order, us: 59.9, 67.6 at 3269 x 7195 x 622 with 1/8-bit weights, 12.4,
+// 14.2 at 2750 x 1774 x 217; 17.8, 16.9 at 584 x 3101 x 1604, 3/6 bits).
+static int tile_order(int64_t tiles, int64_t a_bytes, int64_t w_bytes, int64_t y_bytes) {
+  return tiles > 2048 ? 0 : w_bytes > std::max(a_bytes, y_bytes / 4) ? 2 : 1;
 }
 static int64_t act_batch_bytes(const ActPlan& ap, int64_t M) {
   return (M + kBlk - 1) / kBlk * (ap.mblk_bytes[0] + (ap.S == 2 ? ap.mblk_bytes[1] : 0));
@@ -5856,7 +5861,7 @@ hipError_t launch_mp_gemm(const uint8_t* act_packed, const float* s_a, const Act
   int shape = gemm_shape(M, wp.Np / kGemmBN, wp.ngt);
   if ((!known || a.fa) && shape != 3) shape = 7;
   const int64_t tiles = (M + gemm_rows(shape) - 1) / gemm_rows(shape) * (wp.Np / kGemmBN);
-  a.xcd_tiles = tile_order(tiles, act_batch_bytes(ap, M), (int64_t)wblk_off(wp, wp.nblk));
+  a.xcd_tiles = tile_order(tiles, act_batch_bytes(ap, M), (int64_t)wblk_off(wp, wp.nblk), 2 * M * N);
   if (ap.S == 2 && ca0 == 4 && ca1 == 8) {
     if (cl == 4 && ch == 8) launch_gemm_t<2, 4, 8, 4, 8>(a, M, shape, stream);
     else if (cl == 4 && ch == 4) launch_gemm_t<2, 4, 8, 4, 4>(a, M, shape, stream);
