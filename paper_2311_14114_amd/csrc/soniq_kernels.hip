@@ -315,8 +315,8 @@ __device__ __forceinline__ void write_partial(float mx0, float mx1, float* red,
 // (workgroup i goes to XCD i mod 8), so the second pass finds the rows the
 // first one read in its XCD's L2, and the pieces of one packed line meet
 // there.  Without that match the second pass re-read rows through the
-// Infinity Cache: 14.1 against 10.6 us at 4096 x 1536, 9.3 against 8.7 at
-// 4096 x 768 (both passes).  The grid is a multiple of 128 rows; workgroups
+// Infinity Cache: 14.1 against 10.6 us at 4096 x 1536, 14.0 against 11.4 at
+// 1500 x 4096 (both passes).  The grid is a multiple of 128 rows; workgroups
 // past the batch get rows past it.
 template <int RB>
 __device__ __forceinline__ int64_t xcd_row0() {
@@ -4475,10 +4475,12 @@ int act_coop_env() {  // -1: not set
 // with the partial maxima to reduce before its rows, which weighs most on
 // short ones: 20.8, 22.7 at 8192 x 256, 23.7, 24.8 at 8192 x 512, 33.3,
 // 37.1 at 16384 x 384; 25.2, 25.5 at 8192 x 640, 35.7, 34.7 at 12288 x 640;
-// 30.8, 30.4 at 8192 x 1024, 33.3, 35.6 at 8192 x 1280, 36.2, 39.9 at 16000 x 530.
+// 30.8, 30.4 at 8192 x 1024, 33.3, 35.6 at 8192 x 1280, 36.2, 39.9 at 16000 x
+// 530.  Past 4096 values the second pass is the slower J = 4 (quantizer
+// alone: 21.8, 23.9 at 2439 x 4393).
 int64_t coop_from(int64_t M, int64_t K) {
   if (act_coop_env() == 1) return kCoopMinElems;
-  if (M <= 7168) return (int64_t)12 << 20;
+  if (M <= 7168 && K <= 4096) return (int64_t)12 << 20;
   return K <= 512 ? kCoopMinElems : (int64_t)8 << 20;
 }
 
