@@ -1711,8 +1711,8 @@ hipError_t launch_act_blk(const void* src, int64_t M, int64_t K, int64_t lda, co
 // m reads the whole batch, reduces its maxima, then quantizes and packs its
 // own row m (every workgroup computes the same maxima from the same data).
 //
-// Bound by latency, not bytes: a decode batch is 16 to 256 KB and the
-// launch is one chain of load, reduce, quantize, store, behind 1.8 us that
+// Bound by latency, not bytes: a batch is at most 512 KB (8 rows of 16384)
+// and the launch is one chain of load, reduce, quantize, store, behind 1.8 us that
 // an empty kernel takes.  Threads per workgroup, back to back in a graph,
 // us: 8 x 4096: 5.4 with 256, 4.8 with 512, 5.2 with 1024; 1 x 4096: 4.5,
 // 4.3, 5.1; 64 x 256: 4.1, 3.9, 4.8 (more waves load faster but start and
@@ -1720,19 +1720,22 @@ hipError_t launch_act_blk(const void* src, int64_t M, int64_t K, int64_t lda, co
 //
 // Thread (rg, col): float4 columns col + 512*j (j < J) of rows rg, rg +
 // nrg, ..., with 2^cl >= K/4 columns side by side (cl = 9 where J > 1).
+// U rows in flight per thread, no more than it has (repeats of the last row
+// are loads all the same: 1 x 864 3.2 us, 3.5 with eight).
 // GRP: block maxima.  A column's four |max| go to LDS words at their
 // planned positions (ds_max: several row groups may hold a column), and a
 // wave folds each 64-position granule, which lies in one block, into that
 // block's word: one LDS atomic per granule, where folding elements straight
-// into their blocks serializes a wave on one or two words.
+// into their blocks serializes a wave on one or two words (8 x 4096: 7.7
+// against 9.3 us).  A few short rows have few such steps and go straight,
+// after the rows (direct): 2 x 1024 4.2 against 4.5, 1 x 136 3.3, 4.1.
 // Dynamic LDS: Kp code bytes, then for GRP Kp words and 3*nsub words.
-template <int J, bool GRP>
+template <int J, int U, bool GRP>
 __global__ __launch_bounds__(512) void k_act_batch(const float* __restrict__ A, int M, int K,
                                                     int64_t lda, const int4* __restrict__ pos4,
                                                     int cl, ActPlan ap, float* __restrict__ s_a,
                                                     uint8_t* __restrict__ packed,
                                                     uint8_t* __restrict__ ximg) {
-  constexpr int U = 8 / J;  // rows in flight per thread
   extern __shared__ __align__(16) uint8_t codes[];
   __shared__ float red[16];
   const int tid = threadIdx.x;
@@ -1752,13 +1755,14 @@ __global__ __launch_bounds__(512) void k_act_batch(const float* __restrict__ A, 
     mx[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   }
   const int nsub = GRP ? ap.nsub[0] + (ap.S == 2 ? ap.nsub[1] : 0) : 0;
+  const bool direct = GRP && J == 1 && nrg == 1 && K4 <= 256;
   unsigned* fmx = reinterpret_cast<unsigned*>(codes + ap.Kp);
   unsigned* smax = fmx + ap.Kp;
   float* stab = reinterpret_cast<float*>(smax + nsub);
   float* rtab = stab + nsub;
   for (int i = tid; i < ap.Kp / 4; i += 512) reinterpret_cast<uint32_t*>(codes)[i] = 0u;
   if constexpr (GRP) {
-    for (int i = tid; i < ap.Kp + nsub; i += 512) fmx[i] = 0u;
+    for (int i = tid + (direct ? ap.Kp : 0); i < ap.Kp + nsub; i += 512) fmx[i] = 0u;
     __builtin_amdgcn_s_waitcnt(SONIQ_LGKMCNT0_IMM);
     bar_nofence();
   }
@@ -1780,18 +1784,27 @@ __global__ __launch_bounds__(512) void k_act_batch(const float* __restrict__ A, 
   }
   float s0 = 0.0f, s1 = 0.0f;
   if constexpr (GRP) {
+    if (direct) {
+      if (col < K4) {
+        atomicMax(&smax[p[0].x >> 16], __float_as_uint(mx[0].x));
+        atomicMax(&smax[p[0].y >> 16], __float_as_uint(mx[0].y));
+        atomicMax(&smax[p[0].z >> 16], __float_as_uint(mx[0].z));
+        atomicMax(&smax[p[0].w >> 16], __float_as_uint(mx[0].w));
+      }
+    } else {
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      atomicMax(&fmx[p[j].x & 0xFFFF], __float_as_uint(mx[j].x));
-      atomicMax(&fmx[p[j].y & 0xFFFF], __float_as_uint(mx[j].y));
-      atomicMax(&fmx[p[j].z & 0xFFFF], __float_as_uint(mx[j].z));
-      atomicMax(&fmx[p[j].w & 0xFFFF], __float_as_uint(mx[j].w));
-    }
-    __syncthreads();
-    for (int q = tid >> 6; q < ap.Kp / kGran; q += 8) {
-      const float gm = wave_max(__uint_as_float(fmx[q * kGran + (tid & 63)]));
-      const int b = q < ap.ng[0] ? q / ap.gsub[0] : ap.nsub[0] + (q - ap.ng[0]) / ap.gsub[1];
-      if ((tid & 63) == 0) atomicMax(&smax[b], __float_as_uint(gm));
+      for (int j = 0; j < J; ++j) {
+        atomicMax(&fmx[p[j].x & 0xFFFF], __float_as_uint(mx[j].x));
+        atomicMax(&fmx[p[j].y & 0xFFFF], __float_as_uint(mx[j].y));
+        atomicMax(&fmx[p[j].z & 0xFFFF], __float_as_uint(mx[j].z));
+        atomicMax(&fmx[p[j].w & 0xFFFF], __float_as_uint(mx[j].w));
+      }
+      __syncthreads();
+      for (int q = tid >> 6; q < ap.Kp / kGran; q += 8) {
+        const float gm = wave_max(__uint_as_float(fmx[q * kGran + (tid & 63)]));
+        const int b = q < ap.ng[0] ? q / ap.gsub[0] : ap.nsub[0] + (q - ap.ng[0]) / ap.gsub[1];
+        if ((tid & 63) == 0) atomicMax(&smax[b], __float_as_uint(gm));
+      }
     }
     __syncthreads();
     for (int j = tid; j < nsub; j += 512) {
@@ -1878,16 +1891,24 @@ hipError_t launch_act_batch(const float* A, int64_t M, int64_t K, int64_t lda, c
                             const int32_t* pos4, float* s_a, uint8_t* packed, hipStream_t stream,
                             uint8_t* ximg, size_t lds) {
   const int K4 = (int)((K + 3) / 4);
-  int cl = 6;
+  // block maxima of a few short rows: one row group (direct)
+  int cl = GRP && M <= 8 && K4 <= 256 ? 9 : 6;
   while (cl < 9 && (1 << cl) < K4) ++cl;
   const int J = (K4 + 511) / 512;
-#define SONIQ_BATCH(J_)                                                                            \
-  hipLaunchKernelGGL((k_act_batch<J_, GRP>), dim3((unsigned)M), dim3(512), lds, stream, A, (int)M, \
+  const int64_t rows = (M + (512 >> cl) - 1) / (512 >> cl);  // per thread
+#define SONIQ_BATCH(J_, U_)                                                                        \
+  hipLaunchKernelGGL((k_act_batch<J_, U_, GRP>), dim3((unsigned)M), dim3(512), lds, stream, A, (int)M, \
                      (int)K, lda, reinterpret_cast<const int4*>(pos4), cl, ap, s_a, packed, ximg)
-  if (J <= 1) SONIQ_BATCH(1);
-  else if (J <= 2) SONIQ_BATCH(2);
-  else if (J <= 4) SONIQ_BATCH(4);
-  else SONIQ_BATCH(8);
+  if (J <= 1) {
+    if (rows <= 1) SONIQ_BATCH(1, 1); else if (rows <= 2) SONIQ_BATCH(1, 2);
+    else if (rows <= 4) SONIQ_BATCH(1, 4); else SONIQ_BATCH(1, 8);
+  } else if (J <= 2) {
+    if (rows <= 1) SONIQ_BATCH(2, 1); else if (rows <= 2) SONIQ_BATCH(2, 2); else SONIQ_BATCH(2, 4);
+  } else if (J <= 4) {
+    if (rows <= 1) SONIQ_BATCH(4, 1); else SONIQ_BATCH(4, 2);
+  } else {
+    SONIQ_BATCH(8, 1);
+  }
 #undef SONIQ_BATCH
   return hipGetLastError();
 }

@@ -31,6 +31,16 @@ CASES = [  # (M, N, K, a_lo, a_hi, signed, lda pad, first element, group bits)
     (1030, 32, 770, 4, 8, False, 1, 0, 0),
     (2050, 32, 513, 4, 8, True, 1, 1, 0),     # eight rows
     (7169, 32, 149, 4, 8, False, 0, 3, 0),    # many short rows: the single pass
+    (2, 40, 1500, 4, 8, True, 0, 0, 0),       # small batches: two, four, one row in flight
+    (4, 40, 1902, 4, 8, False, 1, 1, 0),
+    (1, 40, 3001, 4, 8, True, 0, 0, 0),
+    (2, 40, 3001, 3, 6, True, 0, 2, 0),
+    (1, 40, 5000, 4, 8, True, 0, 0, 0),
+    (1, 48, 130, 4, 8, True, 0, 0, 512),      # block maxima of few short rows: the longest, and past it
+    (8, 48, 1024, 4, 8, True, 0, 0, 512),
+    (7, 48, 1023, 3, 6, False, 1, 1, 1024),
+    (8, 48, 1025, 4, 8, True, 0, 0, 512),
+    (9, 48, 500, 4, 8, True, 0, 0, 512),
     (1, 48, 1027, 4, 8, True, 0, 1, 512),
     (8, 48, 4099, 4, 8, True, 1, 1, 512),
     (33, 48, 1981, 4, 8, True, 0, 3, 512),
