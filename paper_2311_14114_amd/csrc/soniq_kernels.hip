@@ -4256,8 +4256,10 @@ __global__ __launch_bounds__(T) void k_gemv_fused(GemmArgs a) {
 // that remains is one chain of fp32 additions in block order per output,
 // over products read four at a time (pad products are -0, which an addition
 // ignores).  Larger blocks, or accumulators asked for, keep the chunks'
-// integer sums and fold those.  8 x 11008 x 4096: 7.5 us, where summing
-// slots into LDS words by atomics and folding took 21.9.
+// integer sums, which all threads turn into block products before the chain
+// (1 x 11008 x 4096, 1024-bit blocks: 10.8 us where the chain summed them,
+// 8.1).  8 x 11008 x 4096: 7.5 us, where summing slots into LDS words by
+// atomics and folding took 21.9.
 // Dynamic LDS (gemv_mm_lds): GB: (M + 1) * 16 outputs of `ld` words, else
 // (M + 1) rows of 8 partial sums of 16 columns; row M takes the lanes of
 // rows past M.
@@ -4411,33 +4413,41 @@ __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* r
     put(32 * wid + 16, acc1);
   }
   __syncthreads();
-  if (em >= M || ci.n < 0) return;
   if constexpr (GB) {
-    float y = 0.0f;
-    const int* rr = red + (em * kBlk + en) * ld;
-    if (scaled) {
-      const float4* pr = reinterpret_cast<const float4*>(rr);
-      for (int j = 0; j < ld / 4; j += 4) {
-        float4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = pr[min(j + u, ld / 4 - 1)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (j + u < ld / 4)
-            y = __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(y, v[u].x), v[u].y), v[u].z), v[u].w);
-      }
-    } else {
+    if (!scaled) {
+      // each block's product f(sum) * s_a into its first chunk's word, -0
+      // into its others, one item (block, row, column) a thread
       const int per = ap.gsub[0] / 2;  // chunks of a block
-      for (int j = 0; j < nsub; ++j) {
+      for (int i = em; i < M * nsub; i += 16) {
+        const int j = i / M, m = i - j * M;
         const bool g1 = j >= nsub0;
         const int c0 = g1 ? nc0 + (j - nsub0) * per : j * per;
         const int c1 = min(c0 + per, g1 ? nch : nc0);
-        int t = 0;
-        for (int c = c0; c < c1; ++c) t += rr[c];
+        int* w = red + (m * kBlk + en) * ld;
+        int t = w[c0];
+        for (int c = c0 + 1; c < c1; ++c) {
+          t += w[c];
+          w[c] = (int)0x80000000;
+        }
         t >>= g1 ? sh1 : sh0;
-        y = __fadd_rn(y, __fmul_rn((float)t, a.s_a[j]));
-        if (a.acc) a.acc[((int64_t)j * a.M + em) * a.N + ci.n] = t;
+        if (a.acc && ci.n >= 0) a.acc[((int64_t)j * a.M + m) * a.N + ci.n] = t;
+        w[c0] = __float_as_int(__fmul_rn((float)t, a.s_a[j]));
       }
+      __syncthreads();
+    }
+  }
+  if (em >= M || ci.n < 0) return;
+  if constexpr (GB) {
+    float y = 0.0f;
+    const float4* pr = reinterpret_cast<const float4*>(red + (em * kBlk + en) * ld);
+    for (int j = 0; j < ld / 4; j += 4) {
+      float4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = pr[min(j + u, ld / 4 - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j + u < ld / 4)
+          y = __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(y, v[u].x), v[u].y), v[u].z), v[u].w);
     }
     gemv_store_out(a, ep, em, ci.n, __fmul_rn(y, ci.s_w));
   } else {
