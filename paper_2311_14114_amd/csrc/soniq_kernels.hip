@@ -4282,13 +4282,18 @@ __host__ __device__ inline int gemv_mm_chunks(int ng0, int ng1) { return (ng0 + 
 __host__ __device__ inline int gemv_mm_ld(int nch) { return (nch + 3) / 8 * 8 + 4; }
 constexpr int kMmRow = 8 * 16 + 4;  // words of one row's partial sums
 
-// SHORT: fewer slots per round, for a K that they hold in one.
-constexpr int kMmShort0 = 3, kMmShort1 = 2;
+// Chunks of each group that a wave has in flight per round (its form): a
+// slot costs its two loads' issue also where it holds no granule, a round its
+// latency.
+struct MmForm {
+  int c0, c1;
+};
+constexpr MmForm kMmForms[] = {{7, 4}, {3, 2}, {2, 8}, {1, 1}, {1, 12}};
+constexpr int kMmFormCount = 5;
 
-template <int CW, bool GB, bool SHORT>
+template <int CW, bool GB, int FORM>
 __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* red) {
-  // chunks in flight per round
-  constexpr int C0 = SHORT ? kMmShort0 : CW == 8 ? 4 : 7, C1 = SHORT ? kMmShort1 : 4;
+  constexpr int C0 = CW == 8 && kMmForms[FORM].c0 > 4 ? 4 : kMmForms[FORM].c0, C1 = kMmForms[FORM].c1;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const ActPlan& ap = a.ap;
@@ -4468,15 +4473,15 @@ __device__ __forceinline__ void gemv_mm_block(const GemmArgs& a, int blk, int* r
   }
 }
 
-template <bool GB, bool SHORT>
+template <bool GB, int FORM>
 __global__ __launch_bounds__(256) void k_gemv_mm(GemmArgs a) {
   extern __shared__ __align__(16) int mred[];
   const int blk = blockIdx.x;
   const int c = wblk_c(a.wp, blk);
-  if (c == 2) gemv_mm_block<2, GB, SHORT>(a, blk, mred);
-  else if (c == 4) gemv_mm_block<4, GB, SHORT>(a, blk, mred);
-  else if (c == 8) gemv_mm_block<8, GB, SHORT>(a, blk, mred);
-  else gemv_mm_block<1, GB, SHORT>(a, blk, mred);
+  if (c == 2) gemv_mm_block<2, GB, FORM>(a, blk, mred);
+  else if (c == 4) gemv_mm_block<4, GB, FORM>(a, blk, mred);
+  else if (c == 8) gemv_mm_block<8, GB, FORM>(a, blk, mred);
+  else gemv_mm_block<1, GB, FORM>(a, blk, mred);
 }
 
 // ------------------------------------------------- single-pass quantize --
@@ -6230,35 +6235,60 @@ static size_t gemv_mm_lds(int64_t M, const ActPlan& ap) {
   return (size_t)(M + 1) * words * 4;
 }
 
+// The form of k_gemv_mm for a plan: the one that issues the fewest slots over
+// its rounds (us, in the order of kMmForms: 5.2, 6.0, 9.0, 5.5 at 8 x 11008 x
+// 4096 with 2/4-bit weights, 80 % of the channels narrow; 6.3, 4.4, 8.1, 4.6 at
+// 4 x 13029 x 1700; 6.7, 5.9, 3.7, 4.5 at 3 x 6382 x 2066, 20 % narrow; 5.3,
+// 4.4, 5.2, 3.3 at 6 x 14889 x 342; the last 3.8 against 4.9 with the third at
+// 8 x 4096 x 3000, 5 % narrow).  Up to two blocks a CU a round's latency
+// counts too, about three slots (quantize + GEMM, 8 x 526 x 4871: 10.7 with the
+// first, two rounds, 11.8 with the fourth, ten), but with block scales a
+// slot costs more than that (1 x 4637 x 1757: 7.0, 5.8).
+static int gemv_mm_form(const ActPlan& ap, const WPlan& wp) {
+  const int ng0 = ap.ng[0], ng1 = wp.ngt - ng0, nc0 = (ng0 + 1) / 2;
+  const int latency = ap.gsub[0] > 0 || wp.nblk > 512 ? 0 : 3;
+  int best = 0, cost = 0, rounds = 0;
+  for (int f = 0; f < kMmFormCount; ++f) {
+    const MmForm m = kMmForms[f];
+    const int r = std::max((nc0 + 4 * m.c0 - 1) / (4 * m.c0), (ng1 + 4 * m.c1 - 1) / (4 * m.c1));
+    const int n = r * (2 * m.c0 + m.c1 + latency);
+    if (f == 0 || n < cost || (n == cost && r < rounds)) {
+      best = f;
+      cost = n;
+      rounds = r;
+    }
+  }
+  return best;
+}
+
+template <bool GB>
+static void launch_gemv_mm(const GemmArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)a.wp.nblk), blk(256);
+  const size_t lds = gemv_mm_lds(a.M, a.ap);
+  switch (gemv_mm_form(a.ap, a.wp)) {
+    case 0: hipLaunchKernelGGL((k_gemv_mm<GB, 0>), grid, blk, lds, stream, a); break;
+    case 1: hipLaunchKernelGGL((k_gemv_mm<GB, 1>), grid, blk, lds, stream, a); break;
+    case 2: hipLaunchKernelGGL((k_gemv_mm<GB, 2>), grid, blk, lds, stream, a); break;
+    case 3: hipLaunchKernelGGL((k_gemv_mm<GB, 3>), grid, blk, lds, stream, a); break;
+    default: hipLaunchKernelGGL((k_gemv_mm<GB, 4>), grid, blk, lds, stream, a); break;
+  }
+}
+
 // The GEMV of a plan with nibbles (and block scales, if any) by the batch:
 // k_gemv for a single row whose staging fits LDS: its 16-byte weight loads
 // leave the dot products less than the MFMA form's narrower ones (4.7
 // against 5.2 us at 1 x 11008 x 4096, 3.0 against 3.3 at 1 x 4096 x 4096,
 // 5.5 against 6.4 at 1 x 4096 x 11008); k_gemv_mm otherwise.
-// Whether every chunk of a row has its slot in a wave's short round.  A slot
-// costs its two loads' issue also where it holds no granule (4 x 13029 x 1700,
-// 4/8-bit weights: 6.2 us with long rounds, 4.3 with short; 4 x 7272 x 1052, 2/8
-// bits: 4.0, 3.1), and a second short round costs more than empty slots.
-static bool gemv_mm_short(const ActPlan& ap, int ngt) {
-  const int ng0 = ap.ng[0], ng1 = ngt - ng0;
-  return (ng0 + 1) / 2 <= 4 * kMmShort0 && ng1 <= 4 * kMmShort1;
-}
-
 static void launch_gemv_form(const GemmArgs& a, hipStream_t stream) {
-  const dim3 grid((unsigned)a.wp.nblk), blk(256);
-  const size_t mm = gemv_mm_lds(a.M, a.ap);
-  const bool shrt = gemv_mm_short(a.ap, a.wp.ngt);
+  const size_t lds = gemv_lds(a.ap, a.wp);
   if (a.ap.gsub[0] > 0) {
-    if (shrt) hipLaunchKernelGGL((k_gemv_mm<true, true>), grid, blk, mm, stream, a);
-    else hipLaunchKernelGGL((k_gemv_mm<true, false>), grid, blk, mm, stream, a);
-  } else if (a.M == 1 && gemv_lds(a.ap, a.wp) + (size_t)2048 * 8 <= 64 * 1024) {
-    const size_t lds = gemv_lds(a.ap, a.wp);
+    launch_gemv_mm<true>(a, stream);
+  } else if (a.M == 1 && lds + (size_t)2048 * 8 <= 64 * 1024) {
+    const dim3 grid((unsigned)a.wp.nblk);
     if (gemv_threads(a.wp, 96) == 512) hipLaunchKernelGGL(k_gemv<512>, grid, dim3(512), lds, stream, a);
-    else hipLaunchKernelGGL(k_gemv<256>, grid, blk, lds, stream, a);
-  } else if (shrt) {
-    hipLaunchKernelGGL((k_gemv_mm<false, true>), grid, blk, mm, stream, a);
+    else hipLaunchKernelGGL(k_gemv<256>, grid, dim3(256), lds, stream, a);
   } else {
-    hipLaunchKernelGGL((k_gemv_mm<false, false>), grid, blk, mm, stream, a);
+    launch_gemv_mm<false>(a, stream);
   }
 }
 

@@ -35,6 +35,14 @@ CASES = [  # (M, N, K, a_lo, a_hi, a_frac, w_lo, w_hi, signed, group bits)
     (4, 40, 2000, 4, 8, 0.8, 2, 8, True, 512),
     (8, 40, 3711, 4, 8, 0.97, 4, 8, True, 512),       # an odd narrow granule count
     (8, 33, 11008, 4, 8, 0.8, 2, 4, True, 512),       # the most products that fit
+    (3, 40, 2066, 4, 8, 0.2, 1, 8, True, 0),          # wide rounds: 26 wide granules in one
+    (2, 40, 6650, 3, 6, 0.2, 2, 8, False, 0),         # and in three
+    (8, 40, 3000, 4, 8, 0.05, 4, 8, True, 0),         # 45 wide granules: the widest round
+    (5, 40, 3300, 4, 8, 0.02, 2, 4, True, 512),       # past it: 51
+    (4, 8300, 2420, 4, 8, 0.8, 2, 4, True, 0),        # several rounds of one chunk
+    (1, 40, 1757, 3, 6, 0.95, 3, 6, True, 1024),
+    (2, 40, 2000, 4, 8, 0.2, 1, 4, True, 1536),       # three chunks per block, partial last blocks
+    (8, 40, 1000, 4, 8, 0.5, 2, 8, True, 65536),      # one block a group
     (6, 40, 2500, 4, 8, 0.7, 2, 4, True, 1024),       # two chunks per block
     (3, 40, 5000, 3, 7, 0.7, 4, 4, False, 2048),      # four, unsigned
 ]
