@@ -7061,10 +7061,13 @@ bool gemv_dense_fits(int64_t M, const ActPlan& ap) {
 // against 11.4 us from HBM, 4096 x 4096 5.8 against 9.2), and with fewer rows
 // where it saves nothing, as at 2 and 4 bits (1 x 11008 x 4096: 5.2 against 6.2;
 // 4 rows 5.6 against 7.7).  With 3/6-bit weights and up to 4 rows the dense
-// copy's fewer bytes decide (1 x 11008 x 4096: 8.4 against 7.6).
+// copy's fewer bytes decide (1 x 11008 x 4096: 8.4 against 7.6), and for one
+// row of 1- and 8-bit weights its sign decoding does, given enough blocks (1 x
+// 11008 x 4096: 6.5 against 5.8, 1 x 4096 x 11008 8.1, 7.3; 157 blocks 4.3, 4.8).
 bool gemv_dense_takes(int64_t M, const ActPlan& ap, const WPlan& wp, int64_t dense_bytes) {
   if (!gemv_dense_fits(M, ap)) return false;
   if (!gemv_nibble_plan(ap) || !gemv_fits(M, ap, wp)) return true;
+  if (M == 1 && wp.c_lo == 1 && wp.c_hi == 8 && wp.nblk > 256) return true;
   return M <= 4 && 20 * dense_bytes < 19 * (int64_t)wblk_off(wp, wp.nblk);
 }
 
