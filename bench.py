@@ -66,7 +66,8 @@ def algorithmic(case, info):
         a_packed=act_packed,
         # the dense copy holds each weight in its own width; the container
         # layout rounds a width up to 1, 2, 4 or 8 bits
-        w_packed=(int(case["w_bits"].astype(np.int64).sum()) * K // 8 if case.get("dense")
+        w_packed=(int(case["w_bits"].astype(np.int64).sum()) * K // 8
+                  if case.get("dense") and dense_taken(case)
                   else int(info.packed_w_bytes_algorithmic)),
         # per output channel: scale and one code sum per activation group
         w_side=N * (4 + 4 * S),
@@ -87,10 +88,24 @@ def uses_gemv(case) -> bool:
     return case["M"] <= 8
 
 
+def dense_taken(case) -> bool:
+    """Whether a dense handle's batch reads the dense copy, as the library
+    chooses: always without a 4- and 8-bit activation plan, else up to 4 rows
+    where the copy is at least 5 % smaller than the containers (or one row of
+    1- and 8-bit weights)."""
+    if sorted({container(int(b)) for b in case["a_bits"]}) not in ([4], [4, 8]):
+        return True
+    own = int(case["w_bits"].astype(np.int64).sum())
+    units = sum(container(int(b)) for b in case["w_bits"])
+    if case["M"] == 1 and {container(int(b)) for b in case["w_bits"]} == {1, 8} and case["N"] > 4096:
+        return True
+    return case["M"] <= 4 and 20 * own < 19 * units
+
+
 def gemv_kernel(case) -> str:
     if case.get("act_group_bits", 0):
         return "k_gemv_mm"
-    if case.get("dense") and case["M"] <= 4:
+    if case.get("dense") and dense_taken(case):
         return "k_gemv_dense"
     return "k_gemv" if case["M"] == 1 else "k_gemv_mm"
 
@@ -219,7 +234,8 @@ def run_gpu(case, steps, warmup, rotate=True, graph=True, conv_input=False, f8f6
     # against.
     read_ms = None
     if M <= 8:
-        nbytes = int(info.dense_w_bytes if case.get("dense") else info.packed_w_bytes) // 16 * 16
+        dense = case.get("dense") and dense_taken(case)
+        nbytes = int(info.dense_w_bytes if dense else info.packed_w_bytes) // 16 * 16
         rbuf = torch.empty(ROTATE_W_BYTES, dtype=torch.uint8, device=dev)
         nsl = max(1, ROTATE_W_BYTES // nbytes) if rotate else 1
         sink = torch.empty((nbytes + 8191) // 8192, dtype=torch.int32, device=dev)

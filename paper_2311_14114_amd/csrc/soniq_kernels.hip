@@ -4487,10 +4487,10 @@ __global__ __launch_bounds__(256) void k_gemv_mm(GemmArgs a) {
 // ------------------------------------------------- single-pass quantize --
 // Batches of at least kCoopMinElems elements (without sub-group scales, of
 // coop_from's) whose rows fit the registers of one resident grid take
-// k_act_coop: RB rows per workgroup (4, 8 or 16,
-// the choice wasting the fewest register slots), T float4 per thread, and
-// at most as many workgroups as can be resident at once (by the occupancy
-// of k_act_coop<T> with this LDS size, times the CU count).
+// k_act_coop: RB rows per workgroup (4, 8 or 16, the choice wasting the
+// fewest register slots), T float4 per thread, and at most as many
+// workgroups as can be resident at once (by the occupancy of k_act_coop<T>
+// with this LDS size, kCoopPerCu at most, times the CU count).
 // SONIQ_ACT_COOP overrides the choice (0: never; 1: also for the smaller
 // batches without sub-group scales); results do not depend on it.
 constexpr int64_t kCoopMinElems = (int64_t)1 << 20;
