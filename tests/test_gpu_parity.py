@@ -445,11 +445,12 @@ def test_single_pass_wait_timeout(shape, monkeypatch):
     assert sq.soniq_act_wait_timeouts(g["act"]) == stalls
 
 
-@pytest.mark.parametrize("M,K,gbits", [(28672, 128, 0), (28688, 128, 0), (32768, 128, 512), (8192, 1088, 0)])
+@pytest.mark.parametrize("M,K,gbits", [(28672, 128, 0), (28688, 128, 0), (32768, 128, 512), (8192, 1088, 0),
+                                       (6272, 2304, 512)])
 def test_single_pass_grid_is_resident(M, K, gbits, monkeypatch):
     """Batches at and past the largest grid that a chip of 256 CUs runs at
-    once (7 workgroups of 16 or 4 rows a CU): no workgroup waits for one that has
-    not started.  The short spin limit bounds a wait that would fail."""
+    once (7 workgroups of 16 or 4 rows a CU, 6 where each takes 19 granules
+    of LDS): no workgroup waits for one that has not started.  The short spin limit bounds a wait that would fail."""
     monkeypatch.setenv("SONIQ_ACT_COOP", "1")
     monkeypatch.setenv("SONIQ_COOP_SPINS", "4000")
     print(f"[gpu] single pass grid M={M} K={K} g={gbits}", flush=True)
