@@ -99,8 +99,8 @@ enum { SONIQ_WQ_SYMMETRIC = 0, SONIQ_WQ_TWOS_FRACTION = 1 };
  * 16) + 32 <= 64 KiB, i.e. M * padded K up to about 52 K; larger batches
  * read the units) may read instead of the units: fewer bytes for the
  * weight-bound decode path.  With 8-and-4-bit activation groups they do
- * so up to 4 rows and where the copy is the smaller one; the units are
- * faster otherwise.  Sign (1-bit) weights against a sign
+ * so up to 4 rows and where the copy is the smaller one (and for one row
+ * of 1- and 8-bit weights); the units are faster otherwise.  Sign (1-bit) weights against a sign
  * activation group take XNOR-popcount products there (Sec. 4.2, Hardware
  * Support).  The channels of each 16-row block share one width (two widths
  * in one container are not merged into shared blocks).  Same codes and
